@@ -91,8 +91,19 @@ struct State {
     bool hist_loaded = false, geom_loaded = false;
     int n_mat = 0, n_pbin = 0;
     int64_t version = 0;  // bumped on every table change
-    DevBuf cdf, guide, totals, edges2, alias, blk, grid, nodes;
-    DevBuf box4, material, bfield, magnet, slab_z, slab_mask;
+    DevBuf cdf, guide, alias, nodes, image;
+    // host copies of the tables that every block stages in LDS (see build_image)
+    struct {
+        std::vector<double> e2, box4, slab_z, blk;
+        std::vector<uint32_t> totals;
+        std::vector<int32_t> material, magnet;
+        std::vector<float4> bfield;
+        std::vector<uint64_t> slab_mask, grid;
+        std::vector<mt::BoxRegion> box_region;
+        std::vector<mt::SlabRegion> slab_region;
+        std::vector<mt::BlockRegion> block_region;
+        std::vector<mt::BlockPlanes> block_planes;
+    } host;
     DevBuf map;
     DevBuf queue, partial, scratch, gs_lane, lists;
     Tables T{};
@@ -160,8 +171,9 @@ void tables_changed() {
     g.tuned.clear();
 }
 
-// LDS layout of the staged tables (depends on histogram and geometry sizes).
-void relayout() {
+// Layout and image of the tables staged in LDS (histogram and geometry parts,
+// whichever are loaded), uploaded as one block.
+int build_image() {
     mt::LdsLayout L{};
     int off = 0;
     auto take = [&](int bytes, int align) {
@@ -174,17 +186,63 @@ void relayout() {
     const int np = g.T.geom.n_poly;
     const int nh = g.T.hist.n_mat * P;
     L.off_e2 = take(8 * (P + 1), 16);
+    L.off_band = take(8 * (nh + 1), 16);
     L.off_tot = take(4 * nh, 16);
     L.off_box4 = take(np > 0 ? 0 : 32 * nb, 16);
-    L.off_blk = take(8 * mt::kBlockRec * np, 16);
     L.off_grid = take(np > 0 ? 8 * g.T.geom.gx * g.T.geom.gy * g.T.geom.gz : 0, 16);
+    L.off_planes = take(np > 0 ? (int)sizeof(mt::BlockPlanes) * (np + 1) : 0, 16);
     L.off_bf = take(16 * nb, 16);
     L.off_mat = take(4 * nb, 16);
     L.off_mag = take(4 * nb, 16);
     L.off_slabz = take(8 * (ns + 1), 16);
     L.off_slabm = take(8 * ns, 16);
+    L.off_breg = take(np > 0 ? 0 : (int)sizeof(mt::BoxRegion) * nb, 16);
+    L.off_sreg = take((int)sizeof(mt::SlabRegion) * ns, 16);
     L.bytes = (off + 15) / 16 * 16;
+    // not staged (read from memory beside a block's faces only)
+    L.off_blk = take(8 * mt::kBlockRec * np, 16);
+    L.off_preg = take((int)sizeof(mt::BlockRegion) * np, 16);
+    std::vector<unsigned char> img((size_t)(off + 15) / 16 * 16, 0);
+    auto put = [&](int o, const auto &v) {
+        if (!v.empty()) std::memcpy(img.data() + o, v.data(), v.size() * sizeof(v[0]));
+    };
+    const auto &H = g.host;
+    if (g.hist_loaded) {
+        put(L.off_e2, H.e2);
+        put(L.off_tot, H.totals);
+        // bands (see kBandLow); the kernels raise them to the run's threshold
+        std::vector<uint32_t> band(2 * ((size_t)nh + 1));
+        auto bits = [](float f) { uint32_t u; std::memcpy(&u, &f, 4); return u; };
+        for (int h = 0; h <= nh; ++h) {
+            const int i = h % P;
+            uint32_t lo = bits(mt::kBandLow), hi = 0x7f800000u;
+            if (h < nh && i > 0) lo = std::max(lo, bits((float)H.e2[(size_t)i]) + 1u);
+            if (h < nh && i < P - 1) hi = bits((float)H.e2[(size_t)i + 1]);
+            band[2 * (size_t)h] = lo;
+            band[2 * (size_t)h + 1] = hi > lo ? hi - lo : 0u;
+        }
+        put(L.off_band, band);
+    }
+    put(L.off_bf, H.bfield);
+    put(L.off_mat, H.material);
+    put(L.off_mag, H.magnet);
+    put(L.off_slabz, H.slab_z);
+    put(L.off_slabm, H.slab_mask);
+    if (np > 0) {
+        put(L.off_blk, H.blk);
+        put(L.off_grid, H.grid);
+        put(L.off_preg, H.block_region);
+        put(L.off_planes, H.block_planes);
+    } else {
+        put(L.off_box4, H.box4);
+        put(L.off_breg, H.box_region);
+        put(L.off_sreg, H.slab_region);
+    }
+    const int rc = g.image.upload(img.data(), img.size());
+    if (rc) return rc;
     g.T.lds = L;
+    g.T.image = reinterpret_cast<const uint4 *>(g.image.p);
+    return MT_OK;
 }
 
 std::vector<unsigned char> make_key(const void *a, size_t na, const void *b = nullptr,
@@ -649,14 +707,10 @@ int mt_load_histograms_ex(int32_t n_mat, int32_t n_pbin, const double *p_edges, 
     if ((rc = ensure_device())) return rc;
     if ((rc = g.cdf.upload(cdf.data(), cdf.size() * 4))) return rc;
     if ((rc = g.guide.upload(guide.data(), guide.size() * sizeof(uint2)))) return rc;
-    if ((rc = g.totals.upload(totals.data(), totals.size() * 4))) return rc;
-    if ((rc = g.edges2.upload(e2.data(), e2.size() * 8))) return rc;
     if ((rc = g.alias.upload(alias.data(), alias.size() * sizeof(uint2)))) return rc;
     mt::DevHist &H = g.T.hist;
     H.cdf = reinterpret_cast<const uint32_t *>(g.cdf.p);
     H.guide = reinterpret_cast<const uint2 *>(g.guide.p);
-    H.totals = reinterpret_cast<const uint32_t *>(g.totals.p);
-    H.edges2 = reinterpret_cast<const double *>(g.edges2.p);
     H.alias = reinterpret_cast<const uint2 *>(g.alias.p);
     H.n_mat = n_mat;
     H.n_pbin = n_pbin;
@@ -664,7 +718,8 @@ int mt_load_histograms_ex(int32_t n_mat, int32_t n_pbin, const double *p_edges, 
     H.n_scat = n_scat;
     H.n_cells = (int32_t)K;
     H.gbits = gbits;
-    H.nscat_magic = 0xFFFFFFFFu / (uint32_t)n_scat;
+    H.nscat_f = (float)n_scat;
+    H.nscat_inv = 1.0f / (float)n_scat;
     // axis origin and bin width in the axis' own units (log10 on a log axis)
     const double l0 = log_l ? std::log10(loss_lo) : loss_lo, l1 = log_l ? std::log10(loss_hi) : loss_hi;
     const double s0 = log_s ? std::log10(scat_lo) : scat_lo, s1 = log_s ? std::log10(scat_hi) : scat_hi;
@@ -677,9 +732,40 @@ int mt_load_histograms_ex(int32_t n_mat, int32_t n_pbin, const double *p_edges, 
     g.n_mat = n_mat;
     g.n_pbin = n_pbin;
     g.hist_loaded = true;
-    relayout();
+    g.host.e2 = std::move(e2);
+    g.host.totals = std::move(totals);
+    if ((rc = build_image())) return rc;
     tables_changed();
     return MT_OK;
+}
+
+// One axis of a region [lo, hi]: centre and 1 / half width.  The relative 2^-14
+// and the 1e-7 m cover the lanes' FP32 tracking over the steps between two
+// exact lookups and the FP64 rounding of coordinates up to 2^20 m; a narrower
+// or empty region gets a centre that is outside everything.
+static void region_axis(double lo, double hi, double *centre, float *inv) {
+    lo = std::max(lo, -1048576.0);
+    hi = std::min(hi, 1048576.0);
+    const double half = 0.5 * (hi - lo) * (1.0 - 0x1p-14) - 1e-7;
+    const bool ok = half > 1e-6;
+    *centre = ok ? 0.5 * (lo + hi) : 1e300;
+    *inv = ok ? (float)(1.0 / half) : 1.0f;
+}
+
+// z-slabs of volumes with z ranges zr = lo0, hi0, lo1, hi1, ...: the breaks
+// (with -inf and +inf at the ends) and, per slab, the volumes that span it.
+static void z_slabs(const std::vector<double> &zr, std::vector<double> &slab_z,
+                    std::vector<uint64_t> &mask) {
+    std::vector<double> zs(zr);
+    std::sort(zs.begin(), zs.end());
+    zs.erase(std::unique(zs.begin(), zs.end()), zs.end());
+    slab_z.assign(1, -std::numeric_limits<double>::infinity());
+    slab_z.insert(slab_z.end(), zs.begin(), zs.end());
+    slab_z.push_back(std::numeric_limits<double>::infinity());
+    mask.assign(slab_z.size() - 1, 0ull);
+    for (size_t s = 0; s < mask.size(); ++s)
+        for (size_t b = 0; b < zr.size() / 2; ++b)
+            if (zr[2 * b] <= slab_z[s] && slab_z[s + 1] <= zr[2 * b + 1]) mask[s] |= 1ull << b;
 }
 
 int mt_load_geometry(int32_t n_box, const double *box, const int32_t *material, const float *b_box,
@@ -732,43 +818,41 @@ int mt_load_geometry(int32_t n_box, const double *box, const int32_t *material, 
                           box[6 * b + 2 * ax] < box[6 * a + 2 * ax + 1];
             if (overlap) disjoint = false;
         }
-    std::sort(zs.begin(), zs.end());
-    zs.erase(std::unique(zs.begin(), zs.end()), zs.end());
     std::vector<double> slab_z;
-    slab_z.push_back(-std::numeric_limits<double>::infinity());
-    for (double z : zs) slab_z.push_back(z);
-    slab_z.push_back(std::numeric_limits<double>::infinity());
-    const int n_slab = (int)slab_z.size() - 1;
-    std::vector<uint64_t> mask((size_t)n_slab, 0ull);
+    std::vector<uint64_t> mask;
+    z_slabs(zs, slab_z, mask);
+    const int n_slab = (int)mask.size();
+    std::vector<mt::BoxRegion> breg((size_t)n_box);
+    std::vector<mt::SlabRegion> sreg((size_t)n_slab);
+    for (int b = 0; b < n_box; ++b) {
+        region_axis(std::max(box4[4 * b], -world[0]), std::min(box4[4 * b + 1], world[0]),
+                    &breg[b].xc, &breg[b].ix);
+        region_axis(std::max(box4[4 * b + 2], -world[1]), std::min(box4[4 * b + 3], world[1]),
+                    &breg[b].yc, &breg[b].iy);
+    }
     for (int s = 0; s < n_slab; ++s)
-        for (int b = 0; b < n_box; ++b)
-            if (box[6 * b + 4] <= slab_z[s] && slab_z[s + 1] <= box[6 * b + 5])
-                mask[s] |= 1ull << b;
+        region_axis(slab_z[s], std::min(slab_z[s + 1], world[2]), &sreg[s].zc, &sreg[s].iz);
     if ((rc = ensure_device())) return rc;
-    if ((rc = g.box4.upload(box4.data(), box4.size() * 8))) return rc;
-    if ((rc = g.bfield.upload(bf.data(), bf.size() * 16))) return rc;
-    if ((rc = g.material.upload(mat.data(), mat.size() * 4))) return rc;
-    if ((rc = g.magnet.upload(mag.data(), mag.size() * 4))) return rc;
-    if ((rc = g.slab_z.upload(slab_z.data(), slab_z.size() * 8))) return rc;
-    if ((rc = g.slab_mask.upload(mask.data(), mask.size() * 8))) return rc;
     mt::DevGeom &G = g.T.geom;
     G.n_box = n_box;
     G.n_poly = 0;
     G.n_slab = n_slab;
     G.n_mag = n_mag;
     G.disjoint = disjoint ? 1 : 0;
-    G.box4 = reinterpret_cast<const double *>(g.box4.p);
-    G.material = reinterpret_cast<const int32_t *>(g.material.p);
-    G.bfield = reinterpret_cast<const float4 *>(g.bfield.p);
-    G.magnet = reinterpret_cast<const int32_t *>(g.magnet.p);
-    G.slab_z = reinterpret_cast<const double *>(g.slab_z.p);
-    G.slab_mask = reinterpret_cast<const uint64_t *>(g.slab_mask.p);
+    g.host.box4 = std::move(box4);
+    g.host.bfield = std::move(bf);
+    g.host.material = std::move(mat);
+    g.host.magnet = std::move(mag);
+    g.host.slab_z = std::move(slab_z);
+    g.host.slab_mask = std::move(mask);
+    g.host.box_region = std::move(breg);
+    g.host.slab_region = std::move(sreg);
     G.x_max = world[0];
     G.y_max = world[1];
     G.z_max = world[2];
     g.max_material = max_mat;
     g.geom_loaded = true;
-    relayout();
+    if ((rc = build_image())) return rc;
     tables_changed();
     return MT_OK;
 }
@@ -934,6 +1018,91 @@ int mt_load_blocks(int32_t n, const double *block, const int32_t *material, cons
             rb[3] = ok ? sigma * tau : 0.0;
         }
     }
+    // Regions.  S_i is e_x (y - v_y) - e_y (x - v_x) with e and v linear in z, so
+    // over the block |dS_i| <= EY |dx| + EX |dy| + D |dz| with the largest
+    // |e_y|, |e_x| and |dS_i/dz|.  Each direction in which sigma S_i can fall
+    // may use slack_i / (EX + EY + K D), the z direction K times that (muons
+    // run along z).  err: the FP32 S_i of a point within ext of the centre is
+    // off by less than 2^-18 ext^2 (coordinates, vertices and products each
+    // rounded to 2^-24), and tau is far below that.
+    std::vector<mt::BlockRegion> preg((size_t)n);
+    std::vector<mt::BlockPlanes> planes((size_t)n + 1);
+    for (int b = 0; b < n; ++b) {
+        const double K = 16.0, *r = rec.data() + (size_t)mt::kBlockRec * b, *q = bb.data() + 6 * b;
+        mt::BlockRegion &R = preg[b];
+        const double sigma = (double)quad_orientation(block + 18 * b + 2);
+        const double ext = std::max(q[1] - q[0], q[3] - q[2]);
+        R.xc = 0.5 * (q[0] + q[1]);
+        R.yc = 0.5 * (q[2] + q[3]);
+        R.sigma = (float)sigma;
+        R.ext = (float)ext;
+        R.err = (float)(0x1p-16 * ext * ext);
+        R.tau = r[3] != 0.0 ? (float)(0x1p-16 * ext * ext + 2.0 * std::fabs(r[3])) : INFINITY;
+        for (int i = 0; i < 4; ++i) {
+            const int j = (i + 1) & 3;
+            R.bx[i] = (float)(r[4 + 2 * i] - R.xc);
+            R.by[i] = (float)(r[5 + 2 * i] - R.yc);
+            R.dx[i] = (float)r[12 + 2 * i];
+            R.dy[i] = (float)r[13 + 2 * i];
+            const double e0x = r[4 + 2 * j] - r[4 + 2 * i], e0y = r[5 + 2 * j] - r[5 + 2 * i];
+            const double dex = r[12 + 2 * j] - r[12 + 2 * i], dey = r[13 + 2 * j] - r[13 + 2 * i];
+            const double EX = std::max(std::fabs(e0x), std::fabs(e0x + dex));
+            const double EY = std::max(std::fabs(e0y), std::fabs(e0y + dey));
+            const double D = r[2] * (std::fabs(dex) * (q[3] - q[2]) + EX * std::fabs(r[13 + 2 * i]) +
+                                     std::fabs(dey) * (q[1] - q[0]) + EY * std::fabs(r[12 + 2 * i]));
+            const float c = (float)((1.0 - 1e-6) / (EX + EY + K * D)), none = 1e30f;
+            // dS/dx = -e_y, dS/dy = e_x: the direction in which sigma S falls
+            const bool up_y = std::min(sigma * e0x, sigma * (e0x + dex)) < 0.0;
+            const bool dn_y = std::max(sigma * e0x, sigma * (e0x + dex)) > 0.0;
+            const bool up_x = std::max(sigma * e0y, sigma * (e0y + dey)) > 0.0;
+            const bool dn_x = std::min(sigma * e0y, sigma * (e0y + dey)) < 0.0;
+            R.cxl[i] = dn_x ? c : none;
+            R.cxh[i] = up_x ? c : none;
+            R.cyl[i] = dn_y ? c : none;
+            R.cyh[i] = up_y ? c : none;
+            R.cz[i] = D > 0.0 ? (float)K * c : none;
+        }
+        // Planes: with parallel end edges S_i = |e| g_i, g_i linear in (x, y, z).
+        // The margin pays for kRegionSteps FP32 sums of the tracked position
+        // (2^-17 of the extent E on each axis), the rounding of g_i and tau.
+        mt::BlockPlanes &P = planes[b];
+        const double hz = 0.5 * (q[5] - q[4]), E = std::max(ext, hz);
+        bool plane = r[3] != 0.0 && q[5] <= world[2];
+        for (int a = 0; a < 6; ++a) plane = plane && std::fabs(q[a]) <= 1048576.0;
+        for (int a = 0; a < 4; ++a) plane = plane && std::fabs(q[a]) <= world[a / 2];
+        P.xc = R.xc;
+        P.yc = R.yc;
+        P.zc = 0.5 * (q[4] + q[5]);
+        P.err = 0.f;
+        for (int i = 0; i < 4; ++i) {
+            const int j = (i + 1) & 3;
+            const double e0x = r[4 + 2 * j] - r[4 + 2 * i], e0y = r[5 + 2 * j] - r[5 + 2 * i];
+            const double e1x = e0x + r[12 + 2 * j] - r[12 + 2 * i];
+            const double e1y = e0y + r[13 + 2 * j] - r[13 + 2 * i];
+            const double l0 = std::hypot(e0x, e0y), l1 = std::hypot(e1x, e1y);
+            plane = plane && std::fabs(e0x * e1y - e0y * e1x) <= 1e-12 * l0 * l1;
+            const double nx = -sigma * e0y / l0, ny = sigma * e0x / l0;   // inward
+            // vertex i at height z: its middle + z_rel * r[2] * (top - bottom)
+            const double mx = r[4 + 2 * i] + 0.5 * r[12 + 2 * i] - R.xc;
+            const double my = r[5 + 2 * i] + 0.5 * r[13 + 2 * i] - R.yc;
+            const double nz = -r[2] * (nx * r[12 + 2 * i] + ny * r[13 + 2 * i]);
+            const double err = 0x1p-15 * E * (2.0 + std::fabs(nz)) + 1e-7 +
+                               2.0 * std::fabs(r[3]) / std::min(l0, l1);
+            P.side[i] = make_float4((float)nx, (float)ny, (float)nz,
+                                    (float)(-(nx * mx + ny * my) - err));
+            P.err = std::max(P.err, (float)err);
+        }
+        P.hz = plane ? (float)(hz * (1.0 - 0x1p-14) - 1e-7) : -1.0f;
+        R.xlo = std::nextafter((float)q[0], -INFINITY);
+        R.xhi = std::nextafter((float)q[1], INFINITY);
+        R.ylo = std::nextafter((float)q[2], -INFINITY);
+        R.yhi = std::nextafter((float)q[3], INFINITY);
+    }
+    planes[n].side[0] = make_float4(1.f, 0.f, 0.f, 1.f);
+    planes[n].side[1] = make_float4(-1.f, 0.f, 0.f, 1.f);
+    planes[n].side[2] = make_float4(0.f, 1.f, 0.f, 1.f);
+    planes[n].side[3] = make_float4(0.f, -1.f, 0.f, 1.f);
+    planes[n].hz = 1.0f;
     // Grid: about kGridCells roughly cubic cells over the bounding box grown by
     // a margin far above the rounding of a cell index.
     double ext[3], eps = 0.0;
@@ -969,38 +1138,39 @@ int mt_load_blocks(int32_t n, const double *block, const int32_t *material, cons
                     grid[((size_t)k * dims[1] + j) * dims[0] + i] |= 1ull << b;
     }
     if ((rc = ensure_device())) return rc;
-    if ((rc = g.blk.upload(rec.data(), rec.size() * 8))) return rc;
-    if ((rc = g.grid.upload(grid.data(), grid.size() * 8))) return rc;
-    if ((rc = g.bfield.upload(bf.data(), bf.size() * 16))) return rc;
-    if ((rc = g.material.upload(mat.data(), mat.size() * 4))) return rc;
-    if ((rc = g.magnet.upload(mag.data(), mag.size() * 4))) return rc;
+    std::vector<double> zr;
+    for (int b = 0; b < n; ++b) {
+        zr.push_back(block[18 * b]);
+        zr.push_back(block[18 * b + 1]);
+    }
+    z_slabs(zr, g.host.slab_z, g.host.slab_mask);
     mt::DevGeom &G_ = g.T.geom;
     G_.n_box = n;
     G_.n_poly = n;
-    G_.n_slab = 0;
+    G_.n_slab = (int)g.host.slab_mask.size();
     G_.n_mag = n_mag;
     G_.disjoint = 0;
-    G_.box4 = nullptr;
-    G_.slab_z = nullptr;
-    G_.slab_mask = nullptr;
-    G_.poly = reinterpret_cast<const double *>(g.blk.p);
-    G_.grid = reinterpret_cast<const uint64_t *>(g.grid.p);
+    g.host.blk = std::move(rec);
+    g.host.grid = std::move(grid);
+    g.host.block_region = std::move(preg);
+    g.host.block_planes = std::move(planes);
+    g.host.bfield = std::move(bf);
+    g.host.material = std::move(mat);
+    g.host.magnet = std::move(mag);
     G_.gx = dims[0];
     G_.gy = dims[1];
     G_.gz = dims[2];
     for (int a = 0; a < 3; ++a) {
         G_.g0[a] = lo[a];
+        G_.g1[a] = hi[a];
         G_.ginv[a] = (double)dims[a] / ext[a];
     }
-    G_.material = reinterpret_cast<const int32_t *>(g.material.p);
-    G_.bfield = reinterpret_cast<const float4 *>(g.bfield.p);
-    G_.magnet = reinterpret_cast<const int32_t *>(g.magnet.p);
     G_.x_max = world[0];
     G_.y_max = world[1];
     G_.z_max = world[2];
     g.max_material = max_mat;
     g.geom_loaded = true;
-    relayout();
+    if ((rc = build_image())) return rc;
     tables_changed();
     return MT_OK;
 }
@@ -1290,10 +1460,10 @@ const char *mt_last_error(void) { return g_err.c_str(); }
 void mt_release(void) {
     std::lock_guard<std::mutex> lk(g.mu);
     drop_graphs();
-    for (DevBuf *b : {&g.cdf, &g.guide, &g.totals, &g.edges2, &g.alias, &g.blk, &g.grid, &g.nodes, &g.box4, &g.material, &g.bfield,
-                      &g.magnet, &g.slab_z, &g.slab_mask, &g.map, &g.queue, &g.partial,
+    for (DevBuf *b : {&g.cdf, &g.guide, &g.alias, &g.nodes, &g.image, &g.map, &g.queue, &g.partial,
                       &g.scratch, &g.gs_lane, &g.lists})
         b->release();
+    g.host = {};
     if (g.cap_stream) {
         (void)hipStreamDestroy(g.cap_stream);
         g.cap_stream = nullptr;

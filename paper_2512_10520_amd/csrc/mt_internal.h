@@ -24,34 +24,80 @@ constexpr int kGridCells = 1024;           // cells of the block grid (LDS-resid
 struct DevHist {
     const uint32_t *cdf;
     const uint2 *guide;          // [h][2^gbits]
-    const uint32_t *totals;      // [n_hist]
-    const double *edges2;        // [n_pbin + 1] squared momentum edges
     const uint2 *alias;          // [h][c] alias method: (24-bit threshold split, alias cell)
     int32_t n_mat, n_pbin, n_loss, n_scat, n_cells, gbits;
-    uint32_t nscat_magic;        // floor((2^32 - 1) / n_scat): c / n_scat = umulhi(c + 1, it),
-                                 // exact for n_scat >= 1 and c < 2^16
+    float nscat_f, nscat_inv;    // n_scat, 1 / n_scat
     float loss_lo, loss_w, scat_lo, scat_w;   // log10 units on a logarithmic axis
     int32_t log_loss, log_scat;  // axis binned uniformly in log10 of the value
 };
 
-// Geometry: boxes split into z-slabs.  Slab s covers [slab_z[s], slab_z[s+1])
+// Band of a momentum bin: the floats f for which float(|p|^2) = f proves that
+// |p|^2 lies in the bin (and, once a run has raised it, above its momentum
+// threshold).  Rounding to float is monotone, so f > float(a) gives |p|^2 > a
+// and f < float(b) gives |p|^2 < b; a lane whose f is on a rounded bound itself
+// decides in FP64.  Positive floats order as their bit patterns: a band is
+// (first pattern, number of patterns), and one subtraction and one unsigned
+// compare replace three FP64 compares.  Values below kBandLow, infinities and
+// NaN lie outside every band.  The band after the last histogram's is that of
+// a step outside every material.
+constexpr float kBandLow = 1e-30f;
+
+// Region of a box (x and y) and of a slab (z): centre and 1 / half width, the
+// half widths shrunk by more than a lane's FP32 tracking can be off (see the
+// kernels' struct Lane).  An axis without a usable region has a centre so far
+// away that no position is inside.
+struct BoxRegion {
+    double xc, yc;
+    float ix, iy;
+};
+
+struct SlabRegion {
+    double zc;
+    float iz, pad;
+};
+
+// A convex block in FP32 about the centre of its bounding box, for points that
+// are clear of its faces.  S_i formed in FP32 is off by less than err: a point
+// with sigma S_i < -err for some i is outside; one with the slack of edge i =
+// sigma S_i - tau > 0 for every i (tau >= err) is inside the block and in none
+// of lower index (see mt_load_blocks), and stays so while it moves by at most
+// cxl_i slack_i to the left, cxh_i slack_i to the right, cyl_i, cyh_i down and
+// up, and cz_i slack_i in z, for every i.
+struct BlockRegion {
+    double xc, yc;               // centre; vertices below are relative to it
+    float bx[4], by[4];          // at z_lo
+    float dx[4], dy[4];          // change from z_lo to z_hi
+    float cxl[4], cxh[4], cyl[4], cyh[4], cz[4];
+    float sigma;                 // vertex order +-1
+    float err, tau;              // tau = infinity: the block has no clear points
+    float ext;                   // largest lateral extent: |x - xc|, |y - yc| must be below it
+    float xlo, xhi, ylo, yhi;    // lateral bounding box, rounded outwards
+};
+
+// The sides of a block as planes about its centre (xc, yc, zc): a position
+// (x, y, z) relative to it with f_i = side[i].x x + side[i].y y + side[i].z z +
+// side[i].w > 0 for every i and |z| < hz is clear of the block's faces, as
+// classify_block's clear points are; one with f_i < -2 err for some i is
+// outside.  A block whose sides are not plane (end quads with edges that are
+// not parallel), one that is not clear of those before it and one that reaches
+// out of the world have none (hz = -1).  One more record, the unit box, serves
+// positions tracked in a region (see the kernels' Lane).
+struct BlockPlanes {
+    float4 side[4];
+    float hz, err, pad[2];
+    double xc, yc, zc, pad1;
+};
+
+// Geometry (its tables are in the staged image): boxes split into z-slabs.  Slab s covers [slab_z[s], slab_z[s+1])
 // with slab_z[0] = -inf and slab_z[n_slab] = +inf; slab_mask[s] has bit b set
 // when box b spans the whole slab in z, so inside the slab only the x and y
 // ranges of those boxes need testing, lowest index first.
 struct DevGeom {
     int32_t n_box, n_slab, n_mag;    // n_box: volumes (boxes or blocks)
     int32_t n_poly;              // > 0: the volumes are convex blocks
-    const double *poly;          // [n_poly][kBlockRec]
-    const uint64_t *grid;        // [gz][gy][gx] candidate masks of the block grid
     int32_t gx, gy, gz;
-    double g0[3], ginv[3];       // grid origin and cells per metre
+    double g0[3], g1[3], ginv[3];   // grid origin, end and cells per metre
     int32_t disjoint;            // no two boxes overlap: a box that holds a point is its box
-    const double *box4;          // [n_box][4] xlo, xhi, ylo, yhi
-    const int32_t *material;     // [n_box]
-    const float4 *bfield;        // [n_box] (bx, by, bz, 0)
-    const int32_t *magnet;       // [n_box]
-    const double *slab_z;        // [n_slab + 1]
-    const uint64_t *slab_mask;   // [n_slab]
     double x_max, y_max, z_max;
 };
 
@@ -67,10 +113,11 @@ struct DevField {
     double off[3];               // -lo (n - 1) / (hi - lo): u = x inv_d + off
 };
 
-// Byte offsets of the tables staged in LDS by every block.
+// Byte offsets of the tables every block stages in LDS: squared momentum
+// edges, the bands and totals of the histograms, and the geometry.
 struct LdsLayout {
-    int32_t off_e2, off_tot, off_box4, off_mat, off_bf, off_mag, off_slabz, off_slabm;
-    int32_t off_blk, off_grid;
+    int32_t off_e2, off_band, off_tot, off_box4, off_mat, off_bf, off_mag, off_slabz, off_slabm, off_breg, off_sreg;
+    int32_t off_blk, off_grid, off_preg, off_planes;
     int32_t bytes;
 };
 
@@ -101,6 +148,8 @@ struct DevIO {
 };
 
 struct Tables {
+    const uint4 *image;          // the staged tables as one block of lds.bytes (a multiple of 16),
+                                 // followed by the block records that are not staged
     DevHist hist;
     DevGeom geom;
     DevField field;
@@ -119,6 +168,15 @@ struct PassArgs {
     const int64_t *in;           // [*n_in] output slots to resume
     unsigned long long *n_out;   // slots appended by this pass (zeroed beforehand)
     int64_t *out;                // [lanes] at most
+};
+
+// The one argument of every transport kernel (the pass fields are used by the
+// compacting form only).
+struct KArgs {
+    Tables T;
+    DevRun R;
+    DevIO io;
+    PassArgs P;
 };
 
 // Launchers implemented in mt_kernels.hip.

@@ -103,10 +103,31 @@ __device__ __forceinline__ uint4 philox_step(const PhiloxPrefix &P, uint32_t ste
 }
 
 // ---------------------------------------------------------------------------
+// Kernel arguments read where they are used.  A step loop that keeps every
+// argument in scalar registers needs more than the 102 a wave has; the
+// compiler then parks them in vector-register lanes and reads each back with a
+// v_readlane (a vector instruction) on every step.  What only the cold paths
+// of a step need is therefore loaded there, from the kernel's argument segment
+// through a pointer the compiler cannot see through (cold): a scalar load of a
+// few cached words.  The argument of every transport kernel is one KArgs.
+// ---------------------------------------------------------------------------
+using ArgPtr = const __attribute__((address_space(4))) KArgs *;
+
+__device__ __forceinline__ ArgPtr kernel_args() {
+    return (ArgPtr)__builtin_amdgcn_kernarg_segment_ptr();
+}
+
+__device__ __forceinline__ ArgPtr cold(ArgPtr p) {
+    __asm__ volatile("" : "+s"(p));
+    return p;
+}
+
+// ---------------------------------------------------------------------------
 // Tables staged in LDS by every block.
 // ---------------------------------------------------------------------------
 struct Lds {
     const double *e2;
+    const uint2 *band;          // [n_hist + 1]: band of |p|^2 of every histogram, see kBandLow
     const uint32_t *tot;
     const double *box4;
     const int32_t *mat;
@@ -114,67 +135,120 @@ struct Lds {
     const int32_t *mag;
     const double *slabz;
     const uint64_t *slabm;
-    const double *blk;          // convex blocks [n_poly][kBlockRec]
+    const BoxRegion *breg;
+    const SlabRegion *sreg;
+    const double *blk;          // convex blocks [n_poly][kBlockRec], not staged
+    const BlockRegion *preg;    // [n_poly], not staged
+    const BlockPlanes *planes;
     const uint64_t *grid;       // block grid candidate masks
 };
 
-template <bool POLY>
-__device__ __forceinline__ Lds stage_tables(char *smem, const Tables &T) {
-    const LdsLayout &L = T.lds;
-    double *e2 = reinterpret_cast<double *>(smem + L.off_e2);
-    uint32_t *tot = reinterpret_cast<uint32_t *>(smem + L.off_tot);
-    double *box4 = reinterpret_cast<double *>(smem + L.off_box4);
-    int32_t *mat = reinterpret_cast<int32_t *>(smem + L.off_mat);
-    float4 *bf = reinterpret_cast<float4 *>(smem + L.off_bf);
-    int32_t *mag = reinterpret_cast<int32_t *>(smem + L.off_mag);
-    double *slabz = reinterpret_cast<double *>(smem + L.off_slabz);
-    uint64_t *slabm = reinterpret_cast<uint64_t *>(smem + L.off_slabm);
-    const int tid = threadIdx.x, nt = blockDim.x;
-    for (int i = tid; i <= T.hist.n_pbin; i += nt) e2[i] = T.hist.edges2[i];
-    const int nh = T.hist.n_mat * T.hist.n_pbin;
-    for (int i = tid; i < nh; i += nt) tot[i] = T.hist.totals[i];
-    for (int i = tid; i < T.geom.n_box; i += nt) {
-        mat[i] = T.geom.material[i];
-        bf[i] = T.geom.bfield[i];
-        mag[i] = T.geom.magnet[i];
-    }
-    double *blk = reinterpret_cast<double *>(smem + L.off_blk);
-    uint64_t *grid = reinterpret_cast<uint64_t *>(smem + L.off_grid);
-    if constexpr (POLY) {
-        for (int i = tid; i < kBlockRec * T.geom.n_poly; i += nt) blk[i] = T.geom.poly[i];
-        const int G = T.geom.gx * T.geom.gy * T.geom.gz;
-        for (int i = tid; i < G; i += nt) grid[i] = T.geom.grid[i];
-    } else {
-        for (int i = tid; i < 4 * T.geom.n_box; i += nt) box4[i] = T.geom.box4[i];
-        for (int i = tid; i <= T.geom.n_slab; i += nt) slabz[i] = T.geom.slab_z[i];
-        for (int i = tid; i < T.geom.n_slab; i += nt) slabm[i] = T.geom.slab_mask[i];
+__device__ __forceinline__ char *lds_base() {
+    extern __shared__ __align__(16) char smem[];
+    return smem;
+}
+
+// The staged tables of a layout.
+template <class TT>
+__device__ __forceinline__ Lds lds_view(const TT &T) {
+    const auto &L = T.lds;
+    char *smem = lds_base();
+    const char *image = reinterpret_cast<const char *>(T.image);
+    return Lds{reinterpret_cast<double *>(smem + L.off_e2),
+               reinterpret_cast<uint2 *>(smem + L.off_band),
+               reinterpret_cast<uint32_t *>(smem + L.off_tot),
+               reinterpret_cast<double *>(smem + L.off_box4),
+               reinterpret_cast<int32_t *>(smem + L.off_mat),
+               reinterpret_cast<float4 *>(smem + L.off_bf),
+               reinterpret_cast<int32_t *>(smem + L.off_mag),
+               reinterpret_cast<double *>(smem + L.off_slabz),
+               reinterpret_cast<uint64_t *>(smem + L.off_slabm),
+               reinterpret_cast<BoxRegion *>(smem + L.off_breg),
+               reinterpret_cast<SlabRegion *>(smem + L.off_sreg),
+               reinterpret_cast<const double *>(image + L.off_blk),
+               reinterpret_cast<const BlockRegion *>(image + L.off_preg),
+               reinterpret_cast<BlockPlanes *>(smem + L.off_planes),
+               reinterpret_cast<uint64_t *>(smem + L.off_grid)};
+}
+
+// Copies the image of the tables (one coalesced 16-byte load per thread and
+// trip, all in flight together) and raises the bands to the momentum threshold
+// of the run.
+__device__ __forceinline__ void stage_tables(const Tables &T, double pmin2) {
+    uint4 *dst = reinterpret_cast<uint4 *>(lds_base());
+    const int tid = threadIdx.x, nt = blockDim.x, n16 = T.lds.bytes / 16;
+    for (int i = tid; i < n16; i += nt) dst[i] = T.image[i];
+    __syncthreads();
+    uint2 *band = reinterpret_cast<uint2 *>(lds_base() + T.lds.off_band);
+    const uint32_t above = __float_as_uint((float)pmin2) + 1u;
+    for (int i = tid; i <= T.hist.n_mat * T.hist.n_pbin; i += nt) {
+        const uint2 b = band[i];
+        const uint32_t lo = max(b.x, above), hi = b.x + b.y;
+        band[i] = make_uint2(lo, hi > lo ? hi - lo : 0u);
     }
     __syncthreads();
-    return Lds{e2, tot, box4, mat, bf, mag, slabz, slabm, blk, grid};
 }
 
 // ---------------------------------------------------------------------------
-// Lane state.  Besides the muon, a lane caches what rarely changes from one
-// step to the next: the z-slab, the box, the momentum bin and the scaled
-// field of the box.  Cached values are the
-// same numbers a fresh lookup gives, so caching never changes a result.
+// Lane state.  Besides the muon, a lane keeps what rarely changes from one
+// step to the next: the volume, its field, its histogram and the momentum
+// band of the bin, and how far it may still travel before any of the FP64
+// tests of the loop could come out differently:
+//   xr, yr, zr  position relative to the centre of a box (the region), in
+//               units of its half widths, ix, iy, iz being 1 / half width:
+//               while max(|xr|, |yr|, |zr|) < 1 the position is inside the
+//               same volume and the world.
+// A step whose position is inside the region skips the volume lookup and the
+// break test; otherwise it repeats them in FP64 (locate_region) and forms the
+// region again, as every lane does at each step that is a multiple of
+// kRegionSteps.  The region is smaller than the true one by more than xr, yr,
+// zr can be off after that many FP32 sums, so a skipped test is one whose
+// outcome is known: results do not change.
+//
+// With convex blocks the box test is a test of four planes and |zr| (record
+// rec in LDS): for a lane in a block with plane sides the block's, with xr, yr,
+// zr in metres about the block's centre (ix = iy = iz = 1); for the others the
+// unit box.
 // ---------------------------------------------------------------------------
+constexpr int kRegionSteps = 128;              // steps a region is used for at most
+constexpr float kRegionHalf = 16.0f;           // its largest half width (m)
+constexpr double kRegionCoord = 1048576.0;     // |x|, |y|, |z| (m) up to which regions are used
+
 struct Lane {
     double x, y, z, px, py, pz;
-    double zlo, zhi;
-    double e2lo, e2hi;
-    float q;
-    float bx, by, bz;     // scaled field of box bvol
-    int32_t k, status, ibin, slab, vol, bvol, var;
+    float kq;             // kappa q
+    float xr, yr, zr, ix, iy, iz;
+    uint32_t rec;         // LDS byte offset of the BlockPlanes record (convex blocks)
+    uint32_t plo, pspan;  // band of float(|p|^2), see kBandLow
+    uint32_t hoff;        // the histogram's row in the sampler's table (see row_of), or kVacuum
+    uint32_t tot;         // the histogram's total (inverse CDF)
+    float bx, by, bz;     // scaled field of the volume (times kq in kernels without a map)
+    bool bent;            // that field is not zero
+    int32_t steps, status, slab, vol;
     PhiloxPrefix ph;
-    int64_t g;
-    int32_t mcell;        // field-map cell whose corner values are in mc (-1: none)
-    float mc[24];         // its 8 corners (bx, by, bz), corner order of the cell record
+    float ci, cj, ck;     // field-map cell (or node) whose values are in mc; NaN: none
+    float mc[24];         // its coefficients (bx, by, bz) x 8 (or the node's value)
 };
 
-// Lane state of output slot g = var * n + j (input muon j, variant var).
-__device__ __forceinline__ void load_lane_at(Lane &L, int64_t j, int64_t var, int64_t g,
-                                             const DevIO &io, const DevRun &R) {
+constexpr uint32_t kVacuum = 0xFFFFFFFFu;      // hoff outside every material
+
+__device__ __forceinline__ void reset_lane_caches(Lane &L) {
+    L.xr = L.yr = L.zr = 2.0f;
+    L.ix = L.iy = L.iz = 0.0f;
+    L.rec = 0u;
+    L.plo = L.pspan = 0u;
+    L.hoff = kVacuum;
+    L.tot = 0u;
+    L.slab = -1;
+    L.vol = -2;
+    L.bx = L.by = L.bz = 0.0f;
+    L.bent = false;
+    L.ci = L.cj = L.ck = __builtin_nanf("");
+}
+
+// Lane state of input muon j.
+__device__ __forceinline__ void load_lane_at(Lane &L, int64_t j, const DevIO &io,
+                                             const DevRun &R) {
     L.x = io.x[j];
     L.y = io.y[j];
     L.z = io.z[j];
@@ -182,21 +256,10 @@ __device__ __forceinline__ void load_lane_at(Lane &L, int64_t j, int64_t var, in
     L.py = io.py[j];
     L.pz = io.pz[j];
     const int qi = io.q[j];
-    L.q = (float)qi;
-    L.var = (int32_t)var;
+    L.kq = (float)kKappa * (float)qi;
     L.ph = philox_prefix((uint32_t)j, (uint32_t)((uint64_t)j >> 32), R.key0, R.key1);
-    L.g = g;
-    L.k = 0;
-    L.ibin = -1;
-    L.slab = -1;
-    L.vol = -1;
-    L.bvol = -2;
-    L.mcell = -1;
-    L.bx = L.by = L.bz = 0.0f;
-    L.zlo = INFINITY;
-    L.zhi = -INFINITY;
-    L.e2lo = INFINITY;
-    L.e2hi = -INFINITY;
+    L.steps = 0;
+    reset_lane_caches(L);
     L.status = MT_ST_RUNNING;
     const double p2 = L.px * L.px + L.py * L.py + L.pz * L.pz;
     const bool ok = isfinite(L.x) && isfinite(L.y) && isfinite(L.z) && isfinite(p2) &&
@@ -204,17 +267,16 @@ __device__ __forceinline__ void load_lane_at(Lane &L, int64_t j, int64_t var, in
     if (!ok) L.status = MT_ST_INVALID;
 }
 
+// Variant of output slot g = var * n + j.  Formed where it is needed (a new
+// volume's scaled field) rather than kept in a register.
+template <class RR>
+__device__ __forceinline__ int64_t variant_of(int64_t g, const RR &R) {
+    if (R.lanes == R.n) return 0;
+    return R.lanes <= 0xFFFFFFFFll ? (int64_t)((uint32_t)g / (uint32_t)R.n) : g / R.n;
+}
+
 __device__ __forceinline__ void load_lane(Lane &L, int64_t g, const DevIO &io, const DevRun &R) {
-    int64_t var = 0, j = g;
-    if (R.lanes != R.n) {
-        if (R.lanes <= 0xFFFFFFFFll) {
-            var = (uint32_t)g / (uint32_t)R.n;
-        } else {
-            var = g / R.n;
-        }
-        j = g - var * R.n;
-    }
-    load_lane_at(L, j, var, g, io, R);
+    load_lane_at(L, g - variant_of(g, R) * R.n, io, R);
 }
 
 // ---------------------------------------------------------------------------
@@ -253,100 +315,275 @@ __device__ __forceinline__ int find_box(const Lds &S, int s, double x, double y)
     return -1;
 }
 
-// Box containing the lane's position (lowest index), using the cached slab
-// and, for geometries without overlapping boxes, the cached box.
-__device__ __forceinline__ int locate(Lane &L, const Tables &T, const Lds &S) {
-    const bool same_slab = L.z >= L.zlo && L.z < L.zhi;
-    if (!same_slab) {
-        L.slab = find_slab(S, T.geom.n_slab, L.z, L.slab);
-        L.zlo = S.slabz[L.slab];
-        L.zhi = S.slabz[L.slab + 1];
-    } else if (L.vol >= 0 && T.geom.disjoint && in_box_xy(S, L.vol, L.x, L.y)) {
-        return L.vol;
+// Distances from the position to both ends of a region on every axis.  In
+// FP32 (the lookups around them are FP64): set_region takes off more than that
+// rounds.
+struct Region {
+    float xl, xh, yl, yh, zl, zh;
+};
+
+// Box containing the lane's position (lowest index).
+template <class TT>
+__device__ __forceinline__ int locate_box(Lane &L, const TT &T, const Lds &S) {
+    L.slab = find_slab(S, T.geom.n_slab, L.z, L.slab);
+    return find_box(S, L.slab, L.x, L.y);
+}
+
+// Region of the position from the tables: the loader keeps one of every slab
+// and, for geometries without overlapping boxes, of every box (within the
+// world).  Returns whether the position is inside it.
+template <class TT>
+__device__ __forceinline__ bool table_region(Lane &L, int vol, const TT &T, const Lds &S) {
+    if (vol < 0 || !T.geom.disjoint) return false;
+    const BoxRegion b = S.breg[vol];
+    const SlabRegion z = S.sreg[L.slab];
+    L.ix = b.ix;
+    L.iy = b.iy;
+    L.iz = z.iz;
+    L.xr = (float)(L.x - b.xc) * b.ix;
+    L.yr = (float)(L.y - b.yc) * b.iy;
+    L.zr = (float)(L.z - z.zc) * z.iz;
+    return fmaxf(fmaxf(fabsf(L.xr), fabsf(L.yr)), fabsf(L.zr)) < 1.0f;
+}
+
+// Region of a position in empty space, in overlapping boxes or beside a face:
+// in z the slab; laterally the box, no nearer than any candidate of lower
+// index (all of them in empty space).
+__device__ __forceinline__ Region box_region(const Lane &L, int vol, const Lds &S) {
+    Region r;
+    float gap = kRegionHalf;    // largest violated bound of the nearest candidate passed over
+    uint64_t c = S.slabm[L.slab];
+    while (c) {
+        const int b = __builtin_ctzll(c);
+        if (b == vol) break;
+        const double *bx = S.box4 + 4 * b;
+        gap = fminf(gap, fmaxf(fmaxf((float)(bx[0] - L.x), (float)(L.x - bx[1])),
+                               fmaxf((float)(bx[2] - L.y), (float)(L.y - bx[3]))));
+        c &= c - 1;
     }
-    L.vol = find_box(S, L.slab, L.x, L.y);
-    return L.vol;
+    r.xl = r.xh = r.yl = r.yh = gap;
+    if (vol >= 0) {
+        const double *bx = S.box4 + 4 * vol;
+        r.xl = fminf(gap, (float)(L.x - bx[0]));
+        r.xh = fminf(gap, (float)(bx[1] - L.x));
+        r.yl = fminf(gap, (float)(L.y - bx[2]));
+        r.yh = fminf(gap, (float)(bx[3] - L.y));
+    }
+    r.zl = fminf(kRegionHalf, (float)(L.z - S.slabz[L.slab]));
+    r.zh = fminf(kRegionHalf, (float)(S.slabz[L.slab + 1] - L.z));
+    return r;
+}
+
+// One axis of the region: relative position and 1 / half width.  The 2^-14
+// and the 1e-7 m pay for the rounding of the distances, of at most
+// kRegionSteps FP32 sums and of FP64 positions below kRegionCoord; a region
+// narrower than that is none (relative position 2).
+__device__ __forceinline__ void set_axis(float lo, float hi, bool use, float &rel, float &inv) {
+    const float half = fmaf(0.5f * (lo + hi), 1.0f - 0x1p-14f, -1e-7f);
+    const bool ok = use & (half > 1e-6f);
+    inv = ok ? __builtin_amdgcn_rcpf(half) : 0.0f;
+    rel = ok ? 0.5f * (lo - hi) * inv : 2.0f;
+}
+
+template <class GG>
+__device__ __forceinline__ void set_region(Lane &L, Region r, const GG &G) {
+    r.xl = fminf(r.xl, (float)(G.x_max + L.x));
+    r.xh = fminf(r.xh, (float)(G.x_max - L.x));
+    r.yl = fminf(r.yl, (float)(G.y_max + L.y));
+    r.yh = fminf(r.yh, (float)(G.y_max - L.y));
+    r.zh = fminf(r.zh, (float)(G.z_max - L.z));
+    const bool use = (fabs(L.x) <= kRegionCoord) & (fabs(L.y) <= kRegionCoord) &
+                     (fabs(L.z) <= kRegionCoord);
+    set_axis(r.xl, r.xh, use, L.xr, L.ix);
+    set_axis(r.yl, r.yh, use, L.yr, L.iy);
+    set_axis(r.zl, r.zh, use, L.zr, L.iz);
+}
+
+__device__ __forceinline__ bool outside_region(const Lane &L, int k) {
+    return (k % kRegionSteps == 0) |
+           !(fmaxf(fmaxf(fabsf(L.xr), fabsf(L.yr)), fabsf(L.zr)) < 1.0f);
+}
+
+// Least of the plane functions and hz - |zr|: positive inside.
+__device__ __forceinline__ float plane_slack(const BlockPlanes &b, float x, float y, float z) {
+    float f[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float4 p = b.side[i];
+        f[i] = fmaf(p.x, x, fmaf(p.y, y, fmaf(p.z, z, p.w)));
+    }
+    return fminf(fminf(fminf(f[0], f[1]), f[2]), fminf(f[3], b.hz - fabsf(z)));
+}
+
+__device__ __forceinline__ bool outside_planes(const Lane &L, int k) {
+    const BlockPlanes &b = *reinterpret_cast<const BlockPlanes *>(lds_base() + L.rec);
+    return (k % kRegionSteps == 0) | !(plane_slack(b, L.xr, L.yr, L.zr) > 0.0f);
+}
+
+__device__ __forceinline__ void move_in_region(Lane &L, float dx, float dy, float dz) {
+    L.xr = fmaf(dx, L.ix, L.xr);
+    L.yr = fmaf(dy, L.iy, L.yr);
+    L.zr = fmaf(dz, L.iz, L.zr);
 }
 
 // Convex block b holds (x, y, z): z_lo <= z < z_hi and the edge cross
-// products of the slice at z (Eq. (1)) all >= 0 or all <= 0.
+// products of the slice at z (Eq. (1)) all >= 0 or all <= 0.  Needed only
+// beside a face, so it is a loop over the edges with few registers.
 __device__ __forceinline__ bool in_block(const Lds &S, int b, double x, double y, double z) {
     const double *r = S.blk + kBlockRec * b;
     if (!(r[0] <= z && z < r[1])) return false;
     const double t = (z - r[0]) * r[2];
-    double vx[4], vy[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        vx[i] = fma(t, r[12 + 2 * i], r[4 + 2 * i]);
-        vy[i] = fma(t, r[13 + 2 * i], r[5 + 2 * i]);
-    }
     bool pos = true, neg = true;
-#pragma unroll
+#pragma unroll 1
     for (int i = 0; i < 4; ++i) {
         const int j = (i + 1) & 3;
-        const double si = (vx[j] - vx[i]) * (y - vy[i]) - (vy[j] - vy[i]) * (x - vx[i]);
+        const double vxi = fma(t, r[12 + 2 * i], r[4 + 2 * i]);
+        const double vyi = fma(t, r[13 + 2 * i], r[5 + 2 * i]);
+        const double vxj = fma(t, r[12 + 2 * j], r[4 + 2 * j]);
+        const double vyj = fma(t, r[13 + 2 * j], r[5 + 2 * j]);
+        const double si = (vxj - vxi) * (y - vyi) - (vyj - vyi) * (x - vxi);
         pos = pos && si >= 0.0;
         neg = neg && si <= 0.0;
     }
     return pos || neg;
 }
 
-// Is (x, y, z) inside block b with every edge product beyond the block's
-// margin (sigma S_i > tau, record word 3 = sigma tau, 0 = never)?  Then no
-// block of lower index holds the point (the loader checked that each of
-// them lies on the outer side of one of b's edge lines up to tau / 2).
-__device__ __forceinline__ bool in_block_clear(const Lds &S, int b, double x, double y, double z) {
-    const double *r = S.blk + kBlockRec * b;
-    const double m = r[3];
-    if (m == 0.0 || !(r[0] <= z && z < r[1])) return false;
-    const double t = (z - r[0]) * r[2];
-    double vx[4], vy[4];
+// Where the position lies with respect to block b, decided in FP32 with a
+// margin for its rounding (see BlockRegion): 1 inside and clear of the faces
+// (then no block of lower index holds it, and r is the region in which that
+// stays so), -1 outside, 0 too close to a face to say.
+__device__ __forceinline__ int classify_block(const Lds &S, int b, const Lane &L, Region &r) {
+    const BlockRegion &c = S.preg[b];
+    const double *q = S.blk + kBlockRec * b;
+    if (!(q[0] <= L.z && L.z < q[1])) return -1;
+    const float x = (float)(L.x - c.xc), y = (float)(L.y - c.yc);
+    const float zl = (float)(L.z - q[0]), zh = (float)(q[1] - L.z);
+    if (!(fmaxf(fabsf(x), fabsf(y)) < c.ext)) return -1;
+    const float t = zl * (float)q[2];
+    r = Region{kRegionHalf, kRegionHalf, kRegionHalf, kRegionHalf, zl, zh};
+    const float vx0 = fmaf(t, c.dx[0], c.bx[0]), vy0 = fmaf(t, c.dy[0], c.by[0]);
+    float vx = vx0, vy = vy0, least = INFINITY;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        vx[i] = fma(t, r[12 + 2 * i], r[4 + 2 * i]);
-        vy[i] = fma(t, r[13 + 2 * i], r[5 + 2 * i]);
+        const float wx = i == 3 ? vx0 : fmaf(t, c.dx[(i + 1) & 3], c.bx[(i + 1) & 3]);
+        const float wy = i == 3 ? vy0 : fmaf(t, c.dy[(i + 1) & 3], c.by[(i + 1) & 3]);
+        const float s = fmaf(wx - vx, y - vy, -((wy - vy) * (x - vx)));
+        const float side = c.sigma * s, slack = side - c.tau;
+        least = fminf(least, side);
+        r.xl = fminf(r.xl, slack * c.cxl[i]);
+        r.xh = fminf(r.xh, slack * c.cxh[i]);
+        r.yl = fminf(r.yl, slack * c.cyl[i]);
+        r.yh = fminf(r.yh, slack * c.cyh[i]);
+        r.zl = fminf(r.zl, slack * c.cz[i]);
+        r.zh = fminf(r.zh, slack * c.cz[i]);
+        vx = wx;
+        vy = wy;
     }
-    const double m2 = m * m;
-    bool clear = true;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int j = (i + 1) & 3;
-        const double si = (vx[j] - vx[i]) * (y - vy[i]) - (vy[j] - vy[i]) * (x - vx[i]);
-        clear = clear & (si * m > m2);
-    }
-    return clear;
+    return least > c.tau ? 1 : (least < -c.err ? -1 : 0);
 }
 
-// Lowest-index block holding the lane's position: the block of the previous
-// step if the point is clear inside it, else the grid cell's candidate mask,
-// then the sign test, lowest index first.
-__device__ __forceinline__ int locate_block(Lane &L, const Tables &T, const Lds &S) {
-    if (L.vol >= 0 && in_block_clear(S, L.vol, L.x, L.y, L.z)) return L.vol;
-    const DevGeom &G = T.geom;
+// Cuts r laterally so that it stays out of a rectangle, on the axis on which the
+// position is farther from it; leaves it no width if that is not outside.
+__device__ __forceinline__ void cut_region(Region &r, const Lane &L, double xlo, double xhi,
+                                           double ylo, double yhi) {
+    const float ax = (float)(xlo - L.x), bx = (float)(L.x - xhi);
+    const float ay = (float)(ylo - L.y), by = (float)(L.y - yhi);
+    const float gx = fmaxf(ax, bx), gy = fmaxf(ay, by);
+    if (gx > 0.0f && gx >= gy) {
+        if (ax > bx) r.xh = fminf(r.xh, gx); else r.xl = fminf(r.xl, gx);
+    } else if (gy > 0.0f) {
+        if (ay > by) r.yh = fminf(r.yh, gy); else r.yl = fminf(r.yl, gy);
+    } else {
+        r.yl = r.yh = 0.0f;
+    }
+}
+
+// Lowest-index block holding the lane's position.  In turn the block found last
+// and the candidates (those of the grid cell that span the z-slab) are
+// classified in FP32, by their planes where they have any; a clear one is the
+// answer.  Only if none is and some cannot be told apart the exact sign test
+// decides, lowest index first.  known: the answer is a block whose planes track
+// the lane from here (the position is inside the world too).  Otherwise r: a
+// region in which the answer stays, or one of no width (beside a face).  In
+// empty space that is the slab, laterally without limit where no block spans
+// it, else the grid cell (or the space beside the grid) without the bounding
+// boxes of the candidates.
+template <class TT>
+__device__ __forceinline__ int locate_block(Lane &L, const TT &T, const Lds &S, Region &r,
+                                            bool &known) {
+    const auto &G = T.geom;
+    const int sl = find_slab(S, G.n_slab, L.z, L.slab);
+    L.slab = sl;
+    const uint64_t in_slab = S.slabm[sl];
     const double u = (L.x - G.g0[0]) * G.ginv[0];
     const double v = (L.y - G.g0[1]) * G.ginv[1];
     const double w = (L.z - G.g0[2]) * G.ginv[2];
-    int vol = -1;
-    if (u >= 0.0 && v >= 0.0 && w >= 0.0 && u < (double)G.gx && v < (double)G.gy &&
-        w < (double)G.gz) {
-        uint64_t m = S.grid[((int)w * G.gy + (int)v) * G.gx + (int)u];
-        while (m) {
-            const int b = __builtin_ctzll(m);
-            if (in_block(S, b, L.x, L.y, L.z)) {
-                vol = b;
-                break;
+    const bool in_grid = u >= 0.0 && v >= 0.0 && w >= 0.0 && u < (double)G.gx &&
+                         v < (double)G.gy && w < (double)G.gz;
+    const int cu = (int)u, cv = (int)v, cw = (int)w;
+    uint64_t mask = 0;
+    if (in_grid && in_slab != 0) mask = S.grid[(cw * G.gy + cv) * G.gx + cu] & in_slab;
+    bool unsure = false;
+    uint64_t m = mask;
+    int b = L.vol >= 0 && ((in_slab >> L.vol) & 1) ? L.vol : -1;
+    for (;;) {
+        if (b >= 0) {
+            const BlockPlanes &P = S.planes[b];
+            const float x = (float)(L.x - P.xc), y = (float)(L.y - P.yc), z = (float)(L.z - P.zc);
+            const float slack = plane_slack(P, x, y, z);
+            if (slack > 0.0f) {
+                L.rec = (uint32_t)T.lds.off_planes + (uint32_t)sizeof(BlockPlanes) * (uint32_t)b;
+                L.ix = L.iy = L.iz = 1.0f;
+                L.xr = x;
+                L.yr = y;
+                L.zr = z;
+                known = true;
+                return b;
             }
-            m &= m - 1;
+            // (a block of the slab spans z: a point outside is beside a plane)
+            if (P.hz < 0.0f || !(slack < -2.0f * P.err)) {
+                const int side = classify_block(S, b, L, r);
+                if (side > 0) return b;
+                unsure |= side == 0;
+            }
         }
+        if (m == 0) break;
+        b = __builtin_ctzll(m);
+        m &= m - 1;
     }
-    L.vol = vol;
-    return vol;
+    if (unsure) {
+        r = Region{0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        for (m = mask; m; m &= m - 1) {
+            b = __builtin_ctzll(m);
+            if (in_block(S, b, L.x, L.y, L.z)) return b;
+        }
+        return -1;
+    }
+    r = Region{kRegionHalf, kRegionHalf, kRegionHalf, kRegionHalf,
+               fminf(kRegionHalf, (float)(L.z - S.slabz[sl])),
+               fminf(kRegionHalf, (float)(S.slabz[sl + 1] - L.z))};
+    if (in_slab == 0) return -1;
+    if (!in_grid) {
+        cut_region(r, L, G.g0[0], G.g1[0], G.g0[1], G.g1[1]);
+        return -1;
+    }
+    const float fx = (float)(u - (double)cu), fy = (float)(v - (double)cv);
+    const float cx = __builtin_amdgcn_rcpf((float)G.ginv[0]);
+    const float cy = __builtin_amdgcn_rcpf((float)G.ginv[1]);
+    const float cz = __builtin_amdgcn_rcpf((float)G.ginv[2]), fz = (float)(w - (double)cw);
+    r = Region{fx * cx, (1.0f - fx) * cx, fy * cy, (1.0f - fy) * cy,
+               fminf(r.zl, fz * cz), fminf(r.zh, (1.0f - fz) * cz)};
+    for (m = mask; m; m &= m - 1) {
+        const BlockRegion &c = S.preg[__builtin_ctzll(m)];
+        cut_region(r, L, (double)c.xlo, (double)c.xhi, (double)c.ylo, (double)c.yhi);
+    }
+    return -1;
 }
 
 // Momentum bin i with e_i^2 <= |p|^2 < e_{i+1}^2, clamped to [0, P-1]; the
 // previous step's bin is the starting guess.
 __device__ __forceinline__ int find_bin(const Lds &S, int P, double p2, int i) {
-    if (i < 0) {
+    if (i <= 0) {
         int lo = 0, hi = P - 1;
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
@@ -359,34 +596,26 @@ __device__ __forceinline__ int find_bin(const Lds &S, int P, double p2, int i) {
     return i;
 }
 
-__device__ __forceinline__ int bin_of(Lane &L, const Tables &T, const Lds &S, double p2) {
-    if (!(p2 >= L.e2lo && p2 < L.e2hi)) {
-        const int P = T.hist.n_pbin;
-        const int i = find_bin(S, P, p2, L.ibin);
-        L.ibin = i;
-        L.e2lo = i > 0 ? S.e2[i] : -INFINITY;
-        L.e2hi = i < P - 1 ? S.e2[i + 1] : INFINITY;
-    }
-    return L.ibin;
-}
-
 // Exact inverse CDF: t = floor(w * T / 2^32), cell = smallest c with C[c] > t.
 // The guide entry of the word's top bits brackets c in [lo, hi] and carries
 // C[lo]: t < C[lo] gives lo at once, a bracket of two cells gives hi, and only
 // wider brackets probe C.
-__device__ __forceinline__ int sample_cell(const DevHist &H, const Lds &S, int h, uint32_t w0) {
-    const uint32_t T = S.tot[h];
+__device__ __forceinline__ int sample_cell(const DevHist &H, uint32_t hoff, uint32_t T,
+                                           uint32_t w0) {
     const uint32_t t = __umulhi(w0, T);
-    // h < 2^12 and gbits <= 16: the entry index fits in 32 bits
-    const uint2 e = H.guide[((uint32_t)h << H.gbits) | (w0 >> (32 - H.gbits))];
+    // hoff = 8 h << gbits < 2^31 (h < 2^12, gbits <= 16): the entry's byte
+    // offset is a 32-bit number
+    const uint32_t at = hoff | ((w0 >> (29 - H.gbits)) & ~7u);
+    const uint2 e = *reinterpret_cast<const uint2 *>(reinterpret_cast<const char *>(H.guide) + at);
     int lo = (int)(e.x & 0xFFFFu);
     int hi = (int)(e.x >> 16);
     if (t < e.y) return lo;
     ++lo;
-    const uint32_t *C = H.cdf + (size_t)h * H.n_cells;
+    // h K < 2^28 (4 h K < 2^30 bytes): 32-bit offsets from the table's base
+    const uint32_t row = (hoff >> (H.gbits + 3)) * (uint32_t)H.n_cells;
     while (lo < hi) {
         const int mid = (lo + hi) >> 1;
-        if (C[mid] > t) hi = mid; else lo = mid + 1;
+        if (H.cdf[row + (uint32_t)mid] > t) hi = mid; else lo = mid + 1;
     }
     return lo;
 }
@@ -394,10 +623,11 @@ __device__ __forceinline__ int sample_cell(const DevHist &H, const Lds &S, int h
 // Alias method: column j = floor(w0 K / 2^32); the 24-bit threshold word x
 // (low bytes of w1, w2, w3, which the jitters and the azimuth leave unused)
 // keeps cell j when x is below the column's split, else gives its alias.
-// One 8-byte load per draw.
-__device__ __forceinline__ int alias_cell(const DevHist &H, int h, uint4 w) {
+// One 8-byte load per draw, its byte offset 8 (h K + j) < 2^31.
+__device__ __forceinline__ int alias_cell(const DevHist &H, uint32_t h, uint4 w) {
     const uint32_t j = __umulhi(w.x, (uint32_t)H.n_cells);
-    const uint2 e = H.alias[(size_t)h * H.n_cells + j];
+    const uint2 e = *reinterpret_cast<const uint2 *>(
+        reinterpret_cast<const char *>(H.alias) + 8u * (__umul24(h, (uint32_t)H.n_cells) + j));
     const uint32_t x = (w.y & 0xFFu) | ((w.z & 0xFFu) << 8) | ((w.w & 0xFFu) << 16);
     return (int)(x < e.x ? j : e.y);
 }
@@ -410,8 +640,7 @@ __device__ __forceinline__ int alias_cell(const DevHist &H, int h, uint4 w) {
 // R v = c v + a x v + (a.v) a / (1 + c), a = z x p_hat = (-ny, nx, 0),
 // c = nz (equal to Eq. (2) with k = a/|a|), in FP32.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void kick(Lane &L, double p2, float ux, float uy, float uz) {
-    const float p2f = (float)p2;
+__device__ __forceinline__ void kick(Lane &L, float p2f, float ux, float uy, float uz) {
     const float rinv = __builtin_amdgcn_rsqf(p2f);
     const float pm = p2f * rinv;
     const float nx = (float)L.px * rinv, ny = (float)L.py * rinv, nz = (float)L.pz * rinv;
@@ -463,7 +692,8 @@ __device__ __forceinline__ void map_coords(const DevField &F, double x, double y
 
 // Inside the map's node range on all three axes (closed): six compares
 // combined without branches, against the node counts as doubles.
-__device__ __forceinline__ bool in_map(const DevField &F, double u, double v, double w) {
+template <class FF>
+__device__ __forceinline__ bool in_map(const FF &F, double u, double v, double w) {
     return (u >= 0.0) & (u <= F.umax[0]) & (v >= 0.0) & (v <= F.umax[1]) & (w >= 0.0) &
            (w <= F.umax[2]);
 }
@@ -505,8 +735,9 @@ __device__ __forceinline__ float3 cell_field(const CellPoly &c) {
     return r;
 }
 
-__device__ __forceinline__ float3 box_field(const Tables &T, const Lds &S, const DevRun &R,
-                                            int vol, int var) {
+template <class TT, class RR>
+__device__ __forceinline__ float3 box_field(const TT &T, const Lds &S, const RR &R, int vol,
+                                            int var) {
     float3 B = make_float3(0.f, 0.f, 0.f);
     if (vol >= 0) {
         const float4 b = S.bf[vol];
@@ -532,76 +763,93 @@ __device__ __forceinline__ float3 add_map(const Tables &T, float3 B, double x, d
 }
 
 // Trilinear map at a point (the lane's position, or an RK4 stage point near
-// it) with the lane's current cell's corners kept in registers: consecutive
-// 2 cm steps and their stage points mostly stay in one cell, so the 128-byte
-// record is loaded only when the point lies in another cell (which then
-// becomes the lane's cell).  Same values and arithmetic as map_cell +
-// cell_field.
-__device__ __forceinline__ float3 add_map_cached(Lane &L, const DevField &F, float3 B, double x,
-                                                  double y, double z) {
+// it) with the lane's current cell's coefficients kept in registers:
+// consecutive 2 cm steps and their stage points mostly stay in one cell, so
+// the 128-byte record is loaded only when the point lies in another cell
+// (which then becomes the lane's cell).  The point is in the lane's cell, and
+// so inside the map, when its fractional coordinates in that cell lie in
+// [0, 1): as bit patterns, one unsigned maximum and one compare; negative, NaN
+// and rounded-up values fail it and take the exact lookup.  Same values and
+// arithmetic as map_cell + cell_field.  Outside the map the cell is empty
+// (all coefficients zero, no cell remembered).
+__device__ __forceinline__ float3 add_map_cached(Lane &L, const DevField &H, ArgPtr args, float3 B,
+                                                 double x, double y, double z) {
     double u, v, w;
-    map_coords(F, x, y, z, u, v, w);
-    if (!in_map(F, u, v, w))
-        return B;
-    const int i = min((int)u, F.nx - 2), j = min((int)v, F.ny - 2), k = min((int)w, F.nz - 2);
-    // 24-bit products: the loader keeps nx and ny nz below 2^24
-    const int cell = (int)__umul24(__umul24((uint32_t)k, (uint32_t)(F.ny - 1)) + (uint32_t)j,
-                                   (uint32_t)(F.nx - 1)) + i;
-    if (cell != L.mcell) {
-        const float4 *b = F.map + (size_t)cell * 8;
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            const float4 q = b[c];
-            L.mc[3 * c] = q.x;
-            L.mc[3 * c + 1] = q.y;
-            L.mc[3 * c + 2] = q.z;
-        }
-        L.mcell = cell;
-    }
+    map_coords(H, x, y, z, u, v, w);
     CellPoly c;
-    c.fx = (float)(u - (double)i);
-    c.fy = (float)(v - (double)j);
-    c.fz = (float)(w - (double)k);
+    c.fx = (float)(u - (double)L.ci);      // cell indices are below 2^24: exact floats
+    c.fy = (float)(v - (double)L.cj);
+    c.fz = (float)(w - (double)L.ck);
+    if (max(max(__float_as_uint(c.fx), __float_as_uint(c.fy)), __float_as_uint(c.fz)) >=
+        0x3f800000u) {
+        const auto &F = cold(args)->T.field;
+        if (in_map(F, u, v, w)) {
+            const int i = min((int)u, F.nx - 2), j = min((int)v, F.ny - 2),
+                      k = min((int)w, F.nz - 2);
+            // 24-bit products: the loader keeps nx and ny nz below 2^24
+            const int cell = (int)__umul24(__umul24((uint32_t)k, (uint32_t)(F.ny - 1)) +
+                                               (uint32_t)j, (uint32_t)(F.nx - 1)) + i;
+            const float4 *b = F.map + (size_t)cell * 8;
 #pragma unroll
-    for (int q = 0; q < 8; ++q) c.k[q] = make_float4(L.mc[3 * q], L.mc[3 * q + 1], L.mc[3 * q + 2], 0.f);
+            for (int q = 0; q < 8; ++q) {
+                const float4 r = b[q];
+                L.mc[3 * q] = r.x;
+                L.mc[3 * q + 1] = r.y;
+                L.mc[3 * q + 2] = r.z;
+            }
+            L.ci = (float)i;
+            L.cj = (float)j;
+            L.ck = (float)k;
+            c.fx = (float)(u - (double)i);
+            c.fy = (float)(v - (double)j);
+            c.fz = (float)(w - (double)k);
+        } else {
+#pragma unroll
+            for (int q = 0; q < 24; ++q) L.mc[q] = 0.0f;
+            L.ci = __builtin_nanf("");
+            c.fx = c.fy = c.fz = 0.0f;
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+        c.k[q] = make_float4(L.mc[3 * q], L.mc[3 * q + 1], L.mc[3 * q + 2], 0.f);
     const float3 m = cell_field(c);
     return make_float3(B.x + m.x, B.y + m.y, B.z + m.z);
 }
 
-// Nearest node with the last node's value kept in registers (mcell holds the
-// node index, mc[0..2] its value).
-__device__ __forceinline__ float3 add_nearest_cached(Lane &L, const DevField &F, float3 B,
-                                                      double x, double y, double z) {
+// Nearest-node lookup of the map: the node closest to (x, y, z) on every axis
+// (half-way points take the higher node), zero outside the grid; one 16-byte
+// load from the node-major copy of the map.  The last node's value is kept in
+// registers (mc[0..2]) and used while the point is less than half a spacing
+// from it on every axis; nodes on the map's border are not remembered, since
+// near them that test does not say whether the point is inside the map.
+__device__ __forceinline__ float3 add_nearest_cached(Lane &L, const DevField &H, ArgPtr args,
+                                                     float3 B, double x, double y, double z) {
     double u, v, w;
-    map_coords(F, x, y, z, u, v, w);
-    if (!in_map(F, u, v, w))
-        return B;
-    const int i = min((int)(u + 0.5), F.nx - 1), j = min((int)(v + 0.5), F.ny - 1),
-              k = min((int)(w + 0.5), F.nz - 1);
-    const int node = (int)__umul24(__umul24((uint32_t)k, (uint32_t)F.ny) + (uint32_t)j,
-                                   (uint32_t)F.nx) + i;
-    if (node != L.mcell) {
-        const float4 q = F.nodes[node];
+    map_coords(H, x, y, z, u, v, w);
+    const float du = (float)(u - (double)L.ci), dv = (float)(v - (double)L.cj),
+                dw = (float)(w - (double)L.ck);
+    if (!((fabsf(du) < 0.5f) & (fabsf(dv) < 0.5f) & (fabsf(dw) < 0.5f))) {
+        L.ci = __builtin_nanf("");
+        float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
+        const auto &F = cold(args)->T.field;
+        if (in_map(F, u, v, w)) {
+            const int i = min((int)(u + 0.5), F.nx - 1), j = min((int)(v + 0.5), F.ny - 1),
+                      k = min((int)(w + 0.5), F.nz - 1);
+            const int node = (int)__umul24(__umul24((uint32_t)k, (uint32_t)F.ny) + (uint32_t)j,
+                                           (uint32_t)F.nx) + i;
+            q = F.nodes[node];
+            if ((i > 0) & (i < F.nx - 1) & (j > 0) & (j < F.ny - 1) & (k > 0) & (k < F.nz - 1)) {
+                L.ci = (float)i;
+                L.cj = (float)j;
+                L.ck = (float)k;
+            }
+        }
         L.mc[0] = q.x;
         L.mc[1] = q.y;
         L.mc[2] = q.z;
-        L.mcell = node;
     }
     return make_float3(B.x + L.mc[0], B.y + L.mc[1], B.z + L.mc[2]);
-}
-
-// Nearest-node lookup of the map: the node closest to (x, y, z) on every axis
-// (half-way points take the higher node), zero outside the grid.  One
-// 16-byte load from the node-major copy of the map.
-__device__ __forceinline__ float3 map_nearest(const DevField &F, double x, double y, double z) {
-    double u, v, w;
-    map_coords(F, x, y, z, u, v, w);
-    if (!in_map(F, u, v, w))
-        return make_float3(0.f, 0.f, 0.f);
-    const int i = min((int)(u + 0.5), F.nx - 1), j = min((int)(v + 0.5), F.ny - 1),
-              k = min((int)(w + 0.5), F.nz - 1);
-    const float4 b = F.nodes[((size_t)k * F.ny + j) * F.nx + i];
-    return make_float3(b.x, b.y, b.z);
 }
 
 // ---------------------------------------------------------------------------
@@ -635,18 +883,25 @@ __device__ __forceinline__ float3 stage0(const Lane &L) {
     return make_float3((float)L.px, (float)L.py, (float)L.pz);
 }
 
-// a0 must be stage0(L) (the FP32 momentum the stages start from).
-__device__ __forceinline__ void rk4_from(Lane &L, float3 a0, float3 B, const StepConst &c) {
+// Is any component of b non-zero?  One or of the three bit patterns and one
+// compare (the or is +-0 exactly when all three are).
+__device__ __forceinline__ bool non_zero(float3 b) {
+    return __uint_as_float(__float_as_uint(b.x) | __float_as_uint(b.y) | __float_as_uint(b.z)) !=
+           0.0f;
+}
+
+// a0 must be stage0(L) (the FP32 momentum the stages start from), cb = kq B
+// and bent = (B is not zero).
+__device__ __forceinline__ void rk4_from(Lane &L, float3 a0, float3 cb, bool bent,
+                                         const StepConst &c) {
     const float r0 = __builtin_amdgcn_rsqf(norm2(a0));
     const float3 n0 = scale3(r0, a0);
     float drx, dry, drz;
-    if (B.x == 0.0f && B.y == 0.0f && B.z == 0.0f) {
+    if (!bent) {
         drx = c.h * n0.x;
         dry = c.h * n0.y;
         drz = c.h * n0.z;
     } else {
-        const float kq = (float)kKappa * L.q;
-        const float3 cb = scale3(kq, B);
         const float3 k1 = cross3(n0, cb);
         const float3 a1 = axpy(c.h2, k1, a0);
         const float3 n1 = scale3(__builtin_amdgcn_rsqf(norm2(a1)), a1);
@@ -670,13 +925,10 @@ __device__ __forceinline__ void rk4_from(Lane &L, float3 a0, float3 B, const Ste
     }
     // the position update is shared by both branches (keeps every Lane field
     // in registers: no store through a selected address)
+    move_in_region(L, drx, dry, drz);
     L.x += (double)drx;
     L.y += (double)dry;
     L.z += (double)drz;
-}
-
-__device__ __forceinline__ void rk4(Lane &L, float3 B, const StepConst &c) {
-    rk4_from(L, stage0(L), B, c);
 }
 
 // Compile-time features of a transport kernel (bit mask).
@@ -701,118 +953,257 @@ constexpr bool valid_mask(unsigned F) {
            !((F & kPoly) && (F & (kTape | kStages)));
 }
 
-// Map part of the field at a point.
+// The map part of the field, added to the volume's, through the lane's cell.
 template <unsigned F>
-__device__ __forceinline__ float3 map_field(const Tables &T, float3 B, double x, double y,
-                                            double z) {
-    if constexpr ((F & kNearest) != 0) {
-        const float3 m = map_nearest(T.field, x, y, z);
-        return make_float3(B.x + m.x, B.y + m.y, B.z + m.z);
-    } else {
-        return add_map<(F & kMap) != 0>(T, B, x, y, z);
-    }
+__device__ __forceinline__ float3 with_map(Lane &L, const KArgs &A, ArgPtr args, float3 B, double x,
+                                           double y, double z) {
+    if constexpr ((F & kNearest) != 0) return add_nearest_cached(L, A.T.field, args, B, x, y, z);
+    else if constexpr ((F & kMap) != 0) return add_map_cached(L, A.T.field, args, B, x, y, z);
+    else return B;
 }
 
-// Field at a stage point: scaled field of the box holding it plus the map,
-// read through the lane's cached map cell or node.
-template <unsigned F>
-__device__ __forceinline__ float3 field_at_point(const Tables &T, const Lds &S, const DevRun &R,
-                                                 Lane &L, double x, double y, double z) {
-    const int s = find_slab(S, T.geom.n_slab, z, L.slab);
-    const int vol = find_box(S, s, x, y);
-    float3 B;
-    if (vol == L.bvol) B = make_float3(L.bx, L.by, L.bz);
-    else B = box_field(T, S, R, vol, L.var);
-    if constexpr ((F & kMap) != 0 && (F & kNearest) == 0) return add_map_cached(L, T.field, B, x, y, z);
-    else if constexpr ((F & kNearest) != 0) return add_nearest_cached(L, T.field, B, x, y, z);
-    else return B;
+// Field at a stage point: scaled field of the box holding it plus the map.
+// `inside`: the lane's region proves that the point is in the lane's volume.
+template <unsigned F, typename V>
+__device__ __forceinline__ float3 field_at_point(const KArgs &A, ArgPtr args, Lane &L, bool inside,
+                                                 V &&var, double x, double y, double z) {
+    float3 B = make_float3(L.bx, L.by, L.bz);
+    if (!inside) {
+        const ArgPtr c = cold(args);
+        const Lds S = lds_view(c->T);
+        const int vol = find_box(S, find_slab(S, c->T.geom.n_slab, z, L.slab), x, y);
+        if (vol != L.vol) B = box_field(c->T, S, c->R, vol, var());
+    }
+    return with_map<F>(L, A, args, B, x, y, z);
 }
 
 // RK4 with the field evaluated afresh at each stage position (stage s sits
 // at r + c_s h v_{s-1}, c = 1/2, 1/2, 1); B1 is the step-start field.
-template <unsigned F>
-__device__ __forceinline__ void rk4_stages(Lane &L, float3 B1, const Tables &T, const Lds &S,
-                                           const DevRun &R, const StepConst &c) {
-    const float kq = (float)kKappa * L.q;
+// The stage points lie within one step length of the step start, so they are
+// in its volume when the region reaches that far.
+template <unsigned F, typename V>
+__device__ __forceinline__ void rk4_stages(Lane &L, V &&var, float3 B1, const KArgs &A, ArgPtr args,
+                                           const StepConst &c) {
+    const float kq = L.kq;
+    const float reach = 1.001f * c.h;
+    const bool inside = fmaxf(fmaxf(fmaf(reach, L.ix, fabsf(L.xr)), fmaf(reach, L.iy, fabsf(L.yr))),
+                              fmaf(reach, L.iz, fabsf(L.zr))) < 1.0f;
     const float3 a0 = stage0(L);
     const float3 n0 = scale3(__builtin_amdgcn_rsqf(norm2(a0)), a0);
     const float3 k1 = cross3(n0, scale3(kq, B1));
-    const float3 a1 = axpy(c.h2, k1, a0);
-    const float3 n1 = scale3(__builtin_amdgcn_rsqf(norm2(a1)), a1);
-    const float3 B2 = field_at_point<F>(T, S, R, L, L.x + (double)(c.h2 * n0.x),
-                                        L.y + (double)(c.h2 * n0.y), L.z + (double)(c.h2 * n0.z));
-    const float3 k2 = cross3(n1, scale3(kq, B2));
-    const float3 a2 = axpy(c.h2, k2, a0);
-    const float3 n2 = scale3(__builtin_amdgcn_rsqf(norm2(a2)), a2);
-    const float3 B3 = field_at_point<F>(T, S, R, L, L.x + (double)(c.h2 * n1.x),
-                                        L.y + (double)(c.h2 * n1.y), L.z + (double)(c.h2 * n1.z));
-    const float3 k3 = cross3(n2, scale3(kq, B3));
-    const float3 a3 = axpy(c.h, k3, a0);
-    const float3 n3 = scale3(__builtin_amdgcn_rsqf(norm2(a3)), a3);
-    const float3 B4 = field_at_point<F>(T, S, R, L, L.x + (double)(c.h * n2.x),
-                                        L.y + (double)(c.h * n2.y), L.z + (double)(c.h * n2.z));
-    const float3 k4 = cross3(n3, scale3(kq, B4));
-    L.px += (double)(c.h6 * (fmaf(2.0f, k2.x + k3.x, k1.x) + k4.x));
-    L.py += (double)(c.h6 * (fmaf(2.0f, k2.y + k3.y, k1.y) + k4.y));
-    L.pz += (double)(c.h6 * (fmaf(2.0f, k2.z + k3.z, k1.z) + k4.z));
-    L.x += (double)(c.h6 * (fmaf(2.0f, n1.x + n2.x, n0.x) + n3.x));
-    L.y += (double)(c.h6 * (fmaf(2.0f, n1.y + n2.y, n0.y) + n3.y));
-    L.z += (double)(c.h6 * (fmaf(2.0f, n1.z + n2.z, n0.z) + n3.z));
+    float3 n = n0, kk = k1;                     // direction and slope of the last stage
+    float3 n12 = make_float3(0.f, 0.f, 0.f), k12 = n12;
+    // one copy of the stage (its field lookup holds two cold paths)
+#pragma unroll 1
+    for (int st = 1; st <= 3; ++st) {
+        const float cs = st == 3 ? c.h : c.h2;
+        const float3 B = field_at_point<F>(A, args, L, inside, var, L.x + (double)(cs * n.x),
+                                           L.y + (double)(cs * n.y), L.z + (double)(cs * n.z));
+        const float3 a = axpy(cs, kk, a0);
+        n = scale3(__builtin_amdgcn_rsqf(norm2(a)), a);
+        kk = cross3(n, scale3(kq, B));
+        if (st == 1) {
+            n12 = n;
+            k12 = kk;
+        } else if (st == 2) {
+            n12 = add3(n12, n);
+            k12 = add3(k12, kk);
+        }
+    }
+    const float drx = c.h6 * (fmaf(2.0f, n12.x, n0.x) + n.x);
+    const float dry = c.h6 * (fmaf(2.0f, n12.y, n0.y) + n.y);
+    L.px += (double)(c.h6 * (fmaf(2.0f, k12.x, k1.x) + kk.x));
+    L.py += (double)(c.h6 * (fmaf(2.0f, k12.y, k1.y) + kk.y));
+    L.pz += (double)(c.h6 * (fmaf(2.0f, k12.z, k1.z) + kk.z));
+    const float drz = c.h6 * (fmaf(2.0f, n12.z, n0.z) + n.z);
+    move_in_region(L, drx, dry, drz);
+    L.x += (double)drx;
+    L.y += (double)dry;
+    L.z += (double)drz;
 }
 
 // ---------------------------------------------------------------------------
-// One iteration of the transport loop.  Returns false (with L.status set)
-// when a break condition holds at the top of the iteration.
+// One iteration of the transport loop at step k (the same for all running
+// lanes of a wavefront, so it stays in a scalar register).  Returns false
+// (with L.status and L.steps set) when a break condition holds at the top of
+// the iteration.
+//
+// What bounds it: VALU issue.  On gfx950 an FP32 add / mul / fma or a bitwise
+// operation on vector registers takes 2 cycles per 64-lane instruction, an
+// FP64, compare, conversion or integer product 4, rsq / rcp / sin / cos 8, and
+// an FP32 instruction with a scalar-register operand 4 (measured with all
+// SIMDs full).  So the common step carries no FP64 compare: it is decided by
+// the region and the momentum band of the lane (struct Lane), four cheap
+// tests, and everything about the volume and its histogram that does not
+// change with the step is in registers.
 // ---------------------------------------------------------------------------
 template <unsigned F>
-__device__ __forceinline__ bool advance(Lane &L, const Tables &T, const Lds &S, const DevRun &R,
-                                        const StepConst &sc, uint4 w_shared = uint4{}) {
-    constexpr bool MAP = (F & kMap) != 0, TAPE = (F & kTape) != 0, TRACE = (F & kTrace) != 0;
-    const double p2 = L.px * L.px + L.py * L.py + L.pz * L.pz;
-    // Break test in the order p_min, z_max, x_max, y_max, step cap (the first
-    // that holds decides the status).  The five compares are or-ed as masks;
-    // the status is picked only on the rare step that stops.
-    const bool c_pmin = p2 < R.pmin2, c_z = L.z >= T.geom.z_max;
-    const bool c_x = fabs(L.x) >= T.geom.x_max, c_y = fabs(L.y) >= T.geom.y_max;
-    const bool c_k = L.k >= R.max_steps;
-    int vol;
-    if constexpr ((F & kPoly) != 0) vol = locate_block(L, T, S);
-    else vol = locate(L, T, S);
-    if (c_pmin | c_z | c_x | c_y | c_k) {   // the muon stops here; vol is its final volume
-        L.status = c_pmin ? MT_ST_PMIN
-                 : c_z    ? MT_ST_ZMAX
-                 : c_x    ? MT_ST_XMAX
-                 : c_y    ? MT_ST_YMAX
-                          : MT_ST_MAXSTEPS;
-        return false;
+constexpr bool kScaledField = !(F & (kMap | kStages));   // L.b* holds kq B
+
+// Step of hoff from one histogram to the next: bytes of a guide row, or (alias
+// tables, whose rows are no power of two) one.
+template <unsigned F>
+__device__ __forceinline__ uint32_t row_of(int gbits) {
+    return (F & kAlias) ? 1u : 8u << gbits;
+}
+
+template <unsigned F>
+__device__ __forceinline__ uint32_t hist_of(const Lane &L, int gbits) {
+    return (F & kAlias) ? L.hoff : L.hoff >> (gbits + 3);
+}
+
+// The exact tests of a step that the lane's region or momentum band does not
+// decide.
+template <unsigned F, typename V>
+__device__ __forceinline__ bool locate_region(Lane &L, V &&var, int k, double p2, float p2f,
+                                              bool outside, ArgPtr args) {
+    const ArgPtr c = cold(args);
+    const auto &T = c->T;
+    const auto &R = c->R;
+    const Lds S = lds_view(T);
+    const int P = T.hist.n_pbin, gbits = T.hist.gbits;
+    if (outside) {
+        int vol;
+        bool known = false;
+        Region r{};
+        if constexpr ((F & kPoly) != 0) {
+            vol = locate_block(L, T, S, r, known);
+            known = known & (k < R.max_steps);
+        } else {
+            vol = locate_box(L, T, S);
+            known = table_region(L, vol, T, S) & (k < R.max_steps);
+        }
+        const int old = L.vol;
+        L.vol = vol;
+        if (!known) {
+            // Break test in the order p_min, z_max, x_max, y_max, step cap (the
+            // first that holds decides the status; vol is the final volume).
+            const bool c_pmin = p2 < R.pmin2, c_z = L.z >= T.geom.z_max;
+            const bool c_x = fabs(L.x) >= T.geom.x_max, c_y = fabs(L.y) >= T.geom.y_max;
+            const bool c_k = k >= R.max_steps;
+            if (c_pmin | c_z | c_x | c_y | c_k) {
+                L.status = c_pmin ? MT_ST_PMIN
+                         : c_z    ? MT_ST_ZMAX
+                         : c_x    ? MT_ST_XMAX
+                         : c_y    ? MT_ST_YMAX
+                                  : MT_ST_MAXSTEPS;
+                L.steps = k;
+                return false;
+            }
+            if constexpr ((F & kPoly) == 0) {
+                r = box_region(L, vol, S);
+            } else {
+                L.rec = (uint32_t)T.lds.off_planes +
+                        (uint32_t)sizeof(BlockPlanes) * (uint32_t)T.geom.n_poly;
+            }
+            set_region(L, r, T.geom);
+        }
+        if (vol != old) {
+            const float3 b = box_field(T, S, R, vol, var());
+            L.bent = non_zero(b);
+            const float s = kScaledField<F> ? L.kq : 1.0f;
+            L.bx = s * b.x;
+            L.by = s * b.y;
+            L.bz = s * b.z;
+            // another material: the same momentum bin of its histograms; into
+            // or out of empty space: the band is looked up below
+            const int mat = vol >= 0 ? S.mat[vol] : -1, mat_old = old >= 0 ? S.mat[old] : -1;
+            if (mat != mat_old) {
+                if ((mat >= 0) & (mat_old >= 0)) {
+                    const uint32_t h = hist_of<F>(L, gbits) + (uint32_t)((mat - mat_old) * P);
+                    L.hoff = h * row_of<F>(gbits);
+                    if constexpr ((F & kAlias) == 0) L.tot = S.tot[h];
+                } else {
+                    L.hoff = mat >= 0 ? (uint32_t)(mat * P) * row_of<F>(gbits) : kVacuum;
+                    L.plo = L.pspan = 0u;
+                }
+            }
+        }
     }
-    const int mat = vol >= 0 ? S.mat[vol] : -1;
+    if (__float_as_uint(p2f) - L.plo >= L.pspan) {
+        if (p2 < R.pmin2) {
+            L.status = MT_ST_PMIN;
+            L.steps = k;
+            return false;
+        }
+        uint2 r = S.band[T.hist.n_mat * P];
+        if (L.hoff != kVacuum) {
+            const int h0 = S.mat[L.vol] * P;
+            const uint32_t h = (uint32_t)(h0 + find_bin(S, P, p2, (int)hist_of<F>(L, gbits) - h0));
+            r = S.band[h];
+            L.hoff = h * row_of<F>(gbits);
+            if constexpr ((F & kAlias) == 0) L.tot = S.tot[h];
+        }
+        L.plo = r.x;
+        L.pspan = r.y;
+    }
+    return true;
+}
+
+template <unsigned F, typename V>
+__device__ __forceinline__ bool advance(Lane &L, int64_t g, V &&var, int k, const KArgs &A,
+                                        ArgPtr args, const StepConst &sc,
+                                        uint4 w_shared = uint4{}) {
+    constexpr bool TAPE = (F & kTape) != 0, TRACE = (F & kTrace) != 0;
+    const DevHist &H = A.T.hist;
+    const DevRun &R = A.R;
+    const double p2 = L.px * L.px + L.py * L.py + L.pz * L.pz;
+    const float p2f = (float)p2;
+    bool outside;
+    if constexpr ((F & kPoly) != 0) outside = (k == 0) || outside_planes(L, k);
+    else outside = outside_region(L, k);
+    outside |= k >= R.max_steps;
+    const uint32_t pb = __float_as_uint(p2f);
+    if (outside | (pb - L.plo >= L.pspan)) {
+        // Mostly a muon that went into the next lower bin of the same volume
+        // (3-4 % of steps, so some lane of a wavefront in most of them): the
+        // histogram before its own, whose band is above the threshold.  A
+        // momentum below a material's bin 0 is below that row's band too.
+        // |p| so small or large that the step's FP32 arithmetic may give positions
+        // that are not finite: everything in FP64
+        outside |= !((p2f >= kBandLow) & (p2f < INFINITY));
+        if (!outside & (pb < L.plo) & (L.hoff != kVacuum)) {
+            const uint32_t h = max(hist_of<F>(L, H.gbits), 1u) - 1u;
+            const char *lds = lds_base();
+            const uint2 r = reinterpret_cast<const uint2 *>(lds + A.T.lds.off_band)[h];
+            if (pb - r.x < r.y) {
+                L.hoff -= row_of<F>(H.gbits);
+                if constexpr ((F & kAlias) == 0)
+                    L.tot = reinterpret_cast<const uint32_t *>(lds + A.T.lds.off_tot)[h];
+                L.plo = r.x;
+                L.pspan = r.y;
+            }
+        }
+        if (outside | (pb - L.plo >= L.pspan)) {
+            if (!locate_region<F>(L, var, k, p2, p2f, outside, args)) return false;
+        }
+    }
     float ux = 0.0f, uy = 0.0f, uz = 0.0f;
     int cell = -1;
-    if (mat >= 0) {
-        const int ibin = bin_of(L, T, S, p2);
+    if (L.hoff != kVacuum) {
         uint4 w;
         if constexpr ((F & kShared) != 0) w = w_shared;
-        else w = philox_step(L.ph, (uint32_t)L.k, R.key0, R.key1);
-        // mat < 2^12 and n_pbin <= 1024: a full-rate 24-bit multiply
-        const int h = (int)__umul24((uint32_t)mat, (uint32_t)T.hist.n_pbin) + ibin;
-        if constexpr ((F & kAlias) != 0) cell = alias_cell(T.hist, h, w);
-        else cell = sample_cell(T.hist, S, h, w.x);
-        // cell / n_scat as umulhi(cell + 1, floor((2^32 - 1) / n_scat)): exact
-        // for every n_scat >= 1 and cell < 2^16
-        const int il = (int)__umulhi((uint32_t)cell + 1u, T.hist.nscat_magic);
-        const int is = cell - il * T.hist.n_scat;
-        const float v1 = (float)(w.y >> 8) * 0x1p-24f;
-        const float v2 = (float)(w.z >> 8) * 0x1p-24f;
+        else w = philox_step(L.ph, (uint32_t)k, R.key0, R.key1);
+        if constexpr ((F & kAlias) != 0) cell = alias_cell(H, L.hoff, w);
+        else cell = sample_cell(H, L.hoff, L.tot, w.x);
+        // loss index = floor(cell / n_scat) = floor((cell + 1/2) / n_scat) in
+        // FP32: exact for cell < 2^16 and every n_scat (the quotient is at
+        // least 1 / (2 n_scat) from an integer, its error below 2^-6 / n_scat)
+        const float cf = (float)cell;
+        const float il = floorf(fmaf(cf, H.nscat_inv, 0.5f * H.nscat_inv));
+        const float is = fmaf(-il, H.nscat_f, cf);
+        // index + jitter: the product with 2^-24 is exact, one rounding
+        const float v1 = fmaf((float)(w.y >> 8), 0x1p-24f, il);
+        const float v2 = fmaf((float)(w.z >> 8), 0x1p-24f, is);
         const float v3 = (float)(w.w >> 8) * 0x1p-24f;
-        float f = fmaf((float)il + v1, T.hist.loss_w, T.hist.loss_lo);
-        float tau = fmaf((float)is + v2, T.hist.scat_w, T.hist.scat_lo);
+        float f = fmaf(v1, H.loss_w, H.loss_lo);
+        float tau = fmaf(v2, H.scat_w, H.scat_lo);
         if constexpr ((F & kLog) != 0) {      // jitter uniform in log10 of the value
             // 10^u = 2^(u log2 10) on the hardware exp2 (relative error ~1e-6
             // for |u| <= 7, far inside the FP32 kick arithmetic around it)
             constexpr float kLog2Of10 = 3.32192809488736f;
-            if (T.hist.log_loss) f = __builtin_amdgcn_exp2f(f * kLog2Of10);
-            if (T.hist.log_scat) tau = __builtin_amdgcn_exp2f(tau * kLog2Of10);
+            if (H.log_loss) f = __builtin_amdgcn_exp2f(f * kLog2Of10);
+            if (H.log_scat) tau = __builtin_amdgcn_exp2f(tau * kLog2Of10);
         }
         // v_sin_f32 / v_cos_f32 take their argument in revolutions: sin(2 pi v3).
         const float sn = __builtin_amdgcn_sinf(v3);
@@ -820,37 +1211,28 @@ __device__ __forceinline__ bool advance(Lane &L, const Tables &T, const Lds &S, 
         ux = tau * cs;
         uy = tau * sn;
         uz = -f;
-        kick(L, p2, ux, uy, uz);
+        kick(L, p2f, ux, uy, uz);
     }
     if (TAPE) {   // the local kick; the replay finds the volume again from the state
-        float *t = R.tape + ((size_t)L.k * R.lanes + L.g) * 3;
+        float *t = R.tape + ((size_t)k * R.lanes + g) * 3;
         t[0] = ux;
         t[1] = uy;
         t[2] = uz;
     }
-    if (TRACE && L.g < R.n_trace && L.k < R.trace_steps) {
-        int32_t *tr = R.trace + ((size_t)L.g * R.trace_steps + L.k) * 3;
-        tr[0] = vol;
-        tr[1] = mat >= 0 ? L.ibin : -1;
+    if (TRACE && g < R.n_trace && k < R.trace_steps) {
+        int32_t *tr = R.trace + ((size_t)g * R.trace_steps + k) * 3;
+        tr[0] = L.vol;
+        tr[1] = L.hoff != kVacuum ? (int)(hist_of<F>(L, H.gbits) % (uint32_t)H.n_pbin) : -1;
         tr[2] = cell;
     }
-    if (vol != L.bvol) {
-        const float3 b = box_field(T, S, R, vol, L.var);
-        L.bx = b.x;
-        L.by = b.y;
-        L.bz = b.z;
-        L.bvol = vol;
+    const float3 b = make_float3(L.bx, L.by, L.bz);
+    if constexpr (kScaledField<F>) {
+        rk4_from(L, stage0(L), b, L.bent, sc);
+    } else {
+        const float3 B = with_map<F>(L, A, args, b, L.x, L.y, L.z);
+        if constexpr ((F & kStages) != 0) rk4_stages<F>(L, var, B, A, args, sc);
+        else rk4_from(L, stage0(L), scale3(L.kq, B), non_zero(B), sc);
     }
-    float3 B;
-    if constexpr ((F & kMap) != 0 && (F & kNearest) == 0)
-        B = add_map_cached(L, T.field, make_float3(L.bx, L.by, L.bz), L.x, L.y, L.z);
-    else if constexpr ((F & kNearest) != 0)
-        B = add_nearest_cached(L, T.field, make_float3(L.bx, L.by, L.bz), L.x, L.y, L.z);
-    else
-        B = map_field<F>(T, make_float3(L.bx, L.by, L.bz), L.x, L.y, L.z);
-    if constexpr ((F & kStages) != 0) rk4_stages<F>(L, B, T, S, R, sc);
-    else rk4(L, B, sc);
-    ++L.k;
     return true;
 }
 
@@ -863,9 +1245,8 @@ __device__ __forceinline__ StepConst step_const(const DevRun &R) {
     return c;
 }
 
-__device__ __forceinline__ void store_lane(const Lane &L, const Tables &T, const Lds &S,
-                                           const DevIO &io) {
-    const int64_t g = L.g;
+template <class IO>
+__device__ __forceinline__ void store_lane(const Lane &L, int64_t g, const IO &io) {
     io.ox[g] = L.x;
     io.oy[g] = L.y;
     io.oz[g] = L.z;
@@ -873,12 +1254,12 @@ __device__ __forceinline__ void store_lane(const Lane &L, const Tables &T, const
     io.opy[g] = L.py;
     io.opz[g] = L.pz;
     io.status[g] = L.status;
-    io.n_steps[g] = L.k;
+    io.n_steps[g] = L.steps;
     io.volume[g] = L.status == MT_ST_INVALID ? -1 : L.vol;
 }
 
-__device__ __forceinline__ void write_ckpt(const Lane &L, const DevRun &R) {
-    double *c = R.ckpt + (size_t)(L.k / kCkptEvery) * 6 * R.lanes + L.g;
+__device__ __forceinline__ void write_ckpt(const Lane &L, int64_t g, int k, const DevRun &R) {
+    double *c = R.ckpt + (size_t)(k / kCkptEvery) * 6 * R.lanes + g;
     c[0] = L.x;
     c[R.lanes] = L.y;
     c[2 * R.lanes] = L.z;
@@ -901,22 +1282,24 @@ constexpr int plain_min_waves(unsigned F) {
 
 template <unsigned F>
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(plain_min_waves(F))))
-k_plain(Tables T, DevRun R, DevIO io) {
+k_plain(KArgs A) {
     constexpr bool CKPT = (F & kTape) != 0;
-    extern __shared__ __align__(16) char smem[];
-    const Lds S = stage_tables<(F & kPoly) != 0>(smem, T);
+    const ArgPtr args = kernel_args();
+    const DevRun &R = A.R;
+    stage_tables(A.T, R.pmin2);
     const StepConst sc = step_const(R);
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= R.lanes) return;
     Lane L;
-    load_lane(L, g, io, R);
+    load_lane(L, g, A.io, R);
     if (L.status == MT_ST_RUNNING) {
-        for (;;) {
-            if (CKPT && (L.k % kCkptEvery) == 0 && L.k < R.max_steps) write_ckpt(L, R);
-            if (!advance<F>(L, T, S, R, sc)) break;
+        auto var = [&] { return (int)variant_of(g, cold(args)->R); };
+        for (int k = 0;; ++k) {
+            if (CKPT && (k % kCkptEvery) == 0 && k < R.max_steps) write_ckpt(L, g, k, R);
+            if (!advance<F>(L, g, var, k, A, args, sc)) break;
         }
     }
-    store_lane(L, T, S, io);
+    store_lane(L, g, cold(args)->io);
 }
 
 // ---------------------------------------------------------------------------
@@ -945,42 +1328,38 @@ k_plain(Tables T, DevRun R, DevIO io) {
 // when a muon is resumed.
 // ---------------------------------------------------------------------------
 
-// Lane state of the muon of output slot g resumed at step k from that slot.
-__device__ __forceinline__ void resume_lane(Lane &L, int64_t g, int32_t k, const DevIO &io,
+// Lane state of the muon of output slot g resumed from that slot.
+__device__ __forceinline__ void resume_lane(Lane &L, int64_t g, const DevIO &io,
                                             const DevRun &R) {
-    int64_t var = 0, j = g;
-    if (R.lanes != R.n) {
-        var = R.lanes <= 0xFFFFFFFFll ? (int64_t)((uint32_t)g / (uint32_t)R.n) : g / R.n;
-        j = g - var * R.n;
-    }
-    load_lane_at(L, j, var, g, io, R);      // charge, Philox prefix, caches reset
+    load_lane(L, g, io, R);                 // charge, Philox prefix, caches reset
     L.x = io.ox[g];
     L.y = io.oy[g];
     L.z = io.oz[g];
     L.px = io.opx[g];
     L.py = io.opy[g];
     L.pz = io.opz[g];
-    L.k = k;
     L.status = MT_ST_RUNNING;
 }
 
 template <unsigned F>     // F never holds kTape
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(plain_min_waves(F))))
-k_pass(Tables T, DevRun R, DevIO io, PassArgs P) {
-    extern __shared__ __align__(16) char smem[];
+k_pass(KArgs A) {
+    const ArgPtr args = kernel_args();
+    const DevRun &R = A.R;
+    const PassArgs &P = A.P;
     // items of this pass: the launch's lanes (first pass) or the survivors
     // of the previous pass, whose count that pass left in memory
     const int64_t items = P.n_in ? (int64_t)*P.n_in : R.lanes;
     if ((int64_t)blockIdx.x * blockDim.x >= items) return;     // the whole block
-    const Lds S = stage_tables<(F & kPoly) != 0>(smem, T);
+    stage_tables(A.T, R.pmin2);
     const StepConst sc = step_const(R);
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     bool parked = false;        // still running at the pass's end: goes on in the next pass
     int64_t slot = 0;           // its output slot
     if (i < items) {
         Lane L;
-        if (P.n_in) resume_lane(L, P.in[i], P.k_begin, io, R);
-        else load_lane(L, i, io, R);
+        if (P.n_in) resume_lane(L, P.in[i], A.io, R);
+        else load_lane(L, i, A.io, R);
         // The pass ends where R.max_steps says (the host sets it to the
         // pass's last step, or to the step cap in the last pass), so the
         // step loop is the plain form's: a muon that meets no other break
@@ -988,30 +1367,39 @@ k_pass(Tables T, DevRun R, DevIO io, PassArgs P) {
         // is parked here if the real cap lies beyond.  The break test it
         // passed there is the one the next pass repeats at the same step.
         if (L.status == MT_ST_RUNNING) {
-            for (;;) {
-                if (!advance<F>(L, T, S, R, sc)) break;
+            // the output slot, which only traces need in the loop
+            const int64_t g = (F & kTrace) && P.n_in ? P.in[i] : i;
+            auto var = [&] {
+                const ArgPtr c = cold(args);
+                return (int)variant_of(c->P.n_in ? c->P.in[i] : i, c->R);
+            };
+            for (int k = P.k_begin;; ++k) {
+                if (!advance<F>(L, g, var, k, A, args, sc)) break;
             }
         }
-        if (L.status == MT_ST_MAXSTEPS && L.k < P.max_steps) {
+        const ArgPtr c = cold(args);
+        if (L.status == MT_ST_MAXSTEPS && L.steps < c->P.max_steps) {
             parked = true;
-            slot = L.g;
             L.status = MT_ST_RUNNING;
         }
-        store_lane(L, T, S, io);            // status running if parked
+        // the slot is read again rather than kept in registers over the loop
+        slot = c->P.n_in ? c->P.in[i] : i;
+        store_lane(L, slot, c->io);         // status running if parked
     }
     // wave-aggregated append of the survivors' slots (no block barrier: a
     // wave that is done leaves at once and frees its registers for the next)
     const uint64_t m = __ballot(parked);
     if (m) {
+        const ArgPtr c = cold(args);
         unsigned long long base = 0;
         if ((threadIdx.x & (kWave - 1)) == 0)
-            base = atomicAdd(P.n_out, (unsigned long long)__popcll(m));
+            base = atomicAdd(c->P.n_out, (unsigned long long)__popcll(m));
         base = __builtin_amdgcn_readfirstlane((uint32_t)base) |
                ((unsigned long long)__builtin_amdgcn_readfirstlane((uint32_t)(base >> 32)) << 32);
         if (parked) {
             const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
                 (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-            P.out[base + rank] = slot;
+            c->P.out[base + rank] = slot;
         }
     }
 }
@@ -1035,9 +1423,12 @@ k_pass(Tables T, DevRun R, DevIO io, PassArgs P) {
 // same output slots).
 // ---------------------------------------------------------------------------
 template <unsigned F>     // F holds neither kTape nor kTrace
-__global__ void __launch_bounds__(1024) k_variant_waves(Tables T, DevRun R, DevIO io) {
-    extern __shared__ __align__(16) char smem[];
-    const Lds S = stage_tables<(F & kPoly) != 0>(smem, T);
+__global__ void __launch_bounds__(1024)
+    __attribute__((amdgpu_waves_per_eu((F & (kMap | kStages | kPoly)) ? plain_min_waves(F) : 6)))
+k_variant_waves(KArgs A) {
+    const ArgPtr args = kernel_args();
+    const DevRun &R = A.R;
+    stage_tables(A.T, R.pmin2);
     const StepConst sc = step_const(R);
     const int lane = (int)(threadIdx.x & (kWave - 1));
     const int gs = R.share_shift, gm = (1 << gs) - 1;   // G = 2^gs lanes per muon
@@ -1056,16 +1447,17 @@ __global__ void __launch_bounds__(1024) k_variant_waves(Tables T, DevRun R, DevI
     Lane L;
     bool running = false;
     if (valid) {
-        load_lane_at(L, j, var, 0, io, R);         // output slot formed after the loop
+        load_lane_at(L, j, A.io, R);
         running = L.status == MT_ST_RUNNING;
     }
     const PhiloxPrefix P =
         philox_prefix((uint32_t)j, (uint32_t)((uint64_t)j >> 32), R.key0, R.key1);
     // the wavefront's Philox blocks: lane l holds its group's block of step
     // k0 + (l mod G), 1 KB of LDS per wavefront
-    uint4 *wblk = reinterpret_cast<uint4 *>(smem + ((T.lds.bytes + 15) & ~15)) +
+    uint4 *wblk = reinterpret_cast<uint4 *>(lds_base() + A.T.lds.bytes) +
                   (threadIdx.x & ~(unsigned)(kWave - 1));
     const int base = lane & ~gm;
+    auto var_of = [&] { return (int)var; };
     for (int k = 0; __ballot(running) != 0; ++k) {
         const int sl = k & gm;
         if (sl == 0) {
@@ -1079,12 +1471,11 @@ __global__ void __launch_bounds__(1024) k_variant_waves(Tables T, DevRun R, DevI
         }
         if (running) {
             const uint4 w = wblk[base + sl];      // one address per group: a broadcast
-            running = advance<F | kShared>(L, T, S, R, sc, w);
+            running = advance<F | kShared>(L, 0, var_of, k, A, args, sc, w);
         }
     }
     if (valid) {
-        L.g = (int64_t)L.var * n + j;
-        store_lane(L, T, S, io);
+        store_lane(L, var * n + j, cold(args)->io);
     }
 }
 
@@ -1254,35 +1645,44 @@ __device__ __forceinline__ float3 kick_again(float3 p0, float3 u) {
     K.py = (double)p0.y;
     K.pz = (double)p0.z;
     const double p2 = K.px * K.px + K.py * K.py + K.pz * K.pz;
-    kick(K, p2, u.x, u.y, u.z);
+    kick(K, (float)p2, u.x, u.y, u.z);
     return stage0(K);
 }
 
 // Re-run one step of a segment with its recorded kick (the arithmetic of
 // advance(), so the same bits).  The volume is looked up again from the
 // state, which is the forward's to the bit, so it is the forward's volume.
-// B caches the field of volume bvol.  Returns the volume.
+// Returns the volume.
 template <bool MAP>
-__device__ __forceinline__ int replay_step(Lane &L, const Tables &T, const Lds &S,
+__device__ __forceinline__ int replay_step(Lane &L, int k, const Tables &T, const Lds &S,
                                            const DevRun &R, const StepConst &sc, int var,
                                            float3 u) {
-    const int vol = locate(L, T, S);
-    const int mat = vol >= 0 ? S.mat[vol] : -1;
-    if (mat >= 0) {
+    if (outside_region(L, k)) {
+        const int vol = locate_box(L, T, S);
+        if (!table_region(L, vol, T, S)) set_region(L, box_region(L, vol, S), T.geom);
+        if (vol != L.vol) {
+            L.vol = vol;
+            const float3 b = box_field(T, S, R, vol, var);
+            L.bent = non_zero(b);
+            const float s = MAP ? 1.0f : L.kq;
+            L.bx = s * b.x;
+            L.by = s * b.y;
+            L.bz = s * b.z;
+            L.hoff = vol >= 0 && S.mat[vol] >= 0 ? 0u : kVacuum;
+        }
+    }
+    if (L.hoff != kVacuum) {
         const double p2 = L.px * L.px + L.py * L.py + L.pz * L.pz;
-        kick(L, p2, u.x, u.y, u.z);
+        kick(L, (float)p2, u.x, u.y, u.z);
     }
-    if (vol != L.bvol) {
-        const float3 b = box_field(T, S, R, vol, var);
-        L.bx = b.x;
-        L.by = b.y;
-        L.bz = b.z;
-        L.bvol = vol;
+    const float3 b = make_float3(L.bx, L.by, L.bz);
+    if (MAP) {
+        const float3 B = add_map<MAP>(T, b, L.x, L.y, L.z);
+        rk4_from(L, stage0(L), scale3(L.kq, B), non_zero(B), sc);
+    } else {
+        rk4_from(L, stage0(L), b, L.bent, sc);
     }
-    const float3 B = add_map<MAP>(T, make_float3(L.bx, L.by, L.bz), L.x, L.y, L.z);
-    const float3 a0 = stage0(L);
-    rk4_from(L, a0, B, sc);
-    return vol;
+    return L.vol;
 }
 
 // The segment's start momenta are kept either in LDS (LDSH) or in a per-lane
@@ -1294,8 +1694,9 @@ template <bool MAP, bool LDSH>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MAP ? 1 : 5)))
 k_adjoint(Tables T, DevRun R, DevIO io, const double *g_out,
                                                  double *g_in, double *gs_lane, char *scratch) {
-    extern __shared__ __align__(16) char smem[];
-    const Lds S = stage_tables<false>(smem, T);
+    stage_tables(T, R.pmin2);
+    const Lds S = lds_view(T);
+    char *smem = lds_base();
     const StepConst sc = step_const(R);
     const int bd = blockDim.x;
     const int n_mag = T.geom.n_mag;
@@ -1350,14 +1751,10 @@ k_adjoint(Tables T, DevRun R, DevIO io, const double *g_out,
             L.px = c[3 * lanes];
             L.py = c[4 * lanes];
             L.pz = c[5 * lanes];
-            L.q = q;
+            L.kq = kq;
             // kick records of the segment: three floats per (step, lane)
             const float *rec = R.tape + ((size_t)k0 * lanes + g) * 3;
-            L.bvol = -2;
-            L.vol = -1;                  // lookup caches start empty
-            L.slab = -1;
-            L.zlo = INFINITY;
-            L.zhi = -INFINITY;
+            reset_lane_caches(L);        // lookup caches start empty
             // history of the segment: the pre-kick momentum p0 of every step
             // (FP32), [step][3][thread] in LDS (LDSH) or one 12-byte record per
             // (step, lane) in device memory.  The stage-0 momentum a0 is formed
@@ -1393,7 +1790,7 @@ k_adjoint(Tables T, DevRun R, DevIO io, const double *g_out,
                     hrp[2 * lanes] = L.z;
                     hrp += 3 * lanes;
                 }
-                vh[(k - k0) * bd] = (int8_t)replay_step<MAP>(L, T, S, R, sc, var, cur);
+                vh[(k - k0) * bd] = (int8_t)replay_step<MAP>(L, k, T, S, R, sc, var, cur);
                 if (LDSH) {
                     float *h = hp + (size_t)(k - k0) * 3 * hs;
                     h[0] = p0x;
@@ -1622,16 +2019,12 @@ hipError_t launch_plain(const Tables &T, const DevRun &R, const DevIO &io, int b
     static const auto fns = plain_kernels(std::make_index_sequence<kFeatures>());
     if (R.lanes == 0) return hipSuccess;
     const unsigned grid = (unsigned)((R.lanes + block - 1) / block);
-    Tables t = T;
-    DevRun r = R;
-    DevIO o = io;
-    void *args[] = {&t, &r, &o};
+    KArgs a{T, R, io, PassArgs{}};
+    void *args[] = {&a};
     const void *fn = fns[feature_mask(T, R)];
     if (fn == nullptr) return hipErrorInvalidValue;     // excluded by argument validation
     return hipLaunchKernel(fn, dim3(grid), dim3(block), args, (size_t)T.lds.bytes, s);
 }
-
-static size_t persistent_lds(const Tables &T) { return (size_t)T.lds.bytes; }
 
 static const void *persistent_fn(unsigned mask) {
     static const auto fns = persistent_kernels(std::make_index_sequence<kFeatures>());
@@ -1644,14 +2037,11 @@ hipError_t launch_pass(const Tables &T, const DevRun &R, const DevIO &io, int bl
     // sized for every lane (the survivors of a pass are at most that many);
     // blocks past the pass's items exit before staging their tables
     const unsigned grid = (unsigned)((R.lanes + block - 1) / block);
-    Tables t = T;
-    DevRun r = R;
-    DevIO o = io;
-    PassArgs pa = P;
-    void *args[] = {&t, &r, &o, &pa};
+    KArgs a{T, R, io, P};
+    void *args[] = {&a};
     const void *fn = persistent_fn(feature_mask(T, R) & ~kTape);
     if (fn == nullptr) return hipErrorInvalidValue;     // excluded by argument validation
-    return hipLaunchKernel(fn, dim3(grid), dim3(block), args, persistent_lds(T), s);
+    return hipLaunchKernel(fn, dim3(grid), dim3(block), args, (size_t)T.lds.bytes, s);
 }
 
 hipError_t launch_variant_waves(const Tables &T, const DevRun &R, const DevIO &io, int block,
@@ -1664,13 +2054,11 @@ hipError_t launch_variant_waves(const Tables &T, const DevRun &R, const DevIO &i
     const int64_t waves = (units + per_wave - 1) / per_wave;
     const int64_t per_block = block / kWave;
     const unsigned grid = (unsigned)((waves + per_block - 1) / per_block);
-    Tables t = T;
-    DevRun r = R;
-    DevIO o = io;
-    void *args[] = {&t, &r, &o};
+    KArgs a{T, R, io, PassArgs{}};
+    void *args[] = {&a};
     const void *fn = fns[feature_mask(T, R)];
     if (fn == nullptr) return hipErrorInvalidValue;     // excluded by argument validation
-    const size_t lds = (size_t)((T.lds.bytes + 15) & ~15) + (size_t)block * sizeof(uint4);
+    const size_t lds = (size_t)T.lds.bytes + (size_t)block * sizeof(uint4);
     return hipLaunchKernel(fn, dim3(grid), dim3(block), args, lds, s);
 }
 
