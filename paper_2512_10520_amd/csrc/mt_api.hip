@@ -91,7 +91,7 @@ struct State {
     bool hist_loaded = false, geom_loaded = false;
     int n_mat = 0, n_pbin = 0;
     int64_t version = 0;  // bumped on every table change
-    DevBuf cdf, guide, alias, nodes, image;
+    DevBuf cdf, guide, alias, nodes, nodesv, image;
     // host copies of the tables that every block stages in LDS (see build_image)
     struct {
         std::vector<double> e2, box4, slab_z, blk;
@@ -104,7 +104,7 @@ struct State {
         std::vector<mt::BlockRegion> block_region;
         std::vector<mt::BlockPlanes> block_planes;
     } host;
-    DevBuf map;
+    DevBuf map, mapv;
     DevBuf queue, partial, scratch, gs_lane, lists;
     Tables T{};
     int max_material = -1;
@@ -752,6 +752,10 @@ static void region_axis(double lo, double hi, double *centre, float *inv) {
     *inv = ok ? (float)(1.0 / half) : 1.0f;
 }
 
+static bool all_vertical(const std::vector<float4> &b) {
+    return std::all_of(b.begin(), b.end(), [](float4 v) { return v.x == 0.f && v.z == 0.f; });
+}
+
 // z-slabs of volumes with z ranges zr = lo0, hi0, lo1, hi1, ...: the breaks
 // (with -inf and +inf at the ends) and, per slab, the volumes that span it.
 static void z_slabs(const std::vector<double> &zr, std::vector<double> &slab_z,
@@ -839,6 +843,7 @@ int mt_load_geometry(int32_t n_box, const double *box, const int32_t *material, 
     G.n_slab = n_slab;
     G.n_mag = n_mag;
     G.disjoint = disjoint ? 1 : 0;
+    G.vertical = all_vertical(bf) ? 1 : 0;
     g.host.box4 = std::move(box4);
     g.host.bfield = std::move(bf);
     g.host.material = std::move(mat);
@@ -1150,6 +1155,7 @@ int mt_load_blocks(int32_t n, const double *block, const int32_t *material, cons
     G_.n_slab = (int)g.host.slab_mask.size();
     G_.n_mag = n_mag;
     G_.disjoint = 0;
+    G_.vertical = all_vertical(bf) ? 1 : 0;
     g.host.blk = std::move(rec);
     g.host.grid = std::move(grid);
     g.host.block_region = std::move(preg);
@@ -1180,8 +1186,7 @@ int mt_load_field(int32_t nx, int32_t ny, int32_t nz, const double *lo, const do
     std::lock_guard<std::mutex> lk(g.mu);
     int rc = MT_OK;
     if (!b) {
-        g.map.release();
-        g.nodes.release();
+        for (DevBuf *d : {&g.map, &g.mapv, &g.nodes, &g.nodesv}) d->release();
         g.T.field = mt::DevField{};
         tables_changed();
         return MT_OK;
@@ -1191,12 +1196,13 @@ int mt_load_field(int32_t nx, int32_t ny, int32_t nz, const double *lo, const do
     for (int a = 0; a < 3; ++a)
         if (!std::isfinite(lo[a]) || !std::isfinite(hi[a]) || !(hi[a] > lo[a]))
             return fail(MT_ERR_INVALID_ARG, "field bounds must be finite with hi > lo (axis %d)", a);
-    // Cell-major copy: every cell's trilinear interpolant in one 128-byte
+    // Cell-major table: every cell's trilinear interpolant in one 128-byte
     // record, as the coefficients k0..k7 of
     //   k0 + k1 fx + k2 fy + k3 fz + k4 fx fy + k5 fx fz + k6 fy fz + k7 fx fy fz
     // in the fractional coordinates of the cell (formed in FP64 from the 8
     // corner values, then rounded), so a lookup touches one cache line
-    // instead of four and evaluates 7 FMAs per component.
+    // instead of four and evaluates 7 FMAs per component.  A vertical map (bx =
+    // bz = 0 everywhere: dipoles) also gets by alone, a 32-byte record.
     const size_t cx = (size_t)nx - 1, cy = (size_t)ny - 1, cz = (size_t)nz - 1;
     const size_t cells = cx * cy * cz;
     if ((size_t)nx * ny * nz > 0x7FFFFFFFull)
@@ -1205,63 +1211,52 @@ int mt_load_field(int32_t nx, int32_t ny, int32_t nz, const double *lo, const do
     if ((size_t)nx >= (1u << 24) || (size_t)ny * nz >= (1u << 24))
         return fail(MT_ERR_LIMIT, "the field map needs nx < 2^24 and ny nz < 2^24 (cell and "
                                   "node indices are formed with 24-bit products)");
-    for (size_t i = 0; i < 3 * (size_t)nx * ny * nz; ++i)
+    const size_t n_nodes = (size_t)nx * ny * nz;
+    bool vertical = true;
+    for (size_t i = 0; i < 3 * n_nodes; ++i) {
         if (!std::isfinite(b[i]))
             return fail(MT_ERR_INVALID_ARG, "field map value %zu (node %zu, component %zu) is "
                                             "not finite", i, i / 3, i % 3);
-    std::vector<float4> m;
-    try {
-        m.resize(cells * 8);
-    } catch (const std::bad_alloc &) {
-        return fail(MT_ERR_OOM, "host memory for %zu field-map cells", cells);
+        if (i % 3 != 1 && b[i] != 0.0f) vertical = false;
     }
-    for (size_t k = 0; k < cz; ++k)
-        for (size_t j = 0; j < cy; ++j)
-            for (size_t i = 0; i < cx; ++i) {
-                float4 *rec = m.data() + ((k * cy + j) * cx + i) * 8;
-                float kc[8][3];
-                for (int a = 0; a < 3; ++a) {
-                    // corner values C[c], c = dx + 2 dy + 4 dz
-                    double C[8];
-                    for (int c = 0; c < 8; ++c) {
-                        const size_t node = ((k + (c >> 2)) * (size_t)ny + (j + ((c >> 1) & 1))) *
-                                                nx + (i + (c & 1));
-                        C[c] = (double)b[3 * node + a];
-                    }
-                    const double q[8] = {
-                        C[0],
-                        C[1] - C[0],
-                        C[2] - C[0],
-                        C[4] - C[0],
-                        C[3] - C[1] - C[2] + C[0],
-                        C[5] - C[1] - C[4] + C[0],
-                        C[6] - C[2] - C[4] + C[0],
-                        C[7] - C[3] - C[5] - C[6] + C[1] + C[2] + C[4] - C[0]};
-                    for (int c = 0; c < 8; ++c) {
-                        kc[c][a] = (float)q[c];
-                        if (!std::isfinite(kc[c][a]))
-                            return fail(MT_ERR_INVALID_ARG,
-                                        "field map cell (%zu, %zu, %zu): an interpolation "
-                                        "coefficient overflows single precision", i, j, k);
-                    }
-                }
-                for (int c = 0; c < 8; ++c) rec[c] = make_float4(kc[c][0], kc[c][1], kc[c][2], 0.f);
-            }
-    // Node-major copy for the nearest-node lookup (one value per lookup).
-    std::vector<float4> nd;
-    try {
-        nd.resize((size_t)nx * ny * nz);
-    } catch (const std::bad_alloc &) {
-        return fail(MT_ERR_OOM, "host memory for %zu field-map nodes", nd.size());
-    }
-    for (size_t i = 0; i < nd.size(); ++i)
-        nd[i] = make_float4(b[3 * i], b[3 * i + 1], b[3 * i + 2], 0.f);
+    // The tables are formed on the device from the node values (launch_map_tables);
+    // they replace the loaded map only once they are known to be good.
     if ((rc = ensure_device())) return rc;
-    if ((rc = g.map.upload(m.data(), m.size() * sizeof(float4)))) return rc;
-    if ((rc = g.nodes.upload(nd.data(), nd.size() * sizeof(float4)))) return rc;
+    DevBuf raw, bad, map, mapv, nodes, nodesv;
+    auto drop = [&](int code) {
+        for (DevBuf *d : {&raw, &bad, &map, &mapv, &nodes, &nodesv}) d->release();
+        return code;
+    };
+    const unsigned long long none = ~0ull;
+    unsigned long long first = none;
+    if ((rc = raw.upload(b, 3 * n_nodes * sizeof(float))) || (rc = bad.upload(&none, sizeof(none))) ||
+        (rc = map.ensure(cells * 8 * sizeof(float4))) ||
+        (rc = nodes.ensure(n_nodes * sizeof(float4))) ||
+        (vertical && (rc = mapv.ensure(cells * 2 * sizeof(float4)))) ||
+        (vertical && (rc = nodesv.ensure(n_nodes * sizeof(float)))))
+        return drop(rc);
+    const hipError_t e = mt::launch_map_tables(
+        reinterpret_cast<const float *>(raw.p), nx, ny, nz, reinterpret_cast<float4 *>(nodes.p),
+        reinterpret_cast<float *>(nodesv.p), reinterpret_cast<float4 *>(map.p),
+        reinterpret_cast<float4 *>(mapv.p), reinterpret_cast<unsigned long long *>(bad.p), nullptr);
+    if (e != hipSuccess || hipMemcpy(&first, bad.p, sizeof(first), hipMemcpyDeviceToHost) != hipSuccess)
+        return drop(fail(MT_ERR_HIP, "building the field map tables failed: %s",
+                         hipGetErrorString(e != hipSuccess ? e : hipGetLastError())));
+    if (first != none)
+        return drop(fail(MT_ERR_INVALID_ARG, "field map cell (%zu, %zu, %zu): an interpolation "
+                                             "coefficient overflows single precision",
+                         (size_t)first % cx, (size_t)first / cx % cy, (size_t)first / (cx * cy)));
+    std::swap(map, g.map);
+    std::swap(mapv, g.mapv);
+    std::swap(nodes, g.nodes);
+    std::swap(nodesv, g.nodesv);
+    drop(MT_OK);
     mt::DevField &F = g.T.field;
     F.map = reinterpret_cast<const float4 *>(g.map.p);
     F.nodes = reinterpret_cast<const float4 *>(g.nodes.p);
+    F.mapv = reinterpret_cast<const float4 *>(g.mapv.p);
+    F.nodesv = reinterpret_cast<const float *>(g.nodesv.p);
+    F.vertical = vertical ? 1 : 0;
     F.nx = nx;
     F.ny = ny;
     F.nz = nz;
@@ -1460,7 +1455,8 @@ const char *mt_last_error(void) { return g_err.c_str(); }
 void mt_release(void) {
     std::lock_guard<std::mutex> lk(g.mu);
     drop_graphs();
-    for (DevBuf *b : {&g.cdf, &g.guide, &g.alias, &g.nodes, &g.image, &g.map, &g.queue, &g.partial,
+    for (DevBuf *b : {&g.cdf, &g.guide, &g.alias, &g.nodes, &g.nodesv, &g.image, &g.map, &g.mapv,
+                      &g.queue, &g.partial,
                       &g.scratch, &g.gs_lane, &g.lists})
         b->release();
     g.host = {};

@@ -97,6 +97,7 @@ struct DevGeom {
     int32_t n_poly;              // > 0: the volumes are convex blocks
     int32_t gx, gy, gz;
     double g0[3], g1[3], ginv[3];   // grid origin, end and cells per metre
+    int32_t vertical;            // every volume's field has bx = bz = 0
     int32_t disjoint;            // no two boxes overlap: a box that holds a point is its box
     double x_max, y_max, z_max;
 };
@@ -106,6 +107,9 @@ struct DevField {
                                  // trilinear interpolant as coefficients of 1, fx, fy, fz, fx fy,
                                  // fx fz, fy fz, fx fy fz; nullptr = no map
     const float4 *nodes;         // node-major [nz][ny][nx] (bx, by, bz, 0), for the nearest node
+    int32_t vertical;            // every node has bx = bz = 0; then also:
+    const float4 *mapv;          // cell-major [..][2]: the 8 coefficients of by
+    const float *nodesv;         // node-major by
     int32_t nx, ny, nz;
     double lo[3];
     double inv_d[3];             // (n - 1) / (hi - lo)
@@ -188,6 +192,11 @@ hipError_t launch_pass(const Tables &T, const DevRun &R, const DevIO &io, int bl
 // Variant-wave form: groups of 2^R.share_shift lanes hold variants of one muon.
 hipError_t launch_variant_waves(const Tables &T, const DevRun &R, const DevIO &io, int block,
                                hipStream_t s);
+// Field map tables from the node values (device pointers; nodesv and mapv may be
+// nullptr).  *bad, set to ~0 beforehand, receives the lowest cell whose
+// coefficients overflow float.
+hipError_t launch_map_tables(const float *b, int nx, int ny, int nz, float4 *nodes, float *nodesv,
+                             float4 *map, float4 *mapv, unsigned long long *bad, hipStream_t s);
 hipError_t launch_queue_reset(unsigned long long *queue, double *zero, int64_t n_zero,
                               hipStream_t s);
 hipError_t launch_adjoint(const Tables &T, const DevRun &R, const DevIO &io,

@@ -772,6 +772,7 @@ __device__ __forceinline__ float3 add_map(const Tables &T, float3 B, double x, d
 // and rounded-up values fail it and take the exact lookup.  Same values and
 // arithmetic as map_cell + cell_field.  Outside the map the cell is empty
 // (all coefficients zero, no cell remembered).
+template <bool V>
 __device__ __forceinline__ float3 add_map_cached(Lane &L, const DevField &H, ArgPtr args, float3 B,
                                                  double x, double y, double z) {
     double u, v, w;
@@ -789,13 +790,26 @@ __device__ __forceinline__ float3 add_map_cached(Lane &L, const DevField &H, Arg
             // 24-bit products: the loader keeps nx and ny nz below 2^24
             const int cell = (int)__umul24(__umul24((uint32_t)k, (uint32_t)(F.ny - 1)) +
                                                (uint32_t)j, (uint32_t)(F.nx - 1)) + i;
-            const float4 *b = F.map + (size_t)cell * 8;
+            if constexpr (V) {
+                const float4 *b = F.mapv + (size_t)cell * 2;
+                const float4 p = b[0], r = b[1];
+                L.mc[0] = p.x;
+                L.mc[1] = p.y;
+                L.mc[2] = p.z;
+                L.mc[3] = p.w;
+                L.mc[4] = r.x;
+                L.mc[5] = r.y;
+                L.mc[6] = r.z;
+                L.mc[7] = r.w;
+            } else {
+                const float4 *b = F.map + (size_t)cell * 8;
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const float4 r = b[q];
-                L.mc[3 * q] = r.x;
-                L.mc[3 * q + 1] = r.y;
-                L.mc[3 * q + 2] = r.z;
+                for (int q = 0; q < 8; ++q) {
+                    const float4 r = b[q];
+                    L.mc[3 * q] = r.x;
+                    L.mc[3 * q + 1] = r.y;
+                    L.mc[3 * q + 2] = r.z;
+                }
             }
             L.ci = (float)i;
             L.cj = (float)j;
@@ -805,10 +819,15 @@ __device__ __forceinline__ float3 add_map_cached(Lane &L, const DevField &H, Arg
             c.fz = (float)(w - (double)k);
         } else {
 #pragma unroll
-            for (int q = 0; q < 24; ++q) L.mc[q] = 0.0f;
+            for (int q = 0; q < (V ? 8 : 24); ++q) L.mc[q] = 0.0f;
             L.ci = __builtin_nanf("");
             c.fx = c.fy = c.fz = 0.0f;
         }
+    }
+    if constexpr (V) {
+        const float by = cell_poly1(L.mc[0], L.mc[1], L.mc[2], L.mc[3], L.mc[4], L.mc[5], L.mc[6],
+                                    L.mc[7], c.fx, c.fy, c.fz);
+        return make_float3(0.0f, B.y + by, 0.0f);
     }
 #pragma unroll
     for (int q = 0; q < 8; ++q)
@@ -823,6 +842,7 @@ __device__ __forceinline__ float3 add_map_cached(Lane &L, const DevField &H, Arg
 // registers (mc[0..2]) and used while the point is less than half a spacing
 // from it on every axis; nodes on the map's border are not remembered, since
 // near them that test does not say whether the point is inside the map.
+template <bool V>
 __device__ __forceinline__ float3 add_nearest_cached(Lane &L, const DevField &H, ArgPtr args,
                                                      float3 B, double x, double y, double z) {
     double u, v, w;
@@ -838,7 +858,8 @@ __device__ __forceinline__ float3 add_nearest_cached(Lane &L, const DevField &H,
                       k = min((int)(w + 0.5), F.nz - 1);
             const int node = (int)__umul24(__umul24((uint32_t)k, (uint32_t)F.ny) + (uint32_t)j,
                                            (uint32_t)F.nx) + i;
-            q = F.nodes[node];
+            if constexpr (V) q.y = F.nodesv[node];
+            else q = F.nodes[node];
             if ((i > 0) & (i < F.nx - 1) & (j > 0) & (j < F.ny - 1) & (k > 0) & (k < F.nz - 1)) {
                 L.ci = (float)i;
                 L.cj = (float)j;
@@ -875,6 +896,27 @@ __device__ __forceinline__ float3 add3(float3 a, float3 b) {
     return make_float3(a.x + b.x, a.y + b.y, a.z + b.z);
 }
 
+// n x b and a h + k where the field may be known to be vertical (V: b.x = b.z =
+// 0, so the product has no y component): the general forms' values without
+// their multiplications by zero.
+template <bool V>
+__device__ __forceinline__ float3 cross_field(float3 n, float3 b) {
+    if constexpr (V) return make_float3(-n.z * b.y, 0.0f, n.x * b.y);
+    else return cross3(n, b);
+}
+
+template <bool V>
+__device__ __forceinline__ float3 axpy_field(float h, float3 k, float3 a) {
+    if constexpr (V) return make_float3(fmaf(h, k.x, a.x), a.y, fmaf(h, k.z, a.z));
+    else return axpy(h, k, a);
+}
+
+template <bool V>
+__device__ __forceinline__ float3 scale_field(float s, float3 b) {
+    if constexpr (V) return make_float3(0.0f, s * b.y, 0.0f);
+    else return scale3(s, b);
+}
+
 struct StepConst {
     float h, h2, h6, h3;   // d, d/2, d/6, d/3
 };
@@ -885,13 +927,16 @@ __device__ __forceinline__ float3 stage0(const Lane &L) {
 
 // Is any component of b non-zero?  One or of the three bit patterns and one
 // compare (the or is +-0 exactly when all three are).
+template <bool V>
 __device__ __forceinline__ bool non_zero(float3 b) {
+    if constexpr (V) return b.y != 0.0f;
     return __uint_as_float(__float_as_uint(b.x) | __float_as_uint(b.y) | __float_as_uint(b.z)) !=
            0.0f;
 }
 
 // a0 must be stage0(L) (the FP32 momentum the stages start from), cb = kq B
 // and bent = (B is not zero).
+template <bool V>
 __device__ __forceinline__ void rk4_from(Lane &L, float3 a0, float3 cb, bool bent,
                                          const StepConst &c) {
     const float r0 = __builtin_amdgcn_rsqf(norm2(a0));
@@ -902,25 +947,27 @@ __device__ __forceinline__ void rk4_from(Lane &L, float3 a0, float3 cb, bool ben
         dry = c.h * n0.y;
         drz = c.h * n0.z;
     } else {
-        const float3 k1 = cross3(n0, cb);
-        const float3 a1 = axpy(c.h2, k1, a0);
+        const float3 k1 = cross_field<V>(n0, cb);
+        const float3 a1 = axpy_field<V>(c.h2, k1, a0);
         const float3 n1 = scale3(__builtin_amdgcn_rsqf(norm2(a1)), a1);
-        const float3 k2 = cross3(n1, cb);
-        const float3 a2 = axpy(c.h2, k2, a0);
+        const float3 k2 = cross_field<V>(n1, cb);
+        const float3 a2 = axpy_field<V>(c.h2, k2, a0);
         const float3 n2 = scale3(__builtin_amdgcn_rsqf(norm2(a2)), a2);
-        const float3 k3 = cross3(n2, cb);
-        const float3 a3 = axpy(c.h, k3, a0);
+        const float3 k3 = cross_field<V>(n2, cb);
+        const float3 a3 = axpy_field<V>(c.h, k3, a0);
         const float3 n3 = scale3(__builtin_amdgcn_rsqf(norm2(a3)), a3);
-        const float3 k4 = cross3(n3, cb);
+        const float3 k4 = cross_field<V>(n3, cb);
         // h/6 (v1 + 2 v2 + 2 v3 + v4)
         drx = c.h6 * (fmaf(2.0f, n1.x + n2.x, n0.x) + n3.x);
         dry = c.h6 * (fmaf(2.0f, n1.y + n2.y, n0.y) + n3.y);
         drz = c.h6 * (fmaf(2.0f, n1.z + n2.z, n0.z) + n3.z);
         const float dpx = c.h6 * (fmaf(2.0f, k2.x + k3.x, k1.x) + k4.x);
-        const float dpy = c.h6 * (fmaf(2.0f, k2.y + k3.y, k1.y) + k4.y);
         const float dpz = c.h6 * (fmaf(2.0f, k2.z + k3.z, k1.z) + k4.z);
         L.px += (double)dpx;
-        L.py += (double)dpy;
+        if constexpr (!V) {
+            const float dpy = c.h6 * (fmaf(2.0f, k2.y + k3.y, k1.y) + k4.y);
+            L.py += (double)dpy;
+        }
         L.pz += (double)dpz;
     }
     // the position update is shared by both branches (keeps every Lane field
@@ -941,24 +988,26 @@ enum : unsigned {
     kStages = 32u,   // field evaluated at every RK4 stage position
     kPoly = 64u,     // convex-block geometry instead of boxes
     kLog = 128u,     // a histogram axis is binned in log10
-    kFeatures = 256u,// number of masks
-    kShared = 256u   // the step's Philox words come from the caller (not a mask bit)
+    kVert = 256u,    // every field (boxes, blocks and map) is vertical: B = (0, By, 0)
+    kFeatures = 512u,// number of masks
+    kShared = 512u   // the step's Philox words come from the caller (not a mask bit)
 };
 
 // Masks that have a kernel: the tape belongs to the differentiable form,
 // whose adjoint holds the trilinear field over each step, and the
-// nearest-node lookup needs a map.
+// nearest-node lookup needs a map; traces (a debugging aid) run the general
+// field.
 constexpr bool valid_mask(unsigned F) {
     return !((F & kTape) && (F & (kNearest | kStages))) && !((F & kNearest) && !(F & kMap)) &&
-           !((F & kPoly) && (F & (kTape | kStages)));
+           !((F & kPoly) && (F & (kTape | kStages))) && !((F & kVert) && (F & kTrace));
 }
 
 // The map part of the field, added to the volume's, through the lane's cell.
 template <unsigned F>
 __device__ __forceinline__ float3 with_map(Lane &L, const KArgs &A, ArgPtr args, float3 B, double x,
                                            double y, double z) {
-    if constexpr ((F & kNearest) != 0) return add_nearest_cached(L, A.T.field, args, B, x, y, z);
-    else if constexpr ((F & kMap) != 0) return add_map_cached(L, A.T.field, args, B, x, y, z);
+    if constexpr ((F & kNearest) != 0) return add_nearest_cached<(F & kVert) != 0>(L, A.T.field, args, B, x, y, z);
+    else if constexpr ((F & kMap) != 0) return add_map_cached<(F & kVert) != 0>(L, A.T.field, args, B, x, y, z);
     else return B;
 }
 
@@ -984,13 +1033,14 @@ __device__ __forceinline__ float3 field_at_point(const KArgs &A, ArgPtr args, La
 template <unsigned F, typename V>
 __device__ __forceinline__ void rk4_stages(Lane &L, V &&var, float3 B1, const KArgs &A, ArgPtr args,
                                            const StepConst &c) {
+    constexpr bool VERT = (F & kVert) != 0;
     const float kq = L.kq;
     const float reach = 1.001f * c.h;
     const bool inside = fmaxf(fmaxf(fmaf(reach, L.ix, fabsf(L.xr)), fmaf(reach, L.iy, fabsf(L.yr))),
                               fmaf(reach, L.iz, fabsf(L.zr))) < 1.0f;
     const float3 a0 = stage0(L);
     const float3 n0 = scale3(__builtin_amdgcn_rsqf(norm2(a0)), a0);
-    const float3 k1 = cross3(n0, scale3(kq, B1));
+    const float3 k1 = cross_field<VERT>(n0, scale_field<VERT>(kq, B1));
     float3 n = n0, kk = k1;                     // direction and slope of the last stage
     float3 n12 = make_float3(0.f, 0.f, 0.f), k12 = n12;
     // one copy of the stage (its field lookup holds two cold paths)
@@ -999,9 +1049,9 @@ __device__ __forceinline__ void rk4_stages(Lane &L, V &&var, float3 B1, const KA
         const float cs = st == 3 ? c.h : c.h2;
         const float3 B = field_at_point<F>(A, args, L, inside, var, L.x + (double)(cs * n.x),
                                            L.y + (double)(cs * n.y), L.z + (double)(cs * n.z));
-        const float3 a = axpy(cs, kk, a0);
+        const float3 a = axpy_field<VERT>(cs, kk, a0);
         n = scale3(__builtin_amdgcn_rsqf(norm2(a)), a);
-        kk = cross3(n, scale3(kq, B));
+        kk = cross_field<VERT>(n, scale_field<VERT>(kq, B));
         if (st == 1) {
             n12 = n;
             k12 = kk;
@@ -1013,7 +1063,7 @@ __device__ __forceinline__ void rk4_stages(Lane &L, V &&var, float3 B1, const KA
     const float drx = c.h6 * (fmaf(2.0f, n12.x, n0.x) + n.x);
     const float dry = c.h6 * (fmaf(2.0f, n12.y, n0.y) + n.y);
     L.px += (double)(c.h6 * (fmaf(2.0f, k12.x, k1.x) + kk.x));
-    L.py += (double)(c.h6 * (fmaf(2.0f, k12.y, k1.y) + kk.y));
+    if constexpr (!VERT) L.py += (double)(c.h6 * (fmaf(2.0f, k12.y, k1.y) + kk.y));
     L.pz += (double)(c.h6 * (fmaf(2.0f, k12.z, k1.z) + kk.z));
     const float drz = c.h6 * (fmaf(2.0f, n12.z, n0.z) + n.z);
     move_in_region(L, drx, dry, drz);
@@ -1100,7 +1150,7 @@ __device__ __forceinline__ bool locate_region(Lane &L, V &&var, int k, double p2
         }
         if (vol != old) {
             const float3 b = box_field(T, S, R, vol, var());
-            L.bent = non_zero(b);
+            L.bent = non_zero<(F & kVert) != 0>(b);
             const float s = kScaledField<F> ? L.kq : 1.0f;
             L.bx = s * b.x;
             L.by = s * b.y;
@@ -1144,7 +1194,7 @@ template <unsigned F, typename V>
 __device__ __forceinline__ bool advance(Lane &L, int64_t g, V &&var, int k, const KArgs &A,
                                         ArgPtr args, const StepConst &sc,
                                         uint4 w_shared = uint4{}) {
-    constexpr bool TAPE = (F & kTape) != 0, TRACE = (F & kTrace) != 0;
+    constexpr bool TAPE = (F & kTape) != 0, TRACE = (F & kTrace) != 0, VERT = (F & kVert) != 0;
     const DevHist &H = A.T.hist;
     const DevRun &R = A.R;
     const double p2 = L.px * L.px + L.py * L.py + L.pz * L.pz;
@@ -1227,11 +1277,11 @@ __device__ __forceinline__ bool advance(Lane &L, int64_t g, V &&var, int k, cons
     }
     const float3 b = make_float3(L.bx, L.by, L.bz);
     if constexpr (kScaledField<F>) {
-        rk4_from(L, stage0(L), b, L.bent, sc);
+        rk4_from<VERT>(L, stage0(L), b, L.bent, sc);
     } else {
         const float3 B = with_map<F>(L, A, args, b, L.x, L.y, L.z);
         if constexpr ((F & kStages) != 0) rk4_stages<F>(L, var, B, A, args, sc);
-        else rk4_from(L, stage0(L), scale3(L.kq, B), non_zero(B), sc);
+        else rk4_from<VERT>(L, stage0(L), scale_field<VERT>(L.kq, B), non_zero<VERT>(B), sc);
     }
     return true;
 }
@@ -1663,7 +1713,7 @@ __device__ __forceinline__ int replay_step(Lane &L, int k, const Tables &T, cons
         if (vol != L.vol) {
             L.vol = vol;
             const float3 b = box_field(T, S, R, vol, var);
-            L.bent = non_zero(b);
+            L.bent = non_zero<false>(b);
             const float s = MAP ? 1.0f : L.kq;
             L.bx = s * b.x;
             L.by = s * b.y;
@@ -1678,9 +1728,9 @@ __device__ __forceinline__ int replay_step(Lane &L, int k, const Tables &T, cons
     const float3 b = make_float3(L.bx, L.by, L.bz);
     if (MAP) {
         const float3 B = add_map<MAP>(T, b, L.x, L.y, L.z);
-        rk4_from(L, stage0(L), scale3(L.kq, B), non_zero(B), sc);
+        rk4_from<false>(L, stage0(L), scale3(L.kq, B), non_zero<false>(B), sc);
     } else {
-        rk4_from(L, stage0(L), b, L.bent, sc);
+        rk4_from<false>(L, stage0(L), b, L.bent, sc);
     }
     return L.vol;
 }
@@ -1874,6 +1924,58 @@ k_adjoint(Tables T, DevRun R, DevIO io, const double *g_out,
 }
 
 // ---------------------------------------------------------------------------
+// Field map tables from the node values b [nz][ny][nx][3].
+// ---------------------------------------------------------------------------
+__global__ void k_map_nodes(const float *b, int64_t n, float4 *nodes, float *nodesv) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    nodes[i] = make_float4(b[3 * i], b[3 * i + 1], b[3 * i + 2], 0.f);
+    if (nodesv) nodesv[i] = b[3 * i + 1];
+}
+
+// One thread per cell: the coefficients of its trilinear interpolant (see
+// CellPoly), formed in FP64 from the 8 corner values and rounded.  The lowest
+// cell with a coefficient that overflows float goes to *bad.
+__global__ void k_map_cells(const float4 *nodes, int nx, int ny, int nz, float4 *map, float4 *mapv,
+                            unsigned long long *bad) {
+    const int64_t cell = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t cx = nx - 1, cy = ny - 1;
+    if (cell >= cx * cy * (nz - 1)) return;
+    const int64_t i = cell % cx, j = cell / cx % cy, k = cell / (cx * cy);
+    float kc[3][8];
+    bool ok = true;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        double C[8];                             // corner c = dx + 2 dy + 4 dz
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const float4 v = nodes[((k + (c >> 2)) * ny + (j + ((c >> 1) & 1))) * nx + (i + (c & 1))];
+            C[c] = (double)(a == 0 ? v.x : a == 1 ? v.y : v.z);
+        }
+        const double q[8] = {C[0],
+                             C[1] - C[0],
+                             C[2] - C[0],
+                             C[4] - C[0],
+                             C[3] - C[1] - C[2] + C[0],
+                             C[5] - C[1] - C[4] + C[0],
+                             C[6] - C[2] - C[4] + C[0],
+                             C[7] - C[3] - C[5] - C[6] + C[1] + C[2] + C[4] - C[0]};
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            kc[a][c] = (float)q[c];
+            ok = ok && isfinite(kc[a][c]);
+        }
+    }
+    if (!ok) atomicMin(bad, (unsigned long long)cell);
+#pragma unroll
+    for (int c = 0; c < 8; ++c) map[cell * 8 + c] = make_float4(kc[0][c], kc[1][c], kc[2][c], 0.f);
+    if (mapv) {
+        mapv[cell * 2] = make_float4(kc[1][0], kc[1][1], kc[1][2], kc[1][3]);
+        mapv[cell * 2 + 1] = make_float4(kc[1][4], kc[1][5], kc[1][6], kc[1][7]);
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Deterministic per-variant sums (fixed chunking and fixed tree order).
 // ---------------------------------------------------------------------------
 constexpr int kRedBlock = 256;
@@ -2011,7 +2113,8 @@ static unsigned feature_mask(const Tables &T, const DevRun &R) {
            (R.n_trace > 0 ? kTrace : 0u) | (R.sampler == MT_SAMPLER_ALIAS ? kAlias : 0u) |
            (map && R.interp == MT_INTERP_NEAREST ? kNearest : 0u) |
            (R.stage_field ? kStages : 0u) | (T.geom.n_poly > 0 ? kPoly : 0u) |
-           (T.hist.log_loss || T.hist.log_scat ? kLog : 0u);
+           (T.hist.log_loss || T.hist.log_scat ? kLog : 0u) |
+           (T.geom.vertical && (!map || T.field.vertical) && R.n_trace == 0 ? kVert : 0u);
 }
 
 hipError_t launch_plain(const Tables &T, const DevRun &R, const DevIO &io, int block,
@@ -2060,6 +2163,16 @@ hipError_t launch_variant_waves(const Tables &T, const DevRun &R, const DevIO &i
     if (fn == nullptr) return hipErrorInvalidValue;     // excluded by argument validation
     const size_t lds = (size_t)T.lds.bytes + (size_t)block * sizeof(uint4);
     return hipLaunchKernel(fn, dim3(grid), dim3(block), args, lds, s);
+}
+
+hipError_t launch_map_tables(const float *b, int nx, int ny, int nz, float4 *nodes, float *nodesv,
+                             float4 *map, float4 *mapv, unsigned long long *bad, hipStream_t s) {
+    const int64_t n = (int64_t)nx * ny * nz, cells = (int64_t)(nx - 1) * (ny - 1) * (nz - 1);
+    hipLaunchKernelGGL(k_map_nodes, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, b, n, nodes,
+                       nodesv);
+    hipLaunchKernelGGL(k_map_cells, dim3((unsigned)((cells + 255) / 256)), dim3(256), 0, s, nodes,
+                       nx, ny, nz, map, mapv, bad);
+    return hipGetLastError();
 }
 
 hipError_t launch_queue_reset(unsigned long long *queue, double *zero, int64_t n_zero,
