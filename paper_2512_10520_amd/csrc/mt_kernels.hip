@@ -226,6 +226,9 @@ struct Lane {
     bool bent;            // that field is not zero
     int32_t steps, status, slab, vol;
     PhiloxPrefix ph;
+    uint4 w;              // random words of the next step and the entry of the sampler's table
+    uint2 e;              // they select in row eh (kVacuum: neither), see advance
+    uint32_t eh;
     float ci, cj, ck;     // field-map cell (or node) whose values are in mc; NaN: none
     float mc[24];         // its coefficients (bx, by, bz) x 8 (or the node's value)
 };
@@ -238,6 +241,7 @@ __device__ __forceinline__ void reset_lane_caches(Lane &L) {
     L.rec = 0u;
     L.plo = L.pspan = 0u;
     L.hoff = kVacuum;
+    L.eh = kVacuum;
     L.tot = 0u;
     L.slab = -1;
     L.vol = -2;
@@ -600,13 +604,16 @@ __device__ __forceinline__ int find_bin(const Lds &S, int P, double p2, int i) {
 // The guide entry of the word's top bits brackets c in [lo, hi] and carries
 // C[lo]: t < C[lo] gives lo at once, a bracket of two cells gives hi, and only
 // wider brackets probe C.
-__device__ __forceinline__ int sample_cell(const DevHist &H, uint32_t hoff, uint32_t T,
-                                           uint32_t w0) {
-    const uint32_t t = __umulhi(w0, T);
+__device__ __forceinline__ uint2 guide_entry(const DevHist &H, uint32_t hoff, uint32_t w0) {
     // hoff = 8 h << gbits < 2^31 (h < 2^12, gbits <= 16): the entry's byte
     // offset is a 32-bit number
     const uint32_t at = hoff | ((w0 >> (29 - H.gbits)) & ~7u);
-    const uint2 e = *reinterpret_cast<const uint2 *>(reinterpret_cast<const char *>(H.guide) + at);
+    return *reinterpret_cast<const uint2 *>(reinterpret_cast<const char *>(H.guide) + at);
+}
+
+__device__ __forceinline__ int sample_cell(const DevHist &H, uint2 e, uint32_t hoff, uint32_t T,
+                                           uint32_t w0) {
+    const uint32_t t = __umulhi(w0, T);
     int lo = (int)(e.x & 0xFFFFu);
     int hi = (int)(e.x >> 16);
     if (t < e.y) return lo;
@@ -624,10 +631,14 @@ __device__ __forceinline__ int sample_cell(const DevHist &H, uint32_t hoff, uint
 // (low bytes of w1, w2, w3, which the jitters and the azimuth leave unused)
 // keeps cell j when x is below the column's split, else gives its alias.
 // One 8-byte load per draw, its byte offset 8 (h K + j) < 2^31.
-__device__ __forceinline__ int alias_cell(const DevHist &H, uint32_t h, uint4 w) {
-    const uint32_t j = __umulhi(w.x, (uint32_t)H.n_cells);
-    const uint2 e = *reinterpret_cast<const uint2 *>(
+__device__ __forceinline__ uint2 alias_entry(const DevHist &H, uint32_t h, uint32_t w0) {
+    const uint32_t j = __umulhi(w0, (uint32_t)H.n_cells);
+    return *reinterpret_cast<const uint2 *>(
         reinterpret_cast<const char *>(H.alias) + 8u * (__umul24(h, (uint32_t)H.n_cells) + j));
+}
+
+__device__ __forceinline__ int alias_cell(const DevHist &H, uint2 e, uint4 w) {
+    const uint32_t j = __umulhi(w.x, (uint32_t)H.n_cells);
     const uint32_t x = (w.y & 0xFFu) | ((w.z & 0xFFu) << 8) | ((w.w & 0xFFu) << 16);
     return (int)(x < e.x ? j : e.y);
 }
@@ -990,6 +1001,7 @@ enum : unsigned {
     kLog = 128u,     // a histogram axis is binned in log10
     kVert = 256u,    // every field (boxes, blocks and map) is vertical: B = (0, By, 0)
     kFeatures = 512u,// number of masks
+    kPasses = 1024u, // the kernel runs passes (not a mask bit)
     kShared = 512u   // the step's Philox words come from the caller (not a mask bit)
 };
 
@@ -1102,6 +1114,18 @@ __device__ __forceinline__ uint32_t hist_of(const Lane &L, int gbits) {
     return (F & kAlias) ? L.hoff : L.hoff >> (gbits + 3);
 }
 
+// Words and table entry of the next step formed ahead, during this one (see
+// advance): hides the load's latency where few waves share a SIMD (2000 block
+// muons 284 -> 252 us, 123 457 with aliases 322 -> 298, 10^6 1350 -> 1302, 250
+// 007 shield muons in the plain form 3.30 -> 3.17 ms).  Not in the variant-wave
+// form, whose words come from LDS; and not where the seven registers it takes
+// cost more: with a general map (trilinear 3.80 -> 4.39 ms, nearest node, 10^6
+// muons, 9.20 -> 9.48), the field at every stage (7.30 -> 7.41 ms) and the
+// passes over a map, whose waves hide it anyway (10^7 muons 77.7 -> 78.0 ms).
+template <unsigned F>
+constexpr bool kAhead = !(F & (kShared | kStages)) &&
+                        (!(F & kMap) || ((F & kVert) && !(F & kPasses)));
+
 // The exact tests of a step that the lane's region or momentum band does not
 // decide.
 template <unsigned F, typename V>
@@ -1190,6 +1214,32 @@ __device__ __forceinline__ bool locate_region(Lane &L, V &&var, int k, double p2
     return true;
 }
 
+// A muon that went into the next lower bin of the same volume (3-4 % of steps,
+// so some lane of a wavefront in most of them): the histogram before its own,
+// whose band is above the threshold.  A momentum below a material's bin 0 is
+// below that row's band too.
+template <unsigned F>
+__device__ __forceinline__ void next_lower_bin(Lane &L, uint32_t pb, const KArgs &A) {
+    if ((pb < L.plo) & (L.hoff != kVacuum)) {
+        const uint32_t h = max(hist_of<F>(L, A.T.hist.gbits), 1u) - 1u;
+        const char *lds = lds_base();
+        const uint2 r = reinterpret_cast<const uint2 *>(lds + A.T.lds.off_band)[h];
+        if (pb - r.x < r.y) {
+            L.hoff -= row_of<F>(A.T.hist.gbits);
+            if constexpr ((F & kAlias) == 0)
+                L.tot = reinterpret_cast<const uint32_t *>(lds + A.T.lds.off_tot)[h];
+            L.plo = r.x;
+            L.pspan = r.y;
+        }
+    }
+}
+
+template <unsigned F>
+__device__ __forceinline__ uint2 sampler_entry(const DevHist &H, uint32_t hoff, uint32_t w0) {
+    if constexpr ((F & kAlias) != 0) return alias_entry(H, hoff, w0);
+    else return guide_entry(H, hoff, w0);
+}
+
 template <unsigned F, typename V>
 __device__ __forceinline__ bool advance(Lane &L, int64_t g, V &&var, int k, const KArgs &A,
                                         ArgPtr args, const StepConst &sc,
@@ -1205,37 +1255,34 @@ __device__ __forceinline__ bool advance(Lane &L, int64_t g, V &&var, int k, cons
     outside |= k >= R.max_steps;
     const uint32_t pb = __float_as_uint(p2f);
     if (outside | (pb - L.plo >= L.pspan)) {
-        // Mostly a muon that went into the next lower bin of the same volume
-        // (3-4 % of steps, so some lane of a wavefront in most of them): the
-        // histogram before its own, whose band is above the threshold.  A
-        // momentum below a material's bin 0 is below that row's band too.
         // |p| so small or large that the step's FP32 arithmetic may give positions
         // that are not finite: everything in FP64
         outside |= !((p2f >= kBandLow) & (p2f < INFINITY));
-        if (!outside & (pb < L.plo) & (L.hoff != kVacuum)) {
-            const uint32_t h = max(hist_of<F>(L, H.gbits), 1u) - 1u;
-            const char *lds = lds_base();
-            const uint2 r = reinterpret_cast<const uint2 *>(lds + A.T.lds.off_band)[h];
-            if (pb - r.x < r.y) {
-                L.hoff -= row_of<F>(H.gbits);
-                if constexpr ((F & kAlias) == 0)
-                    L.tot = reinterpret_cast<const uint32_t *>(lds + A.T.lds.off_tot)[h];
-                L.plo = r.x;
-                L.pspan = r.y;
-            }
-        }
+        if (!outside) next_lower_bin<F>(L, pb, A);
         if (outside | (pb - L.plo >= L.pspan)) {
             if (!locate_region<F>(L, var, k, p2, p2f, outside, args)) return false;
         }
     }
     float ux = 0.0f, uy = 0.0f, uz = 0.0f;
-    int cell = -1;
+    int cell = -1, bin = -1;
+    if (TRACE && L.hoff != kVacuum) bin = (int)(hist_of<F>(L, H.gbits) % (uint32_t)H.n_pbin);
     if (L.hoff != kVacuum) {
         uint4 w;
-        if constexpr ((F & kShared) != 0) w = w_shared;
-        else w = philox_step(L.ph, (uint32_t)k, R.key0, R.key1);
-        if constexpr ((F & kAlias) != 0) cell = alias_cell(H, L.hoff, w);
-        else cell = sample_cell(H, L.hoff, L.tot, w.x);
+        uint2 e;
+        if constexpr (!kAhead<F>) {
+            if constexpr ((F & kShared) != 0) w = w_shared;
+            else w = philox_step(L.ph, (uint32_t)k, R.key0, R.key1);
+            e = sampler_entry<F>(H, L.hoff, w.x);
+        } else {
+            if (L.eh != L.hoff) {        // a new volume, or a bin not foreseen
+                if (L.eh == kVacuum) L.w = philox_step(L.ph, (uint32_t)k, R.key0, R.key1);
+                L.e = sampler_entry<F>(H, L.hoff, L.w.x);
+            }
+            w = L.w;
+            e = L.e;
+        }
+        if constexpr ((F & kAlias) != 0) cell = alias_cell(H, e, w);
+        else cell = sample_cell(H, e, L.hoff, L.tot, w.x);
         // loss index = floor(cell / n_scat) = floor((cell + 1/2) / n_scat) in
         // FP32: exact for cell < 2^16 and every n_scat (the quotient is at
         // least 1 / (2 n_scat) from an integer, its error below 2^-6 / n_scat)
@@ -1262,6 +1309,19 @@ __device__ __forceinline__ bool advance(Lane &L, int64_t g, V &&var, int k, cons
         uy = tau * sn;
         uz = -f;
         kick(L, p2f, ux, uy, uz);
+        if constexpr (kAhead<F>) {
+            // The next step's words, and its table entry on its way while this
+            // step's Runge-Kutta stages run: they turn the momentum and keep
+            // its size, so the bin of the kicked momentum is the next step's
+            // but for rounding (and a new volume), which the next step checks.
+            const uint32_t q = __float_as_uint(norm2(stage0(L)));
+            if (q - L.plo >= L.pspan) next_lower_bin<F>(L, q, A);
+            L.w = philox_step(L.ph, (uint32_t)k + 1u, R.key0, R.key1);
+            L.e = sampler_entry<F>(H, L.hoff, L.w.x);
+            L.eh = L.hoff;
+        }
+    } else {
+        L.eh = kVacuum;
     }
     if (TAPE) {   // the local kick; the replay finds the volume again from the state
         float *t = R.tape + ((size_t)k * R.lanes + g) * 3;
@@ -1272,7 +1332,7 @@ __device__ __forceinline__ bool advance(Lane &L, int64_t g, V &&var, int k, cons
     if (TRACE && g < R.n_trace && k < R.trace_steps) {
         int32_t *tr = R.trace + ((size_t)g * R.trace_steps + k) * 3;
         tr[0] = L.vol;
-        tr[1] = L.hoff != kVacuum ? (int)(hist_of<F>(L, H.gbits) % (uint32_t)H.n_pbin) : -1;
+        tr[1] = bin;
         tr[2] = cell;
     }
     const float3 b = make_float3(L.bx, L.by, L.bz);
@@ -1424,7 +1484,7 @@ k_pass(KArgs A) {
                 return (int)variant_of(c->P.n_in ? c->P.in[i] : i, c->R);
             };
             for (int k = P.k_begin;; ++k) {
-                if (!advance<F>(L, g, var, k, A, args, sc)) break;
+                if (!advance<F | kPasses>(L, g, var, k, A, args, sc)) break;
             }
         }
         const ArgPtr c = cold(args);
