@@ -344,6 +344,7 @@ int validate(const mt_params *p, int64_t n, const mt_muons *in, const mt_muons *
     R.share_shift = 0;
     while (R.share_shift < 6 && p->n_variants % (2 << R.share_shift) == 0) ++R.share_shift;
     R.pmin2 = p->p_min * p->p_min;
+    R.ahead = c.lanes <= 5 * 64 * 4 * (int64_t)g.cu_count ? 1 : 0;     // see kAhead
     R.max_steps = p->max_steps;
     R.key0 = (uint32_t)p->seed;
     R.key1 = (uint32_t)(p->seed >> 32);
@@ -392,7 +393,9 @@ void pass_plan(int max_steps, int compact, int *S, int *P) {
 // compacting form runs the whole step range as one pass.
 int enqueue_ws(const mt_params *p, const Call &c, hipStream_t s, unsigned long long *counters,
                char *lists, double *partial) {
-    if (p->mode == MT_MODE_PERSISTENT) {
+    if (c.R.solo) {
+        MT_HIP(mt::launch_variant_waves(g.T, c.R, c.io, c.block, s));
+    } else if (p->mode == MT_MODE_PERSISTENT) {
         int S = 0, P = 1;
         pass_plan(p->max_steps, lists ? c.compact : p->max_steps + 1, &S, &P);
         if (P > 1)
@@ -448,6 +451,38 @@ int prepare_workspace(const mt_params *p, const Call &c) {
     return MT_OK;
 }
 
+// Launch shape of a plain or compacting call whose muons do not fill the chip
+// (no block, pass length or tuned choice given).
+//
+// Passes: while every muon is resident at once (5 waves a SIMD), a batch stays
+// together in z by itself and a pass only adds a launch and its last, lonely
+// waves: one pass over the whole range.  Measured passes of 128 steps against
+// one: shield 100 000 muons 3.22 / 2.47 ms, 250 000 3.76 / 3.17, but 500 000
+// 5.37 / 6.00; field at every stage 100 000 7.32 / 6.41, 300 000 8.90 / 8.75,
+// 600 000 14.3 / 16.6; convex blocks 250 000 4.51 / 3.20.
+//
+// Lone muons: below one wave a SIMD a step costs its latency, to which each
+// lane of a wave that leaves its bin, probes the table or changes volume adds
+// its own detour.  So the muons are spread over the SIMDs, 64 / 2^s to a wave
+// (variant-wave kernel), and the idle lanes form the random words of the next
+// 2^s steps.  s brings the launch to one wave a SIMD: 2000 block muons 252 ->
+// 193 us (s = 5; 205 at s = 4, 225 at s = 2); 20 000 shield muons 2.20 -> 2.03
+// ms.  Where lanes hardly diverge it pays only well below that: 10^4 parallel
+// muons 38.6 -> 39.6 us, 20 000 block muons 256 -> 247, hence the lower limit
+// without a map or blocks.
+void shape_small(const mt_params *p, Call &c) {
+    const int64_t wave = 64, simds = 4 * (int64_t)g.cu_count;
+    if (p->mode == MT_MODE_PERSISTENT && c.lanes <= 5 * wave * simds) c.compact = p->max_steps + 1;
+    const bool diverging = g.T.field.map != nullptr || g.T.geom.n_poly > 0;
+    const int64_t most = wave * simds / (diverging ? 2 : 8);
+    if (p->mode == MT_MODE_VARIANT_WAVES || c.R.n_trace > 0 || c.lanes > most) return;
+    c.R.solo = 1;
+    c.R.share_shift = 0;
+    while (c.R.share_shift < 5 && c.lanes << (c.R.share_shift + 1) <= wave * simds)
+        ++c.R.share_shift;
+    c.block = 64;
+}
+
 const TuneEntry *find_tuned(const std::vector<unsigned char> &key) {
     for (auto &t : g.tuned)
         if (t.key == key) return &t;
@@ -494,10 +529,13 @@ int propagate_impl(const mt_params *p, int64_t n, const mt_muons *in, mt_muons *
         }
         return MT_OK;
     }
-    if (p->mode != MT_MODE_PLAIN && p->block == 0 && p->compact_every == 0) {
-        if (const TuneEntry *t = find_tuned(tune_key(p, n))) {
+    if (p->block == 0 && p->compact_every == 0 && !force_block && !force_compact) {
+        const TuneEntry *t = p->mode != MT_MODE_PLAIN ? find_tuned(tune_key(p, n)) : nullptr;
+        if (t) {
             c.block = t->block;
             c.compact = t->compact;
+        } else {
+            shape_small(p, c);
         }
     }
     if (force_block) c.block = force_block;

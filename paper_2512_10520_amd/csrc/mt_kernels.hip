@@ -1001,8 +1001,8 @@ enum : unsigned {
     kLog = 128u,     // a histogram axis is binned in log10
     kVert = 256u,    // every field (boxes, blocks and map) is vertical: B = (0, By, 0)
     kFeatures = 512u,// number of masks
-    kPasses = 1024u, // the kernel runs passes (not a mask bit)
-    kShared = 512u   // the step's Philox words come from the caller (not a mask bit)
+    kPasses = 512u,  // the kernel runs passes (not a mask bit)
+    kNow = 1024u     // the step's draw is not formed ahead (not a mask bit)
 };
 
 // Masks that have a kernel: the tape belongs to the differentiable form,
@@ -1117,13 +1117,15 @@ __device__ __forceinline__ uint32_t hist_of(const Lane &L, int gbits) {
 // Words and table entry of the next step formed ahead, during this one (see
 // advance): hides the load's latency where few waves share a SIMD (2000 block
 // muons 284 -> 252 us, 123 457 with aliases 322 -> 298, 10^6 1350 -> 1302, 250
-// 007 shield muons in the plain form 3.30 -> 3.17 ms).  Not in the variant-wave
-// form, whose words come from LDS; and not where the seven registers it takes
-// cost more: with a general map (trilinear 3.80 -> 4.39 ms, nearest node, 10^6
+// 007 shield muons in the plain form 3.30 -> 3.17 ms).  Not where the seven
+// registers it takes cost more: with a general map (trilinear 3.80 -> 4.39 ms, nearest node, 10^6
 // muons, 9.20 -> 9.48), the field at every stage (7.30 -> 7.41 ms) and the
 // passes over a map, whose waves hide it anyway (10^7 muons 77.7 -> 78.0 ms).
+// The variant-wave form has kernels with and without (DevRun::ahead): 12
+// variants of 20 011 muons 427 -> 417 us, but 64 of 131 072, which fill the chip,
+// 7.72 -> 8.05 ms with it.
 template <unsigned F>
-constexpr bool kAhead = !(F & (kShared | kStages)) &&
+constexpr bool kAhead = !(F & (kStages | kNow)) &&
                         (!(F & kMap) || ((F & kVert) && !(F & kPasses)));
 
 // The exact tests of a step that the lane's region or momentum band does not
@@ -1240,10 +1242,10 @@ __device__ __forceinline__ uint2 sampler_entry(const DevHist &H, uint32_t hoff, 
     else return guide_entry(H, hoff, w0);
 }
 
-template <unsigned F, typename V>
-__device__ __forceinline__ bool advance(Lane &L, int64_t g, V &&var, int k, const KArgs &A,
-                                        ArgPtr args, const StepConst &sc,
-                                        uint4 w_shared = uint4{}) {
+// var() gives the lane's variant, words(k) the Philox words of step k.
+template <unsigned F, typename V, typename W>
+__device__ __forceinline__ bool advance(Lane &L, int64_t g, V &&var, W &&words, int k,
+                                        const KArgs &A, ArgPtr args, const StepConst &sc) {
     constexpr bool TAPE = (F & kTape) != 0, TRACE = (F & kTrace) != 0, VERT = (F & kVert) != 0;
     const DevHist &H = A.T.hist;
     const DevRun &R = A.R;
@@ -1270,12 +1272,11 @@ __device__ __forceinline__ bool advance(Lane &L, int64_t g, V &&var, int k, cons
         uint4 w;
         uint2 e;
         if constexpr (!kAhead<F>) {
-            if constexpr ((F & kShared) != 0) w = w_shared;
-            else w = philox_step(L.ph, (uint32_t)k, R.key0, R.key1);
+            w = words(k);
             e = sampler_entry<F>(H, L.hoff, w.x);
         } else {
             if (L.eh != L.hoff) {        // a new volume, or a bin not foreseen
-                if (L.eh == kVacuum) L.w = philox_step(L.ph, (uint32_t)k, R.key0, R.key1);
+                if (L.eh == kVacuum) L.w = words(k);
                 L.e = sampler_entry<F>(H, L.hoff, L.w.x);
             }
             w = L.w;
@@ -1316,7 +1317,7 @@ __device__ __forceinline__ bool advance(Lane &L, int64_t g, V &&var, int k, cons
             // but for rounding (and a new volume), which the next step checks.
             const uint32_t q = __float_as_uint(norm2(stage0(L)));
             if (q - L.plo >= L.pspan) next_lower_bin<F>(L, q, A);
-            L.w = philox_step(L.ph, (uint32_t)k + 1u, R.key0, R.key1);
+            L.w = words(k + 1);
             L.e = sampler_entry<F>(H, L.hoff, L.w.x);
             L.eh = L.hoff;
         }
@@ -1404,9 +1405,10 @@ k_plain(KArgs A) {
     load_lane(L, g, A.io, R);
     if (L.status == MT_ST_RUNNING) {
         auto var = [&] { return (int)variant_of(g, cold(args)->R); };
+        auto words = [&](int step) { return philox_step(L.ph, (uint32_t)step, R.key0, R.key1); };
         for (int k = 0;; ++k) {
             if (CKPT && (k % kCkptEvery) == 0 && k < R.max_steps) write_ckpt(L, g, k, R);
-            if (!advance<F>(L, g, var, k, A, args, sc)) break;
+            if (!advance<F>(L, g, var, words, k, A, args, sc)) break;
         }
     }
     store_lane(L, g, cold(args)->io);
@@ -1483,8 +1485,11 @@ k_pass(KArgs A) {
                 const ArgPtr c = cold(args);
                 return (int)variant_of(c->P.n_in ? c->P.in[i] : i, c->R);
             };
+            auto words = [&](int step) {
+                return philox_step(L.ph, (uint32_t)step, R.key0, R.key1);
+            };
             for (int k = P.k_begin;; ++k) {
-                if (!advance<F | kPasses>(L, g, var, k, A, args, sc)) break;
+                if (!advance<F | kPasses>(L, g, var, words, k, A, args, sc)) break;
             }
         }
         const ArgPtr c = cold(args);
@@ -1531,10 +1536,18 @@ k_pass(KArgs A) {
 // 64 / G consecutive (muon, group of G variants) units from w 64 / G on.
 // Results are bit-identical to the other forms (same words, same arithmetic,
 // same output slots).
+//
+// Lone muons (DevRun::solo, small launches of the other forms): a group of G
+// lanes belongs to one muon that its first lane carries; the others only form
+// its random words, one step of G each.
 // ---------------------------------------------------------------------------
-template <unsigned F>     // F holds neither kTape nor kTrace
+constexpr int waves_min_waves(unsigned F, bool ahead) {
+    return (F & (kMap | kStages | kPoly)) ? plain_min_waves(F) : (F & kVert) && !ahead ? 7 : 6;
+}
+
+template <unsigned F, bool AHEAD>     // F holds no kTrace; kTape for lone muons only
 __global__ void __launch_bounds__(1024)
-    __attribute__((amdgpu_waves_per_eu((F & (kMap | kStages | kPoly)) ? plain_min_waves(F) : 6)))
+    __attribute__((amdgpu_waves_per_eu(waves_min_waves(F, AHEAD))))
 k_variant_waves(KArgs A) {
     const ArgPtr args = kernel_args();
     const DevRun &R = A.R;
@@ -1543,17 +1556,26 @@ k_variant_waves(KArgs A) {
     const int lane = (int)(threadIdx.x & (kWave - 1));
     const int gs = R.share_shift, gm = (1 << gs) - 1;   // G = 2^gs lanes per muon
     const int64_t n = R.n;
-    const int64_t vgroups = (R.lanes / n) >> gs;       // groups of G variants per muon
-    const int64_t units = n * vgroups;
+    const int64_t vgroups = R.solo ? 1 : (R.lanes / n) >> gs;    // groups of G variants per muon
+    const int64_t units = R.solo ? R.lanes : n * vgroups;
     // the first unit of the wavefront is the same for all its lanes
     const int64_t first = ((int64_t)blockIdx.x * (blockDim.x / kWave) +
                            __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave))) *
                           (kWave >> gs);
     if (first >= units) return;
     const int64_t unit = first + (lane >> gs);
-    const bool valid = unit < units;                   // the last wavefront may be ragged
-    const int64_t j = valid ? unit / vgroups : 0;
-    const int64_t var = valid ? (unit - j * vgroups) * (gm + 1) + (lane & gm) : 0;
+    const bool in_range = unit < units;                // the last wavefront may be ragged
+    int64_t j = 0, var = 0;
+    if (in_range) {
+        if (R.solo) {
+            var = variant_of(unit, R);
+            j = unit - var * n;
+        } else {
+            j = unit / vgroups;
+            var = (unit - j * vgroups) * (gm + 1) + (lane & gm);
+        }
+    }
+    const bool valid = in_range && (!R.solo || (lane & gm) == 0);
     Lane L;
     bool running = false;
     if (valid) {
@@ -1563,25 +1585,31 @@ k_variant_waves(KArgs A) {
     const PhiloxPrefix P =
         philox_prefix((uint32_t)j, (uint32_t)((uint64_t)j >> 32), R.key0, R.key1);
     // the wavefront's Philox blocks: lane l holds its group's block of step
-    // k0 + (l mod G), 1 KB of LDS per wavefront
+    // k0 + (l mod G), 1 KB of LDS per wavefront; two groups of steps where a
+    // step also asks for the next one's words
     uint4 *wblk = reinterpret_cast<uint4 *>(lds_base() + A.T.lds.bytes) +
-                  (threadIdx.x & ~(unsigned)(kWave - 1));
+                  (AHEAD ? 2 : 1) * (threadIdx.x & ~(unsigned)(kWave - 1));
     const int base = lane & ~gm;
+    const int64_t g = var * n + j;
     auto var_of = [&] { return (int)var; };
+    auto words = [&](int step) {                   // one address per group: a broadcast
+        return wblk[(AHEAD ? ((step >> gs) & 1) * kWave : 0) + base + (step & gm)];
+    };
+    // the wavefront's LDS accesses are executed in order; the wave barriers
+    // keep the compiler from moving reads of the group of steps that a write
+    // replaces below it, or reads of the new one above it
+    auto fill = [&](int k0) {
+        __builtin_amdgcn_wave_barrier();
+        wblk[(AHEAD ? ((k0 >> gs) & 1) * kWave : 0) + lane] =
+            philox_step(P, (uint32_t)(k0 + (lane & gm)), R.key0, R.key1);
+        __builtin_amdgcn_wave_barrier();
+    };
+    if (AHEAD) fill(0);
     for (int k = 0; __ballot(running) != 0; ++k) {
-        const int sl = k & gm;
-        if (sl == 0) {
-            // the wavefront's LDS accesses are executed in order; the wave
-            // barriers keep the compiler from moving the reads of the last
-            // group of steps below this write or the reads of the next group
-            // above it
-            __builtin_amdgcn_wave_barrier();
-            wblk[lane] = philox_step(P, (uint32_t)(k + (lane & gm)), R.key0, R.key1);
-            __builtin_amdgcn_wave_barrier();
-        }
+        if ((k & gm) == (AHEAD ? gm : 0)) fill(k + (AHEAD ? 1 : 0));
         if (running) {
-            const uint4 w = wblk[base + sl];      // one address per group: a broadcast
-            running = advance<F | kShared>(L, 0, var_of, k, A, args, sc, w);
+            if ((F & kTape) && (k % kCkptEvery) == 0 && k < R.max_steps) write_ckpt(L, g, k, R);
+            running = advance<AHEAD ? F : F | kNow>(L, g, var_of, words, k, A, args, sc);
         }
     }
     if (valid) {
@@ -2145,16 +2173,18 @@ static const void *persistent_kernel() {
     else return nullptr;
 }
 
-template <unsigned F>
+// Lone muons (the only use with a tape) are always few: their kernel forms
+// draws ahead where it can.
+template <unsigned F, bool AHEAD>
 static const void *variant_waves_kernel() {
-    if constexpr (valid_mask(F) && !(F & (kTape | kTrace)))
-        return reinterpret_cast<const void *>(&k_variant_waves<F>);
-    else return nullptr;
+    if constexpr (!valid_mask(F) || (F & kTrace)) return nullptr;
+    else if constexpr (!AHEAD && kAhead<F> && (F & kTape)) return nullptr;
+    else return reinterpret_cast<const void *>(&k_variant_waves<F, AHEAD && kAhead<F>>);
 }
 
-template <size_t... I>
+template <bool AHEAD, size_t... I>
 static std::array<const void *, sizeof...(I)> variant_waves_kernels(std::index_sequence<I...>) {
-    return {variant_waves_kernel<(unsigned)I>()...};
+    return {variant_waves_kernel<(unsigned)I, AHEAD>()...};
 }
 
 template <size_t... I>
@@ -2209,10 +2239,12 @@ hipError_t launch_pass(const Tables &T, const DevRun &R, const DevIO &io, int bl
 
 hipError_t launch_variant_waves(const Tables &T, const DevRun &R, const DevIO &io, int block,
                                hipStream_t s) {
-    static const auto fns = variant_waves_kernels(std::make_index_sequence<kFeatures>());
+    static const auto now = variant_waves_kernels<false>(std::make_index_sequence<kFeatures>());
+    static const auto ahead = variant_waves_kernels<true>(std::make_index_sequence<kFeatures>());
+    const auto &fns = R.solo || R.ahead ? ahead : now;
     if (R.lanes == 0) return hipSuccess;
     // (muon, group of G variants) units, 64 / G per wavefront
-    const int64_t units = R.lanes >> R.share_shift;
+    const int64_t units = R.solo ? R.lanes : R.lanes >> R.share_shift;
     const int64_t per_wave = kWave >> R.share_shift;
     const int64_t waves = (units + per_wave - 1) / per_wave;
     const int64_t per_block = block / kWave;
@@ -2221,7 +2253,7 @@ hipError_t launch_variant_waves(const Tables &T, const DevRun &R, const DevIO &i
     void *args[] = {&a};
     const void *fn = fns[feature_mask(T, R)];
     if (fn == nullptr) return hipErrorInvalidValue;     // excluded by argument validation
-    const size_t lds = (size_t)T.lds.bytes + (size_t)block * sizeof(uint4);
+    const size_t lds = (size_t)T.lds.bytes + (R.solo || R.ahead ? 2 : 1) * (size_t)block * sizeof(uint4);
     return hipLaunchKernel(fn, dim3(grid), dim3(block), args, lds, s);
 }
 
