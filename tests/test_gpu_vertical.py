@@ -78,6 +78,36 @@ def test_with_map(interp, stage, tilt):
         assert np.array_equal(a[k], c[k]), k
 
 
+@pytest.mark.parametrize("with_map", [False, True], ids=["boxes", "map"])
+def test_gradients(with_map):
+    """Checkpointed forward and adjoint: one more box with a horizontal field,
+    behind the world, selects the general kernels without changing anything."""
+    import torch
+    from paper_2512_10520_amd import api
+    wl = W.make_workload("diff", n_muons=1300, n_fill=100_000)
+    if with_map:
+        rng = np.random.default_rng(8)
+        b = np.zeros((12, 6, 7, 3), np.float32)
+        b[..., 1] = rng.uniform(-0.5, 0.5, b.shape[:3])
+        wl.field = W.FieldMap(lo=np.array([-0.8, -0.9, 0.2]), hi=np.array([0.8, 0.9, 4.5]), b=b)
+    g = wl.geom
+    tilted = dataclasses.replace(
+        g, box=np.vstack([g.box, [[-1, 1, -1, 1, 50, 51]]]), material=np.append(g.material, -1),
+        b_box=np.vstack([g.b_box, [[1, 0, 0]]]).astype(np.float32), magnet=np.append(g.magnet, -1))
+    got = []
+    for geom in (g, tilted):
+        api.load_workload(dataclasses.replace(wl, geom=geom))
+        dm = api.DeviceMuons.from_host(wl.muons)
+        sc = torch.linspace(0.9, 1.1, 8, dtype=torch.float32, device="cuda").reshape(1, 8)
+        spec = api.RunSpec.from_workload(wl, block=64)
+        f = api.propagate(dm, spec, scales=sc, ckpt=True)
+        gx, gs = api.propagate_backward(dm, spec, f, torch.cos(f.state), scales=sc, n_mag=8)
+        got.append((f.state, f.status, f.n_steps, f.volume, gx, gs))
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+    assert float(got[0][5].abs().min()) > 0
+
+
 def test_overflowing_map_is_refused_and_the_loaded_one_stays():
     from paper_2512_10520_amd import api
     wl = W.make_workload("shield", n_muons=500, n_fill=50_000)
