@@ -344,6 +344,7 @@ int validate(const mt_params *p, int64_t n, const mt_muons *in, const mt_muons *
     R.share_shift = 0;
     while (R.share_shift < 6 && p->n_variants % (2 << R.share_shift) == 0) ++R.share_shift;
     R.pmin2 = p->p_min * p->p_min;
+    R.room = c.lanes <= 4 * 64 * 4 * (int64_t)g.cu_count ? 1 : 0;      // see kRoom
     R.ahead = c.lanes <= 5 * 64 * 4 * (int64_t)g.cu_count ? 1 : 0;     // see kAhead
     R.max_steps = p->max_steps;
     R.key0 = (uint32_t)p->seed;
@@ -393,11 +394,13 @@ void pass_plan(int max_steps, int compact, int *S, int *P) {
 // compacting form runs the whole step range as one pass.
 int enqueue_ws(const mt_params *p, const Call &c, hipStream_t s, unsigned long long *counters,
                char *lists, double *partial) {
+    int S = 0, P = 1;
+    if (p->mode == MT_MODE_PERSISTENT)
+        pass_plan(p->max_steps, lists ? c.compact : p->max_steps + 1, &S, &P);
     if (c.R.solo) {
         MT_HIP(mt::launch_variant_waves(g.T, c.R, c.io, c.block, s));
-    } else if (p->mode == MT_MODE_PERSISTENT) {
-        int S = 0, P = 1;
-        pass_plan(p->max_steps, lists ? c.compact : p->max_steps + 1, &S, &P);
+    } else if (p->mode == MT_MODE_PERSISTENT && (P > 1 || !c.R.room)) {
+        // (a single pass of few lanes is the plain form, which has kernels for them: kRoom)
         if (P > 1)
             MT_HIP(mt::launch_queue_reset(counters, reinterpret_cast<double *>(counters), P, s));
         for (int pp = 0; pp < P; ++pp) {

@@ -1002,7 +1002,8 @@ enum : unsigned {
     kVert = 256u,    // every field (boxes, blocks and map) is vertical: B = (0, By, 0)
     kFeatures = 512u,// number of masks
     kPasses = 512u,  // the kernel runs passes (not a mask bit)
-    kNow = 1024u     // the step's draw is not formed ahead (not a mask bit)
+    kNow = 1024u,    // the step's draw is not formed ahead (not a mask bit)
+    kRoom = 2048u    // few waves: registers before occupancy (not a mask bit)
 };
 
 // Masks that have a kernel: the tape belongs to the differentiable form,
@@ -1121,12 +1122,19 @@ __device__ __forceinline__ uint32_t hist_of(const Lane &L, int gbits) {
 // registers it takes cost more: with a general map (trilinear 3.80 -> 4.39 ms, nearest node, 10^6
 // muons, 9.20 -> 9.48), the field at every stage (7.30 -> 7.41 ms) and the
 // passes over a map, whose waves hide it anyway (10^7 muons 77.7 -> 78.0 ms).
+// With a general map and at most 4 waves a SIMD to run (DevRun::room), the
+// occupancy that plain_min_waves keeps is of no use: the plain form then has
+// kernels of its own (kRoom), which take the registers they want and do form
+// draws ahead (100 000 muons in the fringe field 3.03 -> 2.79 ms, 250 007 3.81
+// -> 3.69, nearest node 3.33 -> 3.19).  A persistent call of one pass that small
+// takes the plain form too (200 000: 3.80 -> 3.66; vertical map, 100 000: 2.68 -> 2.47).
+// Past 4 waves a SIMD the waves hide the latency (3.80 -> 4.39 above).
 // The variant-wave form has kernels with and without (DevRun::ahead): 12
 // variants of 20 011 muons 427 -> 417 us, but 64 of 131 072, which fill the chip,
 // 7.72 -> 8.05 ms with it.
 template <unsigned F>
 constexpr bool kAhead = !(F & (kStages | kNow)) &&
-                        (!(F & kMap) || ((F & kVert) && !(F & kPasses)));
+                        (!(F & kMap) || ((F & kVert) && !(F & kPasses)) || (F & kRoom));
 
 // The exact tests of a step that the lane's region or momentum band does not
 // decide.
@@ -1388,7 +1396,7 @@ __device__ __forceinline__ void write_ckpt(const Lane &L, int64_t g, int k, cons
 // the shield 11 % faster than 4 waves.
 // ---------------------------------------------------------------------------
 constexpr int plain_min_waves(unsigned F) {
-    return ((F & kMap) && !(F & (kStages | kNearest | kTape))) ? 5 : 1;
+    return ((F & kMap) && !(F & (kStages | kNearest | kTape | kRoom))) ? 5 : 1;
 }
 
 template <unsigned F>
@@ -2190,10 +2198,11 @@ __global__ void k_pass2(const double *partial, int nb, int n_cols, int n_variant
 // ---------------------------------------------------------------------------
 // Launchers.
 // ---------------------------------------------------------------------------
-template <unsigned F>
+template <unsigned F, unsigned ROOM>
 static const void *plain_kernel() {
-    if constexpr (valid_mask(F)) return reinterpret_cast<const void *>(&k_plain<F>);
-    else return nullptr;
+    constexpr bool own = !(F & kVert) && (F & kMap) && !(F & (kStages | kTape | kTrace));
+    if constexpr (!valid_mask(F)) return nullptr;
+    else return reinterpret_cast<const void *>(&k_plain<own ? F | ROOM : F>);
 }
 
 template <unsigned F>
@@ -2217,9 +2226,9 @@ static std::array<const void *, sizeof...(I)> variant_waves_kernels(std::index_s
     return {variant_waves_kernel<(unsigned)I, AHEAD>()...};
 }
 
-template <size_t... I>
+template <unsigned ROOM, size_t... I>
 static std::array<const void *, sizeof...(I)> plain_kernels(std::index_sequence<I...>) {
-    return {plain_kernel<(unsigned)I>()...};
+    return {plain_kernel<(unsigned)I, ROOM>()...};
 }
 
 template <size_t... I>
@@ -2239,7 +2248,9 @@ static unsigned feature_mask(const Tables &T, const DevRun &R) {
 
 hipError_t launch_plain(const Tables &T, const DevRun &R, const DevIO &io, int block,
                         hipStream_t s) {
-    static const auto fns = plain_kernels(std::make_index_sequence<kFeatures>());
+    static const auto many = plain_kernels<0u>(std::make_index_sequence<kFeatures>());
+    static const auto few = plain_kernels<kRoom>(std::make_index_sequence<kFeatures>());
+    const auto &fns = R.room ? few : many;
     if (R.lanes == 0) return hipSuccess;
     const unsigned grid = (unsigned)((R.lanes + block - 1) / block);
     KArgs a{T, R, io, PassArgs{}};

@@ -63,6 +63,31 @@ def test_kernels(name, opt, mode, n):
     _both(torch, wl, n, mode=mode)
 
 
+@pytest.mark.parametrize("mode", ["plain", "persistent"])
+@pytest.mark.parametrize("general", [True, False])
+@pytest.mark.parametrize("opt", [{}, {"interp": 1}, {"sampler": 1}])
+def test_few_waves(opt, general, mode):
+    """Both sides of the limit of 4 waves a SIMD, where a map's kernels change."""
+    import torch
+    from paper_2512_10520_amd import api
+    edge = 4 * 4 * 64 * torch.cuda.get_device_properties(0).multi_processor_count
+    wl = W.make_workload("shield", n_muons=edge + 1, n_fill=100_000)
+    if general:
+        b = wl.field.b.copy()
+        b[..., 0] += 0.02 * b[..., 1]
+        b[..., 2] += np.float32(0.3) * np.gradient(b[..., 1], axis=0).astype(np.float32)
+        wl.field = W.FieldMap(lo=wl.field.lo, hi=wl.field.hi, b=b)
+    wl.run = dataclasses.replace(wl.run, max_steps=400, **opt)
+    api.load_workload(wl)
+    spec = api.RunSpec.from_workload(wl, mode=mode)
+    dm = api.DeviceMuons.from_host(wl.muons)
+    many = api.propagate(dm, spec)
+    few = api.propagate(api.DeviceMuons.from_host(wl.muons.take(np.arange(edge))), spec)
+    for k in KEYS:
+        a, b = getattr(many, k), getattr(few, k)
+        assert torch.equal(a[..., :edge], b), k
+
+
 @pytest.mark.parametrize("n", [1, 65, 5000])
 def test_checkpoints_and_gradients(n):
     """The tape and checkpoints of the lone-muon kernel, through the adjoint."""
