@@ -203,7 +203,10 @@ __device__ __forceinline__ void stage_tables(const Tables &T, double pmin2) {
 // region again, as every lane does at each step that is a multiple of
 // kRegionSteps.  The region is smaller than the true one by more than xr, yr,
 // zr can be off after that many FP32 sums, so a skipped test is one whose
-// outcome is known: results do not change.
+// outcome is known: results do not change.  Why: a step is bound by VALU issue,
+// an FP64 compare issues in 4.4 cycles against 2.4 of an FP32 operation, and the
+// FP64 tests of every step were some 160 of its 950 (block, 10^6 muons, 1718 ->
+// 1413 us; 2000, 381 -> 298 us; design scan 9.79 -> 8.87 ms).
 //
 // With convex blocks the box test is a test of four planes and |zr| (record
 // rec in LDS): for a lane in a block with plane sides the block's, with xr, yr,
@@ -1119,16 +1122,18 @@ __device__ __forceinline__ uint32_t hist_of(const Lane &L, int gbits) {
 // advance): hides the load's latency where few waves share a SIMD (2000 block
 // muons 284 -> 252 us, 123 457 with aliases 322 -> 298, 10^6 1350 -> 1302, 250
 // 007 shield muons in the plain form 3.30 -> 3.17 ms).  Not where the seven
-// registers it takes cost more: with a general map (trilinear 3.80 -> 4.39 ms, nearest node, 10^6
-// muons, 9.20 -> 9.48), the field at every stage (7.30 -> 7.41 ms) and the
-// passes over a map, whose waves hide it anyway (10^7 muons 77.7 -> 78.0 ms).
+// registers it takes cost more: with a general map (trilinear, compiled for 5
+// waves, 250 007 muons 3.80 -> 4.39 ms; nearest node, 10^6, 9.20 -> 9.48), the
+// field at every stage (7.30 -> 7.41 ms) and the passes over a map, whose waves
+// hide it anyway (10^7 muons 77.7 -> 78.0 ms).
 // With a general map and at most 4 waves a SIMD to run (DevRun::room), the
 // occupancy that plain_min_waves keeps is of no use: the plain form then has
 // kernels of its own (kRoom), which take the registers they want and do form
 // draws ahead (100 000 muons in the fringe field 3.03 -> 2.79 ms, 250 007 3.81
-// -> 3.69, nearest node 3.33 -> 3.19).  A persistent call of one pass that small
-// takes the plain form too (200 000: 3.80 -> 3.66; vertical map, 100 000: 2.68 -> 2.47).
-// Past 4 waves a SIMD the waves hide the latency (3.80 -> 4.39 above).
+// -> 3.69, nearest node 3.33 -> 3.19).  A compacting call of one pass that small
+// takes the plain form too (200 000: 3.80 -> 3.66; vertical map, 100 000: 2.68
+// -> 2.47).
+// Past 4 waves a SIMD the fifth wave hides more than the draw formed ahead.
 // The variant-wave form has kernels with and without (DevRun::ahead): 12
 // variants of 20 011 muons 427 -> 417 us, but 64 of 131 072, which fill the chip,
 // 7.72 -> 8.05 ms with it.
@@ -1390,10 +1395,11 @@ __device__ __forceinline__ void write_ckpt(const Lane &L, int64_t g, int k, cons
 // ---------------------------------------------------------------------------
 // Plain form: one lane per (variant, muon) until it stops.
 //
-// With a trilinear map held over the step, the lane's 24 cached interpolation
-// values leave the kernel a few registers above the 96 that 5 waves/SIMD
-// allow; asking for 5 waves moves two rarely used values to scratch and runs
-// the shield 11 % faster than 4 waves.
+// With a general trilinear map held over the step, the lane's 24 cached
+// interpolation values leave the kernel near the 96 registers that 5 waves/SIMD
+// allow; where more than 4 waves a SIMD run, 5 waves took 11 % less time than 4
+// on the shield (140 -> 124 ms before the vertical kernels, which need 72).
+// With fewer to run the registers serve better (kRoom).
 // ---------------------------------------------------------------------------
 constexpr int plain_min_waves(unsigned F) {
     return ((F & kMap) && !(F & (kStages | kNearest | kTape | kRoom))) ? 5 : 1;
