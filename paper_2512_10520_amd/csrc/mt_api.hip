@@ -344,8 +344,11 @@ int validate(const mt_params *p, int64_t n, const mt_muons *in, const mt_muons *
     R.share_shift = 0;
     while (R.share_shift < 6 && p->n_variants % (2 << R.share_shift) == 0) ++R.share_shift;
     R.pmin2 = p->p_min * p->p_min;
-    R.room = c.lanes <= 4 * 64 * 4 * (int64_t)g.cu_count ? 1 : 0;      // see kRoom
-    R.ahead = c.lanes <= 5 * 64 * 4 * (int64_t)g.cu_count ? 1 : 0;     // see kAhead
+    // few waves to run (see kRoom; blocks without a map: see plain_min_waves)
+    const int64_t chip = 64 * 4 * (int64_t)g.cu_count;      // lanes of one wave a SIMD
+    const bool blocks = g.T.geom.n_poly > 0 && g.T.field.map == nullptr;
+    R.room = c.lanes <= 4 * chip || (blocks && c.lanes > 5 * chip && c.lanes <= 8 * chip);
+    R.ahead = c.lanes <= 5 * chip;                          // see kAhead
     R.max_steps = p->max_steps;
     R.key0 = (uint32_t)p->seed;
     R.key1 = (uint32_t)(p->seed >> 32);

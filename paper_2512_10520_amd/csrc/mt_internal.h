@@ -131,7 +131,7 @@ struct DevRun {
     int32_t interp;              // MT_INTERP_*
     int32_t stage_field;         // 0: field held from the step start, 1: at every RK4 stage
     int32_t share_shift;         // variant-wave form: log2 of the lanes sharing a random stream
-    int32_t room;                // at most 4 waves a SIMD in the launch (see kRoom)
+    int32_t room;                // few waves in the launch (see kRoom)
     int32_t ahead;               // variant-wave form: form the next step's draw ahead
     int32_t solo;                // variant-wave form: one of those lanes carries a muon
     double pmin2;

@@ -1400,9 +1400,20 @@ __device__ __forceinline__ void write_ckpt(const Lane &L, int64_t g, int k, cons
 // allow; where more than 4 waves a SIMD run, 5 waves took 11 % less time than 4
 // on the shield (140 -> 124 ms before the vertical kernels, which need 72).
 // With fewer to run the registers serve better (kRoom).
+//
+// Convex blocks without a map take 116 registers by themselves; held to 96 (5
+// waves) they keep a few values of the cold lookup in scratch.  That pays where
+// the fifth wave saves a dispatch round or the rounds are many (300 000 muons 4.79
+// -> 3.78 ms, 600 000 7.68 -> 7.41, 10^6 11.28 -> 11.02, 3 10^6 29.5 -> 27.9), not with
+// at most 4 waves a SIMD to run (250 000 3.20 -> 3.36, 100 000 2.49 -> 2.66) or 5
+// to 8 (400 000 5.83 -> 5.97, 500 000 6.69 -> 6.74): those run the kernels of
+// kRoom.  Nor with aliases (10^6 10.29 -> 10.52).
 // ---------------------------------------------------------------------------
+constexpr bool blocks_alone(unsigned F) { return (F & kPoly) && !(F & (kMap | kAlias)); }
+
 constexpr int plain_min_waves(unsigned F) {
-    return ((F & kMap) && !(F & (kStages | kNearest | kTape | kRoom))) ? 5 : 1;
+    if (F & kRoom) return 1;
+    return blocks_alone(F) || ((F & kMap) && !(F & (kStages | kNearest | kTape))) ? 5 : 1;
 }
 
 template <unsigned F>
@@ -1556,7 +1567,8 @@ k_pass(KArgs A) {
 // its random words, one step of G each.
 // ---------------------------------------------------------------------------
 constexpr int waves_min_waves(unsigned F, bool ahead) {
-    return (F & (kMap | kStages | kPoly)) ? plain_min_waves(F) : (F & kVert) && !ahead ? 7 : 6;
+    if ((F & kPoly) && !(F & kMap)) return 1;     // lone muons (few waves) run these too
+    return (F & (kMap | kStages)) ? plain_min_waves(F) : (F & kVert) && !ahead ? 7 : 6;
 }
 
 template <unsigned F, bool AHEAD>     // F holds no kTrace; kTape for lone muons only
@@ -2206,15 +2218,17 @@ __global__ void k_pass2(const double *partial, int nb, int n_cols, int n_variant
 // ---------------------------------------------------------------------------
 template <unsigned F, unsigned ROOM>
 static const void *plain_kernel() {
-    constexpr bool own = !(F & kVert) && (F & kMap) && !(F & (kStages | kTape | kTrace));
+    constexpr bool own = !(F & (kStages | kTape | kTrace)) &&
+                         (blocks_alone(F) || ((F & kMap) && !(F & kVert)));
     if constexpr (!valid_mask(F)) return nullptr;
     else return reinterpret_cast<const void *>(&k_plain<own ? F | ROOM : F>);
 }
 
-template <unsigned F>
+template <unsigned F, unsigned ROOM>
 static const void *persistent_kernel() {
+    constexpr bool own = blocks_alone(F) && !(F & kTrace);
     if constexpr (valid_mask(F) && !(F & kTape))
-        return reinterpret_cast<const void *>(&k_pass<F>);
+        return reinterpret_cast<const void *>(&k_pass<own ? F | ROOM : F>);
     else return nullptr;
 }
 
@@ -2237,9 +2251,9 @@ static std::array<const void *, sizeof...(I)> plain_kernels(std::index_sequence<
     return {plain_kernel<(unsigned)I, ROOM>()...};
 }
 
-template <size_t... I>
+template <unsigned ROOM, size_t... I>
 static std::array<const void *, sizeof...(I)> persistent_kernels(std::index_sequence<I...>) {
-    return {persistent_kernel<(unsigned)I>()...};
+    return {persistent_kernel<(unsigned)I, ROOM>()...};
 }
 
 static unsigned feature_mask(const Tables &T, const DevRun &R) {
@@ -2266,20 +2280,18 @@ hipError_t launch_plain(const Tables &T, const DevRun &R, const DevIO &io, int b
     return hipLaunchKernel(fn, dim3(grid), dim3(block), args, (size_t)T.lds.bytes, s);
 }
 
-static const void *persistent_fn(unsigned mask) {
-    static const auto fns = persistent_kernels(std::make_index_sequence<kFeatures>());
-    return fns[mask];
-}
-
 hipError_t launch_pass(const Tables &T, const DevRun &R, const DevIO &io, int block,
                        const PassArgs &P, hipStream_t s) {
+    static const auto many = persistent_kernels<0u>(std::make_index_sequence<kFeatures>());
+    static const auto few = persistent_kernels<kRoom>(std::make_index_sequence<kFeatures>());
+    const auto &fns = R.room ? few : many;
     if (R.lanes == 0) return hipSuccess;
     // sized for every lane (the survivors of a pass are at most that many);
     // blocks past the pass's items exit before staging their tables
     const unsigned grid = (unsigned)((R.lanes + block - 1) / block);
     KArgs a{T, R, io, P};
     void *args[] = {&a};
-    const void *fn = persistent_fn(feature_mask(T, R) & ~kTape);
+    const void *fn = fns[feature_mask(T, R) & ~kTape];
     if (fn == nullptr) return hipErrorInvalidValue;     // excluded by argument validation
     return hipLaunchKernel(fn, dim3(grid), dim3(block), args, (size_t)T.lds.bytes, s);
 }

@@ -68,18 +68,36 @@ def test_kernels(name, opt, mode, n):
 @pytest.mark.parametrize("opt", [{}, {"interp": 1}, {"sampler": 1}])
 def test_few_waves(opt, general, mode):
     """Both sides of the limit of 4 waves a SIMD, where a map's kernels change."""
-    import torch
-    from paper_2512_10520_amd import api
-    edge = 4 * 4 * 64 * torch.cuda.get_device_properties(0).multi_processor_count
-    wl = W.make_workload("shield", n_muons=edge + 1, n_fill=100_000)
+    wl = _few_waves_workload("shield", opt)
     if general:
         b = wl.field.b.copy()
         b[..., 0] += 0.02 * b[..., 1]
         b[..., 2] += np.float32(0.3) * np.gradient(b[..., 1], axis=0).astype(np.float32)
         wl.field = W.FieldMap(lo=wl.field.lo, hi=wl.field.hi, b=b)
+    _few_and_many(wl, mode=mode)
+
+
+@pytest.mark.parametrize("mode,compact", [("plain", 0), ("persistent", 0), ("persistent", 100)])
+@pytest.mark.parametrize("opt,waves", [({}, 4), ({"sampler": 1}, 4), ({}, 5), ({}, 8)])
+def test_few_waves_blocks(opt, waves, mode, compact):
+    """The limits of 4, 5 and 8 waves a SIMD for convex blocks, in passes too."""
+    _few_and_many(_few_waves_workload("blocks", opt, waves), mode=mode, compact_every=compact)
+
+
+def _few_waves_workload(name, opt, waves=4):
+    import torch
+    edge = waves * 4 * 64 * torch.cuda.get_device_properties(0).multi_processor_count
+    wl = W.make_workload(name, n_muons=edge + 1, n_fill=100_000)
     wl.run = dataclasses.replace(wl.run, max_steps=400, **opt)
+    return wl
+
+
+def _few_and_many(wl, **kw):
+    import torch
+    from paper_2512_10520_amd import api
+    edge = len(wl.muons) - 1
     api.load_workload(wl)
-    spec = api.RunSpec.from_workload(wl, mode=mode)
+    spec = api.RunSpec.from_workload(wl, **kw)
     dm = api.DeviceMuons.from_host(wl.muons)
     many = api.propagate(dm, spec)
     few = api.propagate(api.DeviceMuons.from_host(wl.muons.take(np.arange(edge))), spec)
