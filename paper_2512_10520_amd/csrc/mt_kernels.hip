@@ -238,10 +238,20 @@ struct Lane {
 
 constexpr uint32_t kVacuum = 0xFFFFFFFFu;      // hoff outside every material
 
-__device__ __forceinline__ void reset_lane_caches(Lane &L) {
+// LDS byte offset of the unit box, the BlockPlanes record behind the blocks'.
+template <class TT>
+__device__ __forceinline__ uint32_t unit_box(const TT &T) {
+    return (uint32_t)T.lds.off_planes +
+           (uint32_t)sizeof(BlockPlanes) * (uint32_t)T.geom.n_poly;
+}
+
+// A lane that knows nothing yet: outside its region, at whatever step it starts
+// (position 2 on every axis is outside the boxes' region and the unit box).
+template <class TT>
+__device__ __forceinline__ void reset_lane_caches(Lane &L, const TT &T) {
     L.xr = L.yr = L.zr = 2.0f;
     L.ix = L.iy = L.iz = 0.0f;
-    L.rec = 0u;
+    L.rec = unit_box(T);
     L.plo = L.pspan = 0u;
     L.hoff = kVacuum;
     L.eh = kVacuum;
@@ -254,8 +264,9 @@ __device__ __forceinline__ void reset_lane_caches(Lane &L) {
 }
 
 // Lane state of input muon j.
-__device__ __forceinline__ void load_lane_at(Lane &L, int64_t j, const DevIO &io,
-                                             const DevRun &R) {
+__device__ __forceinline__ void load_lane_at(Lane &L, int64_t j, const KArgs &A) {
+    const DevIO &io = A.io;
+    const DevRun &R = A.R;
     L.x = io.x[j];
     L.y = io.y[j];
     L.z = io.z[j];
@@ -266,7 +277,7 @@ __device__ __forceinline__ void load_lane_at(Lane &L, int64_t j, const DevIO &io
     L.kq = (float)kKappa * (float)qi;
     L.ph = philox_prefix((uint32_t)j, (uint32_t)((uint64_t)j >> 32), R.key0, R.key1);
     L.steps = 0;
-    reset_lane_caches(L);
+    reset_lane_caches(L, A.T);
     L.status = MT_ST_RUNNING;
     const double p2 = L.px * L.px + L.py * L.py + L.pz * L.pz;
     const bool ok = isfinite(L.x) && isfinite(L.y) && isfinite(L.z) && isfinite(p2) &&
@@ -282,8 +293,8 @@ __device__ __forceinline__ int64_t variant_of(int64_t g, const RR &R) {
     return R.lanes <= 0xFFFFFFFFll ? (int64_t)((uint32_t)g / (uint32_t)R.n) : g / R.n;
 }
 
-__device__ __forceinline__ void load_lane(Lane &L, int64_t g, const DevIO &io, const DevRun &R) {
-    load_lane_at(L, g - variant_of(g, R) * R.n, io, R);
+__device__ __forceinline__ void load_lane(Lane &L, int64_t g, const KArgs &A) {
+    load_lane_at(L, g - variant_of(g, A.R) * A.R.n, A);
 }
 
 // ---------------------------------------------------------------------------
@@ -1182,8 +1193,7 @@ __device__ __forceinline__ bool locate_region(Lane &L, V &&var, int k, double p2
             if constexpr ((F & kPoly) == 0) {
                 r = box_region(L, vol, S);
             } else {
-                L.rec = (uint32_t)T.lds.off_planes +
-                        (uint32_t)sizeof(BlockPlanes) * (uint32_t)T.geom.n_poly;
+                L.rec = unit_box(T);
             }
             set_region(L, r, T.geom);
         }
@@ -1265,7 +1275,7 @@ __device__ __forceinline__ bool advance(Lane &L, int64_t g, V &&var, W &&words, 
     const double p2 = L.px * L.px + L.py * L.py + L.pz * L.pz;
     const float p2f = (float)p2;
     bool outside;
-    if constexpr ((F & kPoly) != 0) outside = (k == 0) || outside_planes(L, k);
+    if constexpr ((F & kPoly) != 0) outside = outside_planes(L, k);
     else outside = outside_region(L, k);
     outside |= k >= R.max_steps;
     const uint32_t pb = __float_as_uint(p2f);
@@ -1427,7 +1437,7 @@ k_plain(KArgs A) {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= R.lanes) return;
     Lane L;
-    load_lane(L, g, A.io, R);
+    load_lane(L, g, A);
     if (L.status == MT_ST_RUNNING) {
         auto var = [&] { return (int)variant_of(g, cold(args)->R); };
         auto words = [&](int step) { return philox_step(L.ph, (uint32_t)step, R.key0, R.key1); };
@@ -1466,9 +1476,9 @@ k_plain(KArgs A) {
 // ---------------------------------------------------------------------------
 
 // Lane state of the muon of output slot g resumed from that slot.
-__device__ __forceinline__ void resume_lane(Lane &L, int64_t g, const DevIO &io,
-                                            const DevRun &R) {
-    load_lane(L, g, io, R);                 // charge, Philox prefix, caches reset
+__device__ __forceinline__ void resume_lane(Lane &L, int64_t g, const KArgs &A) {
+    const DevIO &io = A.io;
+    load_lane(L, g, A);                     // charge, Philox prefix, caches reset
     L.x = io.ox[g];
     L.y = io.oy[g];
     L.z = io.oz[g];
@@ -1495,8 +1505,8 @@ k_pass(KArgs A) {
     int64_t slot = 0;           // its output slot
     if (i < items) {
         Lane L;
-        if (P.n_in) resume_lane(L, P.in[i], A.io, R);
-        else load_lane(L, i, A.io, R);
+        if (P.n_in) resume_lane(L, P.in[i], A);
+        else load_lane(L, i, A);
         // The pass ends where R.max_steps says (the host sets it to the
         // pass's last step, or to the step cap in the last pass), so the
         // step loop is the plain form's: a muon that meets no other break
@@ -1605,7 +1615,7 @@ k_variant_waves(KArgs A) {
     Lane L;
     bool running = false;
     if (valid) {
-        load_lane_at(L, j, A.io, R);
+        load_lane_at(L, j, A);
         running = L.status == MT_ST_RUNNING;
     }
     const PhiloxPrefix P =
@@ -1948,7 +1958,7 @@ k_adjoint(Tables T, DevRun R, DevIO io, const double *g_out,
             L.kq = kq;
             // kick records of the segment: three floats per (step, lane)
             const float *rec = R.tape + ((size_t)k0 * lanes + g) * 3;
-            reset_lane_caches(L);        // lookup caches start empty
+            reset_lane_caches(L, T);     // lookup caches start empty
             // history of the segment: the pre-kick momentum p0 of every step
             // (FP32), [step][3][thread] in LDS (LDSH) or one 12-byte record per
             // (step, lane) in device memory.  The stage-0 momentum a0 is formed
