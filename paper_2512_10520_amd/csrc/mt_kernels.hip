@@ -236,6 +236,19 @@ struct Lane {
     float mc[24];         // its coefficients (bx, by, bz) x 8 (or the node's value)
 };
 
+// y and p_y of a lane.  A field that is not finite makes a muon NaN; the vertical
+// forms leave out the products that would carry the NaN to y, so it is taken
+// from x and p_x there, where the value counts (outputs and checkpoints).
+template <bool V>
+__device__ __forceinline__ double lane_y(const Lane &L) {
+    return V && L.x != L.x ? L.x : L.y;
+}
+
+template <bool V>
+__device__ __forceinline__ double lane_py(const Lane &L) {
+    return V && L.px != L.px ? L.px : L.py;
+}
+
 constexpr uint32_t kVacuum = 0xFFFFFFFFu;      // hoff outside every material
 
 // LDS byte offset of the unit box, the BlockPlanes record behind the blocks'.
@@ -760,7 +773,10 @@ __device__ __forceinline__ float3 cell_field(const CellPoly &c) {
     return r;
 }
 
-template <class TT, class RR>
+// V: the field is vertical and only its y component is read; a scale that is not
+// finite, which makes a general field NaN on every axis (0 times it is NaN),
+// makes this one NaN too.
+template <bool V, class TT, class RR>
 __device__ __forceinline__ float3 box_field(const TT &T, const Lds &S, const RR &R, int vol,
                                             int var) {
     float3 B = make_float3(0.f, 0.f, 0.f);
@@ -768,7 +784,8 @@ __device__ __forceinline__ float3 box_field(const TT &T, const Lds &S, const RR 
         const float4 b = S.bf[vol];
         const int m = S.mag[vol];
         const float s = (m >= 0 && R.scales != nullptr) ? R.scales[var * T.geom.n_mag + m] : 1.0f;
-        B = make_float3(b.x * s, b.y * s, b.z * s);
+        if (V) B.y = fmaf(-0.0f, fabsf(s), b.y * s);     // + -0 or NaN
+        else B = make_float3(b.x * s, b.y * s, b.z * s);
     }
     return B;
 }
@@ -1048,7 +1065,7 @@ __device__ __forceinline__ float3 field_at_point(const KArgs &A, ArgPtr args, La
         const ArgPtr c = cold(args);
         const Lds S = lds_view(c->T);
         const int vol = find_box(S, find_slab(S, c->T.geom.n_slab, z, L.slab), x, y);
-        if (vol != L.vol) B = box_field(c->T, S, c->R, vol, var());
+        if (vol != L.vol) B = box_field<(F & kVert) != 0>(c->T, S, c->R, vol, var());
     }
     return with_map<F>(L, A, args, B, x, y, z);
 }
@@ -1187,8 +1204,11 @@ __device__ __forceinline__ bool locate_region(Lane &L, V &&var, int k, double p2
                          : c_x    ? MT_ST_XMAX
                          : c_y    ? MT_ST_YMAX
                                   : MT_ST_MAXSTEPS;
+                // (a muon made NaN by its field has no y, see lane_y)
+                if ((F & kVert) && L.status == MT_ST_YMAX && L.x != L.x)
+                    L.status = c_k ? MT_ST_MAXSTEPS : MT_ST_RUNNING;
                 L.steps = k;
-                return false;
+                if (L.status != MT_ST_RUNNING) return false;
             }
             if constexpr ((F & kPoly) == 0) {
                 r = box_region(L, vol, S);
@@ -1198,7 +1218,7 @@ __device__ __forceinline__ bool locate_region(Lane &L, V &&var, int k, double p2
             set_region(L, r, T.geom);
         }
         if (vol != old) {
-            const float3 b = box_field(T, S, R, vol, var());
+            const float3 b = box_field<(F & kVert) != 0>(T, S, R, vol, var());
             L.bent = non_zero<(F & kVert) != 0>(b);
             const float s = kScaledField<F> ? L.kq : 1.0f;
             L.bx = s * b.x;
@@ -1379,26 +1399,27 @@ __device__ __forceinline__ StepConst step_const(const DevRun &R) {
     return c;
 }
 
-template <class IO>
+template <bool V, class IO>
 __device__ __forceinline__ void store_lane(const Lane &L, int64_t g, const IO &io) {
     io.ox[g] = L.x;
-    io.oy[g] = L.y;
+    io.oy[g] = lane_y<V>(L);
     io.oz[g] = L.z;
     io.opx[g] = L.px;
-    io.opy[g] = L.py;
+    io.opy[g] = lane_py<V>(L);
     io.opz[g] = L.pz;
     io.status[g] = L.status;
     io.n_steps[g] = L.steps;
     io.volume[g] = L.status == MT_ST_INVALID ? -1 : L.vol;
 }
 
+template <bool V>
 __device__ __forceinline__ void write_ckpt(const Lane &L, int64_t g, int k, const DevRun &R) {
     double *c = R.ckpt + (size_t)(k / kCkptEvery) * 6 * R.lanes + g;
     c[0] = L.x;
-    c[R.lanes] = L.y;
+    c[R.lanes] = lane_y<V>(L);
     c[2 * R.lanes] = L.z;
     c[3 * R.lanes] = L.px;
-    c[4 * R.lanes] = L.py;
+    c[4 * R.lanes] = lane_py<V>(L);
     c[5 * R.lanes] = L.pz;
 }
 
@@ -1442,11 +1463,11 @@ k_plain(KArgs A) {
         auto var = [&] { return (int)variant_of(g, cold(args)->R); };
         auto words = [&](int step) { return philox_step(L.ph, (uint32_t)step, R.key0, R.key1); };
         for (int k = 0;; ++k) {
-            if (CKPT && (k % kCkptEvery) == 0 && k < R.max_steps) write_ckpt(L, g, k, R);
+            if (CKPT && (k % kCkptEvery) == 0 && k < R.max_steps) write_ckpt<(F & kVert) != 0>(L, g, k, R);
             if (!advance<F>(L, g, var, words, k, A, args, sc)) break;
         }
     }
-    store_lane(L, g, cold(args)->io);
+    store_lane<(F & kVert) != 0>(L, g, cold(args)->io);
 }
 
 // ---------------------------------------------------------------------------
@@ -1534,7 +1555,7 @@ k_pass(KArgs A) {
         }
         // the slot is read again rather than kept in registers over the loop
         slot = c->P.n_in ? c->P.in[i] : i;
-        store_lane(L, slot, c->io);         // status running if parked
+        store_lane<(F & kVert) != 0>(L, slot, c->io);         // status running if parked
     }
     // wave-aggregated append of the survivors' slots (no block barrier: a
     // wave that is done leaves at once and frees its registers for the next)
@@ -1644,12 +1665,12 @@ k_variant_waves(KArgs A) {
     for (int k = 0; __ballot(running) != 0; ++k) {
         if ((k & gm) == (AHEAD ? gm : 0)) fill(k + (AHEAD ? 1 : 0));
         if (running) {
-            if ((F & kTape) && (k % kCkptEvery) == 0 && k < R.max_steps) write_ckpt(L, g, k, R);
+            if ((F & kTape) && (k % kCkptEvery) == 0 && k < R.max_steps) write_ckpt<(F & kVert) != 0>(L, g, k, R);
             running = advance<AHEAD ? F : F | kNow>(L, g, var_of, words, k, A, args, sc);
         }
     }
     if (valid) {
-        store_lane(L, var * n + j, cold(args)->io);
+        store_lane<(F & kVert) != 0>(L, var * n + j, cold(args)->io);
     }
 }
 
@@ -1866,7 +1887,7 @@ __device__ __forceinline__ int replay_step(Lane &L, int k, const Tables &T, cons
         if (!table_region(L, vol, T, S)) set_region(L, box_region(L, vol, S), T.geom);
         if (vol != L.vol) {
             L.vol = vol;
-            const float3 b = box_field(T, S, R, vol, var);
+            const float3 b = box_field<V>(T, S, R, vol, var);
             L.bent = non_zero<V>(b);
             const float s = MAP ? 1.0f : L.kq;
             L.bx = s * b.x;
@@ -2051,7 +2072,7 @@ k_adjoint(Tables T, DevRun R, DevIO io, const double *g_out,
                 const int vol = vh[(k - k0) * bd];
                 const float3 a0 = (vol >= 0 && S.mat[vol] >= 0) ? kick_again(p0, cur) : p0;
                 if (vol != bvol) {
-                    bb = box_field(T, S, R, vol, var);
+                    bb = box_field<V>(T, S, R, vol, var);
                     bvol = vol;
                 }
                 int m;
