@@ -1196,7 +1196,9 @@ __device__ __forceinline__ bool locate_region(Lane &L, V &&var, int k, double p2
             // Break test in the order p_min, z_max, x_max, y_max, step cap (the
             // first that holds decides the status; vol is the final volume).
             const bool c_pmin = p2 < R.pmin2, c_z = L.z >= T.geom.z_max;
-            const bool c_x = fabs(L.x) >= T.geom.x_max, c_y = fabs(L.y) >= T.geom.y_max;
+            // (0 x: a muon made NaN by its field has no y, see lane_y)
+            const double y = (F & kVert) ? fma(0.0, L.x, L.y) : L.y;
+            const bool c_x = fabs(L.x) >= T.geom.x_max, c_y = fabs(y) >= T.geom.y_max;
             const bool c_k = k >= R.max_steps;
             if (c_pmin | c_z | c_x | c_y | c_k) {
                 L.status = c_pmin ? MT_ST_PMIN
@@ -1204,11 +1206,8 @@ __device__ __forceinline__ bool locate_region(Lane &L, V &&var, int k, double p2
                          : c_x    ? MT_ST_XMAX
                          : c_y    ? MT_ST_YMAX
                                   : MT_ST_MAXSTEPS;
-                // (a muon made NaN by its field has no y, see lane_y)
-                if ((F & kVert) && L.status == MT_ST_YMAX && L.x != L.x)
-                    L.status = c_k ? MT_ST_MAXSTEPS : MT_ST_RUNNING;
                 L.steps = k;
-                if (L.status != MT_ST_RUNNING) return false;
+                return false;
             }
             if constexpr ((F & kPoly) == 0) {
                 r = box_region(L, vol, S);
