@@ -23,7 +23,7 @@ static __device__ __align__(256) unsigned char scratch[MT_NOALLOC_SCRATCH_BYTES]
 
 namespace {
 
-using mt::Tables;
+using mt::AllTables;
 
 thread_local std::string g_err;
 
@@ -106,7 +106,7 @@ struct State {
     } host;
     DevBuf map, mapv;
     DevBuf queue, partial, scratch, gs_lane, lists;
-    Tables T{};
+    AllTables T{};
     int max_material = -1;
     hipStream_t cap_stream = nullptr;
     std::vector<GraphEntry> graphs;
@@ -171,10 +171,56 @@ void tables_changed() {
     g.tuned.clear();
 }
 
-// Layout and image of the tables staged in LDS (histogram and geometry parts,
-// whichever are loaded), uploaded as one block.
-int build_image() {
-    mt::LdsLayout L{};
+// Launches that the wide kernels (see AllTables) are the better ones for, besides
+// those that record a trace: those over narrow bins, and those of more waves than
+// the blocks of the ordinary kernels can have resident, from an image on that only
+// three blocks of 4 waves fit a CU (10^6 muons through 40 boxes, 28 materials of 95
+// bins, 4 blocks: 4.77 ms in the ordinary kernels and 4.63 in the wide; 32, 3 blocks:
+// 5.74 and 4.58; 40 convex blocks, 20 materials, 4 blocks: 8.86 and 8.95; 24, 3
+// blocks: 10.9 and 8.90; but 20 000 muons and 36 materials 1.12 and 1.28).
+bool wide_tables(int64_t lanes, int64_t chip) {
+    const int64_t fit = mt::kLdsBytes / g.T.lds.bytes;     // blocks of 4 waves: waves a SIMD
+    return g.T.narrow || (fit < 4 && lanes > fit * chip);
+}
+
+// Do more than 1 in 100 draws of half of the histograms take a muon over two or
+// more momentum edges?  Then some lane of a wavefront does so in most steps.
+// Starting points are uniform in log p over the bin, so a loss of l in log p takes
+// a share (l - width of the bin below) / width of them that far.  With losses
+// uniform up to 2 % bins of 1.93 % are never skipped (10^6 muons 4.20 ms in the
+// ordinary kernels, 4.72 in the wide), of 1.75 % by 0.9 % of the draws (4.70, 4.73),
+// of 1.60 % by 2.3 % (5.72, 4.78).
+bool narrow_bins(const double *p_edges, int n_mat, int n_pbin, int n_loss, int n_scat,
+                 double loss_lo, double loss_hi, bool log_loss, const uint32_t *cdf) {
+    std::vector<double> drop((size_t)n_loss), width((size_t)n_pbin);
+    for (int a = 0; a < n_loss; ++a) {
+        const double t = (a + 0.5) / n_loss;
+        const double f = log_loss ? loss_lo * std::pow(loss_hi / loss_lo, t)
+                                  : loss_lo + t * (loss_hi - loss_lo);
+        drop[(size_t)a] = -std::log1p(-std::min(f, 0.999));
+    }
+    for (int i = 0; i < n_pbin; ++i) width[(size_t)i] = std::log(p_edges[i + 1] / p_edges[i]);
+    const int64_t K = (int64_t)n_loss * n_scat;
+    int64_t skipped = 0;
+    for (int64_t h = 0; h < (int64_t)n_mat * n_pbin; ++h) {
+        const size_t i = (size_t)(h % n_pbin);
+        if (i < 2) continue;
+        const uint32_t *C = cdf + h * K;
+        double far = 0.0, before = 0.0;
+        for (int a = 0; a < n_loss; ++a) {
+            const double upto = C[(int64_t)(a + 1) * n_scat - 1];
+            const double share = (drop[(size_t)a] - width[i - 1]) / width[i];
+            if (share > 0.0) far += (upto - before) * std::min(share, 1.0);
+            before = upto;
+        }
+        if (far > 0.01 * C[K - 1]) ++skipped;
+    }
+    return 2 * skipped > (int64_t)n_mat * n_pbin;
+}
+
+// Layout of the tables staged in LDS (histogram and geometry parts, whichever are
+// loaded), and their image.
+std::vector<unsigned char> make_image(bool wide, mt::LdsLayout &L) {
     int off = 0;
     auto take = [&](int bytes, int align) {
         off = (off + align - 1) / align * align;
@@ -185,8 +231,8 @@ int build_image() {
     const int P = g.T.hist.n_pbin, nb = g.T.geom.n_box, ns = g.T.geom.n_slab;
     const int np = g.T.geom.n_poly;
     const int nh = g.T.hist.n_mat * P;
-    L.off_e2 = take(8 * (P + 1), 16);
-    L.off_band = take(8 * (nh + 1), 16);
+    if (!wide) L.off_e2 = take(8 * (P + 1), 16);
+    L.off_band = wide ? take(4 * (P + 1), 16) : take(8 * (nh + 1), 16);
     L.off_tot = take(4 * nh, 16);
     L.off_box4 = take(np > 0 ? 0 : 32 * nb, 16);
     L.off_grid = take(np > 0 ? 8 * g.T.geom.gx * g.T.geom.gy * g.T.geom.gz : 0, 16);
@@ -197,9 +243,10 @@ int build_image() {
     L.off_slabz = take(8 * (ns + 1), 16);
     L.off_slabm = take(8 * ns, 16);
     L.off_breg = take(np > 0 ? 0 : (int)sizeof(mt::BoxRegion) * nb, 16);
-    L.off_sreg = take((int)sizeof(mt::SlabRegion) * ns, 16);
+    L.off_sreg = take(np > 0 ? 0 : (int)sizeof(mt::SlabRegion) * ns, 16);
     L.bytes = (off + 15) / 16 * 16;
-    // not staged (read from memory beside a block's faces only)
+    // not staged (read from memory beside a block's faces, wide: on a rounded edge)
+    if (wide) L.off_e2 = take(8 * (P + 1), 16);
     L.off_blk = take(8 * mt::kBlockRec * np, 16);
     L.off_preg = take((int)sizeof(mt::BlockRegion) * np, 16);
     std::vector<unsigned char> img((size_t)(off + 15) / 16 * 16, 0);
@@ -210,18 +257,26 @@ int build_image() {
     if (g.hist_loaded) {
         put(L.off_e2, H.e2);
         put(L.off_tot, H.totals);
-        // bands (see kBandLow); the kernels raise them to the run's threshold
-        std::vector<uint32_t> band(2 * ((size_t)nh + 1));
+        // bands or their ends (see kBandLow); the kernels raise them to the run's threshold
         auto bits = [](float f) { uint32_t u; std::memcpy(&u, &f, 4); return u; };
-        for (int h = 0; h <= nh; ++h) {
-            const int i = h % P;
-            uint32_t lo = bits(mt::kBandLow), hi = 0x7f800000u;
-            if (h < nh && i > 0) lo = std::max(lo, bits((float)H.e2[(size_t)i]) + 1u);
-            if (h < nh && i < P - 1) hi = bits((float)H.e2[(size_t)i + 1]);
-            band[2 * (size_t)h] = lo;
-            band[2 * (size_t)h + 1] = hi > lo ? hi - lo : 0u;
+        std::vector<uint32_t> end((size_t)P + 1);
+        for (int i = 0; i <= P; ++i) {
+            end[(size_t)i] = bits(mt::kBandLow) - 1u;
+            if (i > 0) end[(size_t)i] = std::max(end[(size_t)i], bits((float)H.e2[(size_t)i]));
+            if (i == P) end[(size_t)i] = 0x7f800000u;
         }
-        put(L.off_band, band);
+        if (wide) {
+            put(L.off_band, end);
+        } else {
+            std::vector<uint32_t> band;
+            for (int h = 0; h <= nh; ++h) {
+                const uint32_t lo = end[(size_t)(h < nh ? h % P : 0)] + 1u;
+                const uint32_t hi = end[(size_t)(h < nh ? h % P + 1 : P)];
+                band.push_back(lo);
+                band.push_back(hi > lo ? hi - lo : 0u);
+            }
+            put(L.off_band, band);
+        }
     }
     put(L.off_bf, H.bfield);
     put(L.off_mat, H.material);
@@ -238,10 +293,23 @@ int build_image() {
         put(L.off_breg, H.box_region);
         put(L.off_sreg, H.slab_region);
     }
+    return img;
+}
+
+// Both layouts' images, uploaded as one block.
+int build_image() {
+    mt::LdsLayout L{}, W{};
+    std::vector<unsigned char> img = make_image(false, L);
+    const size_t wide_at = (img.size() + 255) / 256 * 256;
+    const std::vector<unsigned char> wide = make_image(true, W);
+    img.resize(wide_at);
+    img.insert(img.end(), wide.begin(), wide.end());
     const int rc = g.image.upload(img.data(), img.size());
     if (rc) return rc;
     g.T.lds = L;
+    g.T.wide_lds = W;
     g.T.image = reinterpret_cast<const uint4 *>(g.image.p);
+    g.T.wide_image = g.T.image + wide_at / sizeof(uint4);
     return MT_OK;
 }
 
@@ -346,6 +414,7 @@ int validate(const mt_params *p, int64_t n, const mt_muons *in, const mt_muons *
     R.pmin2 = p->p_min * p->p_min;
     // few waves to run (see kRoom; blocks without a map: see plain_min_waves)
     const int64_t chip = 64 * 4 * (int64_t)g.cu_count;      // lanes of one wave a SIMD
+    R.wide = (p->trace && p->trace_steps > 0 && p->n_trace > 0) || wide_tables(c.lanes, chip);
     const bool blocks = g.T.geom.n_poly > 0 && g.T.field.map == nullptr;
     R.room = c.lanes <= 4 * chip || (blocks && c.lanes > 5 * chip && c.lanes <= 8 * chip);
     R.ahead = c.lanes <= 5 * chip;                          // see kAhead
@@ -482,6 +551,7 @@ void shape_small(const mt_params *p, Call &c) {
     const bool diverging = g.T.field.map != nullptr || g.T.geom.n_poly > 0;
     const int64_t most = wave * simds / (diverging ? 2 : 8);
     if (p->mode == MT_MODE_VARIANT_WAVES || c.R.n_trace > 0 || c.lanes > most) return;
+    if (c.R.wide && c.R.ckpt) return;          // (no such kernel)
     c.R.solo = 1;
     c.R.share_shift = 0;
     while (c.R.share_shift < 5 && c.lanes << (c.R.share_shift + 1) <= wave * simds)
@@ -762,6 +832,8 @@ int mt_load_histograms_ex(int32_t n_mat, int32_t n_pbin, const double *p_edges, 
     H.n_scat = n_scat;
     H.n_cells = (int32_t)K;
     H.gbits = gbits;
+    g.T.narrow = narrow_bins(p_edges, n_mat, n_pbin, n_loss, n_scat, loss_lo, loss_hi, log_l,
+                             cdf.data());
     H.nscat_f = (float)n_scat;
     H.nscat_inv = 1.0f / (float)n_scat;
     // axis origin and bin width in the axis' own units (log10 on a log axis)
@@ -1508,7 +1580,7 @@ void mt_release(void) {
         (void)hipStreamDestroy(g.cap_stream);
         g.cap_stream = nullptr;
     }
-    g.T = Tables{};
+    g.T = AllTables{};
     g.hist_loaded = g.geom_loaded = false;
     g.n_mat = g.n_pbin = 0;
     g.max_material = -1;

@@ -10,6 +10,7 @@
 namespace mt {
 
 constexpr int kWave = 64;
+constexpr int kLdsBytes = 160 * 1024;      // LDS of a CU
 constexpr int kCkptEvery = 16;             // RK4 state checkpoint interval
 constexpr double kKappa = 0.299792458;     // GeV / (c T m)
 constexpr int kBlockRec = 20;              // doubles per convex block record
@@ -118,7 +119,9 @@ struct DevField {
 };
 
 // Byte offsets of the tables every block stages in LDS: squared momentum
-// edges, the bands and totals of the histograms, and the geometry.
+// edges, the bands and totals of the histograms, and the geometry; in the wide
+// layout (AllTables) the ends of the momentum bins' bands (at off_band), the totals
+// and the geometry.
 struct LdsLayout {
     int32_t off_e2, off_band, off_tot, off_box4, off_mat, off_bf, off_mag, off_slabz, off_slabm, off_breg, off_sreg;
     int32_t off_blk, off_grid, off_preg, off_planes;
@@ -134,6 +137,7 @@ struct DevRun {
     int32_t room;                // few waves in the launch (see kRoom)
     int32_t ahead;               // variant-wave form: form the next step's draw ahead
     int32_t solo;                // variant-wave form: one of those lanes carries a muon
+    int32_t wide;                // the kernels for large tables run (see AllTables)
     double pmin2;
     int32_t max_steps;
     uint32_t key0, key1;
@@ -163,6 +167,21 @@ struct Tables {
     LdsLayout lds;
 };
 
+// Host side: the tables with both layouts of their image.
+//
+// Every block of a launch stages its own copy, so a large copy takes waves off a
+// CU (160 KB of LDS).  And with narrow momentum bins a step takes muons over several
+// of them, past the next lower one that the common step looks at.  The wide kernels,
+// for such tables, stage one band end of 4 bytes per momentum bin instead of a band
+// of 8 per histogram, keep the edges in memory and walk down the bins; they have the
+// general field only.  10^6 muons through 40 boxes: 4 materials of 1024 bins 12.75 ->
+// 5.03 ms, 3 of 600 6.89 -> 4.83, 43 of 95 7.77 -> 4.57; but 3 of 95 bins 3.84 -> 4.55.
+struct AllTables : Tables {
+    int32_t narrow;              // many draws cross more than one momentum bin
+    LdsLayout wide_lds;
+    const uint4 *wide_image;
+};
+
 // One pass of the compacting form: the items (the launch's lanes, or the
 // output slots listed by the previous pass) step from k_begin up to the
 // DevRun::max_steps of the launch;
@@ -184,16 +203,18 @@ struct KArgs {
     DevRun R;
     DevIO io;
     PassArgs P;
+    uint32_t pbin_magic;         // floor((2^32 - 1) / n_pbin): h / n_pbin = umulhi(h + 1, it),
+                                 // exact for h < 2^16
 };
 
 // Launchers implemented in mt_kernels.hip.
-hipError_t launch_plain(const Tables &T, const DevRun &R, const DevIO &io, int block,
+hipError_t launch_plain(const AllTables &T, const DevRun &R, const DevIO &io, int block,
                         hipStream_t s);
 // One pass of the compacting form (see PassArgs).
-hipError_t launch_pass(const Tables &T, const DevRun &R, const DevIO &io, int block,
+hipError_t launch_pass(const AllTables &T, const DevRun &R, const DevIO &io, int block,
                        const PassArgs &P, hipStream_t s);
 // Variant-wave form: groups of 2^R.share_shift lanes hold variants of one muon.
-hipError_t launch_variant_waves(const Tables &T, const DevRun &R, const DevIO &io, int block,
+hipError_t launch_variant_waves(const AllTables &T, const DevRun &R, const DevIO &io, int block,
                                hipStream_t s);
 // Field map tables from the node values (device pointers; nodesv and mapv may be
 // nullptr).  *bad, set to ~0 beforehand, receives the lowest cell whose
@@ -202,7 +223,7 @@ hipError_t launch_map_tables(const float *b, int nx, int ny, int nz, float4 *nod
                              float4 *map, float4 *mapv, unsigned long long *bad, hipStream_t s);
 hipError_t launch_queue_reset(unsigned long long *queue, double *zero, int64_t n_zero,
                               hipStream_t s);
-hipError_t launch_adjoint(const Tables &T, const DevRun &R, const DevIO &io,
+hipError_t launch_adjoint(const AllTables &T, const DevRun &R, const DevIO &io,
                           const double *g_out, double *g_in, double *gs_lane, void *scratch,
                           int block, bool lds_history, hipStream_t s);
 // Deterministic per-variant sums.  tally: (zmax count, hit count, sigmoid sum);

@@ -126,8 +126,9 @@ __device__ __forceinline__ ArgPtr cold(ArgPtr p) {
 // Tables staged in LDS by every block.
 // ---------------------------------------------------------------------------
 struct Lds {
-    const double *e2;
+    const double *e2;           // squared momentum edges (kWide: not staged)
     const uint2 *band;          // [n_hist + 1]: band of |p|^2 of every histogram, see kBandLow
+    const uint32_t *edge;       // kWide, instead: [n_pbin + 1] ends of the momentum bins' bands
     const uint32_t *tot;
     const double *box4;
     const int32_t *mat;
@@ -149,13 +150,14 @@ __device__ __forceinline__ char *lds_base() {
 }
 
 // The staged tables of a layout.
-template <class TT>
+template <bool WIDE, class TT>
 __device__ __forceinline__ Lds lds_view(const TT &T) {
     const auto &L = T.lds;
     char *smem = lds_base();
     const char *image = reinterpret_cast<const char *>(T.image);
-    return Lds{reinterpret_cast<double *>(smem + L.off_e2),
+    return Lds{reinterpret_cast<const double *>(WIDE ? image + L.off_e2 : smem + L.off_e2),
                reinterpret_cast<uint2 *>(smem + L.off_band),
+               reinterpret_cast<uint32_t *>(smem + L.off_band),
                reinterpret_cast<uint32_t *>(smem + L.off_tot),
                reinterpret_cast<double *>(smem + L.off_box4),
                reinterpret_cast<int32_t *>(smem + L.off_mat),
@@ -174,11 +176,19 @@ __device__ __forceinline__ Lds lds_view(const TT &T) {
 // Copies the image of the tables (one coalesced 16-byte load per thread and
 // trip, all in flight together) and raises the bands to the momentum threshold
 // of the run.
+template <bool WIDE>
 __device__ __forceinline__ void stage_tables(const Tables &T, double pmin2) {
     uint4 *dst = reinterpret_cast<uint4 *>(lds_base());
     const int tid = threadIdx.x, nt = blockDim.x, n16 = T.lds.bytes / 16;
     for (int i = tid; i < n16; i += nt) dst[i] = T.image[i];
     __syncthreads();
+    if constexpr (WIDE) {
+        uint32_t *edge = reinterpret_cast<uint32_t *>(lds_base() + T.lds.off_band);
+        const uint32_t threshold = __float_as_uint((float)pmin2);
+        for (int i = tid; i < T.hist.n_pbin; i += nt) edge[i] = max(edge[i], threshold);
+        __syncthreads();
+        return;
+    }
     uint2 *band = reinterpret_cast<uint2 *>(lds_base() + T.lds.off_band);
     const uint32_t above = __float_as_uint((float)pmin2) + 1u;
     for (int i = tid; i <= T.hist.n_mat * T.hist.n_pbin; i += nt) {
@@ -627,6 +637,35 @@ __device__ __forceinline__ int find_bin(const Lds &S, int P, double p2, int i) {
     return i;
 }
 
+// The same with large tables, by pb, the bits of float(|p|^2), and the ends of the
+// bands, which decide as |p|^2 would (a raised end is no larger than pb, |p|^2
+// being at least the threshold) unless pb is on one of them or outside every band:
+// then the edges in memory decide.
+__device__ __forceinline__ int find_bin_wide(const Lds &S, int P, double p2, uint32_t pb, int i) {
+    if (p2 != p2) return max(i, 0);
+    if (i <= 0) {
+        int lo = 0, hi = P - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (S.edge[mid] <= pb) lo = mid; else hi = mid - 1;
+        }
+        i = lo;
+    } else {
+        while (i > 0 && pb < S.edge[i]) --i;
+        while (i < P - 1 && pb >= S.edge[i + 1]) ++i;
+    }
+    if (pb <= S.edge[i] || pb >= 0x7f800000u) {
+        while (i > 0 && p2 < S.e2[i]) --i;
+        while (i < P - 1 && p2 >= S.e2[i + 1]) ++i;
+    }
+    return i;
+}
+
+// The band between two ends: first pattern and number of patterns.
+__device__ __forceinline__ uint2 band_between(uint32_t lo, uint32_t hi) {
+    return make_uint2(lo + 1u, __builtin_elementwise_sub_sat(hi, lo + 1u));
+}
+
 // Exact inverse CDF: t = floor(w * T / 2^32), cell = smallest c with C[c] > t.
 // The guide entry of the word's top bits brackets c in [lo, hi] and carries
 // C[lo]: t < C[lo] gives lo at once, a bracket of two cells gives hi, and only
@@ -1024,7 +1063,7 @@ __device__ __forceinline__ void rk4_from(Lane &L, float3 a0, float3 cb, bool ben
 enum : unsigned {
     kMap = 1u,       // a field map is loaded
     kTape = 2u,      // write checkpoints and the kick tape (differentiable form)
-    kTrace = 4u,     // per-step (volume, bin, cell) trace of the first lanes
+    kWide = 4u,      // large histogram tables (see AllTables), and per-step traces
     kAlias = 8u,     // alias-method sampler instead of the inverse CDF
     kNearest = 16u,  // nearest-node map lookup instead of trilinear (with kMap)
     kStages = 32u,   // field evaluated at every RK4 stage position
@@ -1039,11 +1078,10 @@ enum : unsigned {
 
 // Masks that have a kernel: the tape belongs to the differentiable form,
 // whose adjoint holds the trilinear field over each step, and the
-// nearest-node lookup needs a map; traces (a debugging aid) run the general
-// field.
+// nearest-node lookup needs a map; large tables and traces run the general field.
 constexpr bool valid_mask(unsigned F) {
     return !((F & kTape) && (F & (kNearest | kStages))) && !((F & kNearest) && !(F & kMap)) &&
-           !((F & kPoly) && (F & (kTape | kStages))) && !((F & kVert) && (F & kTrace));
+           !((F & kPoly) && (F & (kTape | kStages))) && !((F & kVert) && (F & kWide));
 }
 
 // The map part of the field, added to the volume's, through the lane's cell.
@@ -1063,7 +1101,7 @@ __device__ __forceinline__ float3 field_at_point(const KArgs &A, ArgPtr args, La
     float3 B = make_float3(L.bx, L.by, L.bz);
     if (!inside) {
         const ArgPtr c = cold(args);
-        const Lds S = lds_view(c->T);
+        const Lds S = lds_view<(F & kWide) != 0>(c->T);
         const int vol = find_box(S, find_slab(S, c->T.geom.n_slab, z, L.slab), x, y);
         if (vol != L.vol) B = box_field<(F & kVert) != 0>(c->T, S, c->R, vol, var());
     }
@@ -1177,7 +1215,7 @@ __device__ __forceinline__ bool locate_region(Lane &L, V &&var, int k, double p2
     const ArgPtr c = cold(args);
     const auto &T = c->T;
     const auto &R = c->R;
-    const Lds S = lds_view(T);
+    const Lds S = lds_view<(F & kWide) != 0>(T);
     const int P = T.hist.n_pbin, gbits = T.hist.gbits;
     if (outside) {
         int vol;
@@ -1244,11 +1282,20 @@ __device__ __forceinline__ bool locate_region(Lane &L, V &&var, int k, double p2
             L.steps = k;
             return false;
         }
-        uint2 r = S.band[T.hist.n_mat * P];
+        uint2 r;
+        if constexpr ((F & kWide) != 0) r = band_between(S.edge[0], S.edge[P]);
+        else r = S.band[T.hist.n_mat * P];
         if (L.hoff != kVacuum) {
-            const int h0 = S.mat[L.vol] * P;
-            const uint32_t h = (uint32_t)(h0 + find_bin(S, P, p2, (int)hist_of<F>(L, gbits) - h0));
-            r = S.band[h];
+            const int h0 = S.mat[L.vol] * P, guess = (int)hist_of<F>(L, gbits) - h0;
+            uint32_t h;
+            if constexpr ((F & kWide) != 0) {
+                const int i = find_bin_wide(S, P, p2, __float_as_uint(p2f), guess);
+                h = (uint32_t)(h0 + i);
+                r = band_between(S.edge[i], S.edge[i + 1]);
+            } else {
+                h = (uint32_t)(h0 + find_bin(S, P, p2, guess));
+                r = S.band[h];
+            }
             L.hoff = h * row_of<F>(gbits);
             if constexpr ((F & kAlias) == 0) L.tot = S.tot[h];
         }
@@ -1258,12 +1305,41 @@ __device__ __forceinline__ bool locate_region(Lane &L, V &&var, int k, double p2
     return true;
 }
 
+// Large tables: a muon that went into a lower bin of the same volume, one or several
+// below its own, walks down the ends of the bands (those at the threshold or below
+// are one and the same: a muon that stops does not walk them).  The bin is the
+// histogram's index modulo n_pbin, an exact division by multiplication.
+template <unsigned F>
+__device__ __forceinline__ void lower_bin(Lane &L, uint32_t pb, const KArgs &A) {
+    const char *lds = lds_base();
+    const uint32_t *edge = reinterpret_cast<const uint32_t *>(lds + A.T.lds.off_band);
+    if ((pb < L.plo) & (L.hoff != kVacuum) & (pb > edge[0])) {
+        const uint32_t h = hist_of<F>(L, A.T.hist.gbits);
+        const uint32_t bin =
+            h - __umulhi(h + 1u, A.pbin_magic) * (uint32_t)A.T.hist.n_pbin;
+        uint32_t i = max(bin, 1u) - 1u, lo = edge[i], hi = edge[i + 1u];
+        while ((pb <= lo) & (i > 0u)) {
+            hi = lo;
+            lo = edge[--i];
+        }
+        const uint2 r = band_between(lo, hi);
+        if (pb - r.x < r.y) {
+            L.hoff -= (bin - i) * row_of<F>(A.T.hist.gbits);
+            if constexpr ((F & kAlias) == 0)
+                L.tot = reinterpret_cast<const uint32_t *>(lds + A.T.lds.off_tot)[h - (bin - i)];
+            L.plo = r.x;
+            L.pspan = r.y;
+        }
+    }
+}
+
 // A muon that went into the next lower bin of the same volume (3-4 % of steps,
 // so some lane of a wavefront in most of them): the histogram before its own,
 // whose band is above the threshold.  A momentum below a material's bin 0 is
 // below that row's band too.
 template <unsigned F>
 __device__ __forceinline__ void next_lower_bin(Lane &L, uint32_t pb, const KArgs &A) {
+    if constexpr ((F & kWide) != 0) return lower_bin<F>(L, pb, A);
     if ((pb < L.plo) & (L.hoff != kVacuum)) {
         const uint32_t h = max(hist_of<F>(L, A.T.hist.gbits), 1u) - 1u;
         const char *lds = lds_base();
@@ -1288,7 +1364,7 @@ __device__ __forceinline__ uint2 sampler_entry(const DevHist &H, uint32_t hoff, 
 template <unsigned F, typename V, typename W>
 __device__ __forceinline__ bool advance(Lane &L, int64_t g, V &&var, W &&words, int k,
                                         const KArgs &A, ArgPtr args, const StepConst &sc) {
-    constexpr bool TAPE = (F & kTape) != 0, TRACE = (F & kTrace) != 0, VERT = (F & kVert) != 0;
+    constexpr bool TAPE = (F & kTape) != 0, TRACE = (F & kWide) != 0, VERT = (F & kVert) != 0;
     const DevHist &H = A.T.hist;
     const DevRun &R = A.R;
     const double p2 = L.px * L.px + L.py * L.py + L.pz * L.pz;
@@ -1372,7 +1448,7 @@ __device__ __forceinline__ bool advance(Lane &L, int64_t g, V &&var, W &&words, 
         t[1] = uy;
         t[2] = uz;
     }
-    if (TRACE && g < R.n_trace && k < R.trace_steps) {
+    if (TRACE && R.n_trace > 0 && g < R.n_trace && k < R.trace_steps) {
         int32_t *tr = R.trace + ((size_t)g * R.trace_steps + k) * 3;
         tr[0] = L.vol;
         tr[1] = bin;
@@ -1452,7 +1528,7 @@ k_plain(KArgs A) {
     constexpr bool CKPT = (F & kTape) != 0;
     const ArgPtr args = kernel_args();
     const DevRun &R = A.R;
-    stage_tables(A.T, R.pmin2);
+    stage_tables<(F & kWide) != 0>(A.T, R.pmin2);
     const StepConst sc = step_const(R);
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= R.lanes) return;
@@ -1518,7 +1594,7 @@ k_pass(KArgs A) {
     // of the previous pass, whose count that pass left in memory
     const int64_t items = P.n_in ? (int64_t)*P.n_in : R.lanes;
     if ((int64_t)blockIdx.x * blockDim.x >= items) return;     // the whole block
-    stage_tables(A.T, R.pmin2);
+    stage_tables<(F & kWide) != 0>(A.T, R.pmin2);
     const StepConst sc = step_const(R);
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     bool parked = false;        // still running at the pass's end: goes on in the next pass
@@ -1535,7 +1611,7 @@ k_pass(KArgs A) {
         // passed there is the one the next pass repeats at the same step.
         if (L.status == MT_ST_RUNNING) {
             // the output slot, which only traces need in the loop
-            const int64_t g = (F & kTrace) && P.n_in ? P.in[i] : i;
+            const int64_t g = (F & kWide) && P.n_in ? P.in[i] : i;
             auto var = [&] {
                 const ArgPtr c = cold(args);
                 return (int)variant_of(c->P.n_in ? c->P.in[i] : i, c->R);
@@ -1601,13 +1677,13 @@ constexpr int waves_min_waves(unsigned F, bool ahead) {
     return (F & (kMap | kStages)) ? plain_min_waves(F) : (F & kVert) && !ahead ? 7 : 6;
 }
 
-template <unsigned F, bool AHEAD>     // F holds no kTrace; kTape for lone muons only
+template <unsigned F, bool AHEAD>     // kTape for lone muons only
 __global__ void __launch_bounds__(1024)
     __attribute__((amdgpu_waves_per_eu(waves_min_waves(F, AHEAD))))
 k_variant_waves(KArgs A) {
     const ArgPtr args = kernel_args();
     const DevRun &R = A.R;
-    stage_tables(A.T, R.pmin2);
+    stage_tables<(F & kWide) != 0>(A.T, R.pmin2);
     const StepConst sc = step_const(R);
     const int lane = (int)(threadIdx.x & (kWave - 1));
     const int gs = R.share_shift, gm = (1 << gs) - 1;   // G = 2^gs lanes per muon
@@ -1918,8 +1994,8 @@ template <bool MAP, bool LDSH, bool V>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MAP ? 1 : 5)))
 k_adjoint(Tables T, DevRun R, DevIO io, const double *g_out,
                                                  double *g_in, double *gs_lane, char *scratch) {
-    stage_tables(T, R.pmin2);
-    const Lds S = lds_view(T);
+    stage_tables<true>(T, R.pmin2);
+    const Lds S = lds_view<true>(T);
     char *smem = lds_base();
     const StepConst sc = step_const(R);
     const int bd = blockDim.x;
@@ -2248,7 +2324,7 @@ __global__ void k_pass2(const double *partial, int nb, int n_cols, int n_variant
 // ---------------------------------------------------------------------------
 template <unsigned F, unsigned ROOM>
 static const void *plain_kernel() {
-    constexpr bool own = !(F & (kStages | kTape | kTrace)) &&
+    constexpr bool own = !(F & (kStages | kTape | kWide)) &&
                          (blocks_alone(F) || ((F & kMap) && !(F & kVert)));
     if constexpr (!valid_mask(F)) return nullptr;
     else return reinterpret_cast<const void *>(&k_plain<own ? F | ROOM : F>);
@@ -2256,17 +2332,17 @@ static const void *plain_kernel() {
 
 template <unsigned F, unsigned ROOM>
 static const void *persistent_kernel() {
-    constexpr bool own = blocks_alone(F) && !(F & kTrace);
+    constexpr bool own = blocks_alone(F) && !(F & kWide);
     if constexpr (valid_mask(F) && !(F & kTape))
         return reinterpret_cast<const void *>(&k_pass<own ? F | ROOM : F>);
     else return nullptr;
 }
 
 // Lone muons (the only use with a tape) are always few: their kernel forms
-// draws ahead where it can.
+// draws ahead where it can.  The kernels for large tables do not, and have no tape.
 template <unsigned F, bool AHEAD>
 static const void *variant_waves_kernel() {
-    if constexpr (!valid_mask(F) || (F & kTrace)) return nullptr;
+    if constexpr (!valid_mask(F) || ((F & kWide) && (AHEAD || (F & kTape)))) return nullptr;
     else if constexpr (!AHEAD && kAhead<F> && (F & kTape)) return nullptr;
     else return reinterpret_cast<const void *>(&k_variant_waves<F, AHEAD && kAhead<F>>);
 }
@@ -2286,31 +2362,43 @@ static std::array<const void *, sizeof...(I)> persistent_kernels(std::index_sequ
     return {persistent_kernel<(unsigned)I, ROOM>()...};
 }
 
-static unsigned feature_mask(const Tables &T, const DevRun &R) {
-    const bool map = T.field.map != nullptr;
+// The tables in the layout of the kernel.
+static Tables tables_for(const AllTables &T, bool wide) {
+    Tables t = T;
+    if (wide) {
+        t.lds = T.wide_lds;
+        t.image = T.wide_image;
+    }
+    return t;
+}
+
+static uint32_t pbin_magic(const Tables &T) { return 0xFFFFFFFFu / (uint32_t)T.hist.n_pbin; }
+
+static unsigned feature_mask(const AllTables &T, const DevRun &R) {
+    const bool map = T.field.map != nullptr, wide = R.wide != 0;
     return (map ? kMap : 0u) | (R.ckpt != nullptr ? kTape : 0u) |
-           (R.n_trace > 0 ? kTrace : 0u) | (R.sampler == MT_SAMPLER_ALIAS ? kAlias : 0u) |
+           (wide ? kWide : 0u) | (R.sampler == MT_SAMPLER_ALIAS ? kAlias : 0u) |
            (map && R.interp == MT_INTERP_NEAREST ? kNearest : 0u) |
            (R.stage_field ? kStages : 0u) | (T.geom.n_poly > 0 ? kPoly : 0u) |
            (T.hist.log_loss || T.hist.log_scat ? kLog : 0u) |
-           (T.geom.vertical && (!map || T.field.vertical) && R.n_trace == 0 ? kVert : 0u);
+           (T.geom.vertical && (!map || T.field.vertical) && !wide ? kVert : 0u);
 }
 
-hipError_t launch_plain(const Tables &T, const DevRun &R, const DevIO &io, int block,
+hipError_t launch_plain(const AllTables &T, const DevRun &R, const DevIO &io, int block,
                         hipStream_t s) {
     static const auto many = plain_kernels<0u>(std::make_index_sequence<kFeatures>());
     static const auto few = plain_kernels<kRoom>(std::make_index_sequence<kFeatures>());
     const auto &fns = R.room ? few : many;
     if (R.lanes == 0) return hipSuccess;
     const unsigned grid = (unsigned)((R.lanes + block - 1) / block);
-    KArgs a{T, R, io, PassArgs{}};
+    KArgs a{tables_for(T, R.wide != 0), R, io, PassArgs{}, pbin_magic(T)};
     void *args[] = {&a};
     const void *fn = fns[feature_mask(T, R)];
     if (fn == nullptr) return hipErrorInvalidValue;     // excluded by argument validation
-    return hipLaunchKernel(fn, dim3(grid), dim3(block), args, (size_t)T.lds.bytes, s);
+    return hipLaunchKernel(fn, dim3(grid), dim3(block), args, (size_t)a.T.lds.bytes, s);
 }
 
-hipError_t launch_pass(const Tables &T, const DevRun &R, const DevIO &io, int block,
+hipError_t launch_pass(const AllTables &T, const DevRun &R, const DevIO &io, int block,
                        const PassArgs &P, hipStream_t s) {
     static const auto many = persistent_kernels<0u>(std::make_index_sequence<kFeatures>());
     static const auto few = persistent_kernels<kRoom>(std::make_index_sequence<kFeatures>());
@@ -2319,18 +2407,19 @@ hipError_t launch_pass(const Tables &T, const DevRun &R, const DevIO &io, int bl
     // sized for every lane (the survivors of a pass are at most that many);
     // blocks past the pass's items exit before staging their tables
     const unsigned grid = (unsigned)((R.lanes + block - 1) / block);
-    KArgs a{T, R, io, P};
+    KArgs a{tables_for(T, R.wide != 0), R, io, P, pbin_magic(T)};
     void *args[] = {&a};
     const void *fn = fns[feature_mask(T, R) & ~kTape];
     if (fn == nullptr) return hipErrorInvalidValue;     // excluded by argument validation
-    return hipLaunchKernel(fn, dim3(grid), dim3(block), args, (size_t)T.lds.bytes, s);
+    return hipLaunchKernel(fn, dim3(grid), dim3(block), args, (size_t)a.T.lds.bytes, s);
 }
 
-hipError_t launch_variant_waves(const Tables &T, const DevRun &R, const DevIO &io, int block,
+hipError_t launch_variant_waves(const AllTables &T, const DevRun &R, const DevIO &io, int block,
                                hipStream_t s) {
     static const auto now = variant_waves_kernels<false>(std::make_index_sequence<kFeatures>());
     static const auto ahead = variant_waves_kernels<true>(std::make_index_sequence<kFeatures>());
-    const auto &fns = R.solo || R.ahead ? ahead : now;
+    const bool draw_ahead = (R.solo || R.ahead) && !R.wide;
+    const auto &fns = draw_ahead ? ahead : now;
     if (R.lanes == 0) return hipSuccess;
     // (muon, group of G variants) units, 64 / G per wavefront
     const int64_t units = R.solo ? R.lanes : R.lanes >> R.share_shift;
@@ -2338,11 +2427,11 @@ hipError_t launch_variant_waves(const Tables &T, const DevRun &R, const DevIO &i
     const int64_t waves = (units + per_wave - 1) / per_wave;
     const int64_t per_block = block / kWave;
     const unsigned grid = (unsigned)((waves + per_block - 1) / per_block);
-    KArgs a{T, R, io, PassArgs{}};
+    KArgs a{tables_for(T, R.wide != 0), R, io, PassArgs{}, pbin_magic(T)};
     void *args[] = {&a};
     const void *fn = fns[feature_mask(T, R)];
     if (fn == nullptr) return hipErrorInvalidValue;     // excluded by argument validation
-    const size_t lds = (size_t)T.lds.bytes + (R.solo || R.ahead ? 2 : 1) * (size_t)block * sizeof(uint4);
+    const size_t lds = (size_t)a.T.lds.bytes + (draw_ahead ? 2 : 1) * (size_t)block * sizeof(uint4);
     return hipLaunchKernel(fn, dim3(grid), dim3(block), args, lds, s);
 }
 
@@ -2371,14 +2460,15 @@ int64_t adjoint_scratch_bytes(const Tables &T, int64_t lanes) {
 // Where the adjoint keeps a segment's start states: device memory (default;
 // at 16 steps x 12 B per lane it stays L2/Infinity-Cache resident and leaves
 // LDS free for occupancy) or, on request and without a field map, LDS.
-hipError_t launch_adjoint(const Tables &T, const DevRun &R, const DevIO &io,
+hipError_t launch_adjoint(const AllTables &T, const DevRun &R, const DevIO &io,
                           const double *g_out, double *g_in, double *gs_lane, void *scratch,
                           int block, bool lds_history, hipStream_t s) {
     if (R.lanes == 0) return hipSuccess;
     const int64_t grid = (R.lanes + block - 1) / block;
     const bool map = T.field.map != nullptr;
     const bool ldsh = lds_history && !map;
-    size_t shm = (size_t)((T.lds.bytes + 15) & ~15) + (size_t)T.geom.n_mag * block * sizeof(double);
+    const Tables t = tables_for(T, true);      // (it looks no momentum bin up: the smaller image)
+    size_t shm = (size_t)((t.lds.bytes + 15) & ~15) + (size_t)T.geom.n_mag * block * sizeof(double);
     if (ldsh) shm += (size_t)kCkptEvery * 3 * block * sizeof(float);   // p0 per step
     shm += (size_t)kCkptEvery * block;                                   // volume per step
     char *sc = reinterpret_cast<char *>(scratch);
@@ -2386,7 +2476,7 @@ hipError_t launch_adjoint(const Tables &T, const DevRun &R, const DevIO &io,
     auto fn = map    ? (vert ? &k_adjoint<true, false, true> : &k_adjoint<true, false, false>)
               : ldsh ? (vert ? &k_adjoint<false, true, true> : &k_adjoint<false, true, false>)
                      : (vert ? &k_adjoint<false, false, true> : &k_adjoint<false, false, false>);
-    hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(block), shm, s, T, R, io, g_out, g_in, gs_lane,
+    hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(block), shm, s, t, R, io, g_out, g_in, gs_lane,
                        sc);
     return hipGetLastError();
 }

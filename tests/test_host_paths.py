@@ -1,0 +1,60 @@
+"""CPU: the library's host code on a HIP runtime of host memory (no kernel runs):
+what the loaders keep on the device, and what the launches ask for."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+from paper_2512_10520_amd import workloads as W
+from tests import _custom as CU
+from tests import _host_stub
+
+MODES = {"plain": 0, "persistent": 1, "variant_waves": 2}
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    return _host_stub.build(tmp_path_factory.mktemp("stub"))
+
+
+def _tables(n_pbin, n_mat, loss=(0.0, 0.05)):
+    h = CU.flat_histograms(n_pbin=n_pbin, p_lo=0.18, p_hi=400.0, loss=loss)
+    return dataclasses.replace(h, counts=np.ascontiguousarray(np.repeat(h.counts, n_mat, axis=0)))
+
+
+def _boxes(n=64):
+    return CU.geometry([[-1, 1, -1, 1, i, i + 0.9] for i in range(n)], [0] * n)
+
+
+def _blocks(n=64):
+    q = [-1, -1, 1, -1, 1, 1, -1, 1]
+    return CU.geometry([], [0] * n, poly=[[i, i + 0.9] + q + q for i in range(n)])
+
+
+# ---- staged tables ---------------------------------------------------------
+def staged(s, n_pbin, n_mat, blocks, loss, n, limit, wide):
+    assert s.histograms(_tables(n_pbin, n_mat, loss)) == 0
+    assert s.geometry(_blocks() if blocks else _boxes()) == 0
+    for mode in (0, 1):
+        assert s.propagate(s.params(mode=mode, block=256), n) == 0
+        for l in s.launches():
+            if "k_plain" in l.name or "k_pass" in l.name:
+                mask = int(l.name.split("ILj")[1].split("E")[0])
+                assert l.lds <= limit, l
+                assert bool(mask & 4) == wide, l
+
+
+@pytest.mark.parametrize("n_pbin,n_mat,blocks,loss,n,limit,wide", [
+    # the largest tables (limit: edges, totals and geometry alone)
+    (1024, 4, False, (0.0, 0.05), 10 ** 6, 30_240, True),
+    (1024, 4, True, (0.0, 0.05), 10 ** 6, 44_552, True),
+    (95, 43, False, (0.0, 0.05), 10 ** 6, 30_240, True),
+    (95, 43, False, (0.0, 0.05), 50_000, 10 ** 6, False),    # all blocks resident at once
+    # narrow bins or not, by the losses of a step
+    (600, 1, False, (0.0, 0.02), 10 ** 6, 30_240, True),
+    (400, 1, False, (0.0, 0.02), 10 ** 6, 30_240, False),
+    (1024, 1, False, (0.0, 0.005), 10 ** 6, 30_240, False),
+    (95, 3, False, (0.0, 0.05), 10 ** 6, 30_240, False)])
+def test_staged_tables(stub, n_pbin, n_mat, blocks, loss, n, limit, wide):
+    _host_stub.run(stub, "tests.test_host_paths", "staged", n_pbin, n_mat, blocks, loss, n, limit,
+                   wide)
