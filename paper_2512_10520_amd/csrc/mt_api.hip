@@ -554,9 +554,14 @@ void shape_small(const mt_params *p, Call &c) {
     if (c.R.wide && c.R.ckpt) return;          // (no such kernel)
     c.R.solo = 1;
     c.R.share_shift = 0;
-    while (c.R.share_shift < 5 && c.lanes << (c.R.share_shift + 1) <= wave * simds)
-        ++c.R.share_shift;
     c.block = 64;
+    // waves resident at once: one a SIMD unless the blocks' tables fill the LDS first
+    // (43 materials of 95 bins, 2 blocks a CU: 2000 muons in 1000 waves 1.21 ms, in 500
+    // waves 0.82; 20 000 through 40 convex blocks 2.68 and 2.09)
+    const int64_t tables = (c.R.wide ? g.T.wide_lds : g.T.lds).bytes + 2 * 64 * (int64_t)sizeof(uint4);
+    const int64_t waves = g.cu_count * std::min<int64_t>(4, mt::kLdsBytes / tables);
+    while (c.R.share_shift < 5 && c.lanes << (c.R.share_shift + 1) <= wave * waves)
+        ++c.R.share_shift;
 }
 
 const TuneEntry *find_tuned(const std::vector<unsigned char> &key) {

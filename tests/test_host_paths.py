@@ -58,3 +58,21 @@ def staged(s, n_pbin, n_mat, blocks, loss, n, limit, wide):
 def test_staged_tables(stub, n_pbin, n_mat, blocks, loss, n, limit, wide):
     _host_stub.run(stub, "tests.test_host_paths", "staged", n_pbin, n_mat, blocks, loss, n, limit,
                    wide)
+
+
+# ---- lone muons ------------------------------------------------------------
+def lone(s, n_mat, blocks, n):
+    assert s.histograms(_tables(95, n_mat)) == 0
+    assert s.geometry(_blocks() if blocks else _boxes()) == 0
+    for mode in (0, 1):
+        assert s.propagate(s.params(mode=mode), n) == 0
+        (l,) = s.launches()
+        assert "k_variant_waves" in l.name and l.block == 64
+        assert l.grid <= 256 * min(4, 160 * 1024 // l.lds), l
+
+
+@pytest.mark.parametrize("n", [1, 1000, 2000, 4097, 8192])
+@pytest.mark.parametrize("n_mat,blocks", [(1, False), (43, False), (20, True), (43, True)])
+def test_lone_muons_are_resident_at_once(stub, n_mat, blocks, n):
+    """One wave a SIMD, or as many as the staged tables leave room for."""
+    _host_stub.run(stub, "tests.test_host_paths", "lone", n_mat, blocks, n)
