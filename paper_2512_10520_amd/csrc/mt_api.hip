@@ -450,12 +450,19 @@ int n_part_blocks(int64_t n) {
 // Passes of the compacting form: steps per pass S (compact_every, at least
 // (max_steps + 1) / kMaxPasses) and their number.  Passes 0 .. P-2 end at
 // (p + 1) S <= max_steps, the last one runs to the step cap.
+// compact = kOnePass: one pass, whatever the step cap.
 constexpr int kMaxPasses = 64;
+constexpr int kOnePass = 0;
 
 void pass_plan(int max_steps, int compact, int *S, int *P) {
     const int64_t span = (int64_t)max_steps + 1;
     int64_t st = std::max<int64_t>(compact, (span + kMaxPasses - 1) / kMaxPasses);
-    *S = (int)std::min<int64_t>(st, span);
+    if (compact == kOnePass || st >= span) {
+        *S = 0;
+        *P = 1;
+        return;
+    }
+    *S = (int)st;
     *P = (int)((span + *S - 1) / *S);
 }
 
@@ -468,7 +475,7 @@ int enqueue_ws(const mt_params *p, const Call &c, hipStream_t s, unsigned long l
                char *lists, double *partial) {
     int S = 0, P = 1;
     if (p->mode == MT_MODE_PERSISTENT)
-        pass_plan(p->max_steps, lists ? c.compact : p->max_steps + 1, &S, &P);
+        pass_plan(p->max_steps, lists ? c.compact : kOnePass, &S, &P);
     if (c.R.solo) {
         MT_HIP(mt::launch_variant_waves(g.T, c.R, c.io, c.block, s));
     } else if (p->mode == MT_MODE_PERSISTENT && (P > 1 || !c.R.room)) {
@@ -547,7 +554,7 @@ int prepare_workspace(const mt_params *p, const Call &c) {
 // without a map or blocks.
 void shape_small(const mt_params *p, Call &c) {
     const int64_t wave = 64, simds = 4 * (int64_t)g.cu_count;
-    if (p->mode == MT_MODE_PERSISTENT && c.lanes <= 5 * wave * simds) c.compact = p->max_steps + 1;
+    if (p->mode == MT_MODE_PERSISTENT && c.lanes <= 5 * wave * simds) c.compact = kOnePass;
     const bool diverging = g.T.field.map != nullptr || g.T.geom.n_poly > 0;
     const int64_t most = wave * simds / (diverging ? 2 : 8);
     if (p->mode == MT_MODE_VARIANT_WAVES || c.R.n_trace > 0 || c.lanes > most) return;

@@ -16,7 +16,7 @@ struct Launch {
     std::string name;
     unsigned grid, block;
     size_t lds;
-    const void *image;      // first word of the first argument
+    const void *image;      // first word of the first argument (transport kernels: the tables)
     bool image_live;
 };
 
@@ -112,6 +112,22 @@ hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, si
     l.image_live = is_live(l.image);
     launches.push_back(l);
     clock_ms += !cheap.empty() && l.name.find(cheap) != std::string::npos ? 1.f : 2.f;
+    return hipSuccess;
+}
+
+static dim3 next_grid, next_block;
+static size_t next_lds;
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t lds, hipStream_t) {
+    next_grid = grid;
+    next_block = block;
+    next_lds = lds;
+    return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *lds, hipStream_t *s) {
+    *grid = next_grid;
+    *block = next_block;
+    *lds = next_lds;
+    *s = nullptr;
     return hipSuccess;
 }
 

@@ -76,3 +76,23 @@ def lone(s, n_mat, blocks, n):
 def test_lone_muons_are_resident_at_once(stub, n_mat, blocks, n):
     """One wave a SIMD, or as many as the staged tables leave room for."""
     _host_stub.run(stub, "tests.test_host_paths", "lone", n_mat, blocks, n)
+
+
+# ---- passes ----------------------------------------------------------------
+def one_pass(s):
+    assert s.histograms(_tables(95, 1)) == 0
+    assert s.geometry(_boxes()) == 0
+    for max_steps in (0, 1, 1000, 2 ** 31 - 1):
+        p = s.params(mode=1, max_steps=max_steps)
+        assert s.propagate(p, 10 ** 6, noalloc=True) == 0       # no lists to park muons in
+        assert [l.name.count("k_pass") for l in s.launches()] == [1], max_steps
+        assert s.propagate(p, 60_000) == 0                      # all resident at once
+        assert len(s.launches()) == 1, max_steps
+        assert s.propagate(s.params(mode=1, max_steps=max_steps, compact_every=2 ** 31 - 1),
+                           10 ** 6) == 0
+        names = [l.name for l in s.launches()]
+        assert len(names) == (1 if max_steps < 2 ** 31 - 1 else 3), (max_steps, names)
+
+
+def test_one_pass_at_any_step_cap(stub):
+    _host_stub.run(stub, "tests.test_host_paths", "one_pass")
