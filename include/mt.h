@@ -21,7 +21,9 @@
  *   - loaders take HOST arrays, deep-copy them into library-owned device
  *     tables and return after the copy; the caller may free its arrays at
  *     once.  Reloading replaces the tables; do not reload while a launch that
- *     reads them may still run;
+ *     reads them may still run.  A loader that fails leaves the loaded tables as
+ *     they were; only where new tables do not fit beside them, the loaded ones
+ *     make room first, and if it fails then none are loaded;
  *   - mt_propagate* take DEVICE pointers owned by the caller and enqueue
  *     work on the caller's HIP stream (NULL = the null stream) without
  *     waiting for it; the buffers must stay alive until that work is done;

@@ -85,14 +85,14 @@ struct TuneEntry {
     int block = 0, compact = 0;
 };
 
-struct State {
-    std::mutex mu;
-    int device = -1;
+// What the loaders set.  A loader works on a copy, which takes the place of the
+// loaded state once everything on the device is there (see publish).
+struct Loaded {
     bool hist_loaded = false, geom_loaded = false;
     int n_mat = 0, n_pbin = 0;
-    int64_t version = 0;  // bumped on every table change
-    DevBuf cdf, guide, alias, nodes, nodesv, image;
-    // host copies of the tables that every block stages in LDS (see build_image)
+    int max_material = -1;
+    AllTables T{};
+    // host copies of the tables that every block stages in LDS (see make_image)
     struct {
         std::vector<double> e2, box4, slab_z, blk;
         std::vector<uint32_t> totals;
@@ -104,10 +104,14 @@ struct State {
         std::vector<mt::BlockRegion> block_region;
         std::vector<mt::BlockPlanes> block_planes;
     } host;
-    DevBuf map, mapv;
+};
+
+struct State : Loaded {
+    std::mutex mu;
+    int device = -1;
+    int64_t version = 0;  // bumped on every table change
+    DevBuf cdf, guide, alias, nodes, nodesv, map, mapv, image;
     DevBuf queue, partial, scratch, gs_lane, lists;
-    AllTables T{};
-    int max_material = -1;
     hipStream_t cap_stream = nullptr;
     std::vector<GraphEntry> graphs;
     std::vector<TuneEntry> tuned;
@@ -220,7 +224,7 @@ bool narrow_bins(const double *p_edges, int n_mat, int n_pbin, int n_loss, int n
 
 // Layout of the tables staged in LDS (histogram and geometry parts, whichever are
 // loaded), and their image.
-std::vector<unsigned char> make_image(bool wide, mt::LdsLayout &L) {
+std::vector<unsigned char> make_image(const Loaded &t, bool wide, mt::LdsLayout &L) {
     int off = 0;
     auto take = [&](int bytes, int align) {
         off = (off + align - 1) / align * align;
@@ -228,14 +232,14 @@ std::vector<unsigned char> make_image(bool wide, mt::LdsLayout &L) {
         off += bytes;
         return o;
     };
-    const int P = g.T.hist.n_pbin, nb = g.T.geom.n_box, ns = g.T.geom.n_slab;
-    const int np = g.T.geom.n_poly;
-    const int nh = g.T.hist.n_mat * P;
+    const int P = t.T.hist.n_pbin, nb = t.T.geom.n_box, ns = t.T.geom.n_slab;
+    const int np = t.T.geom.n_poly;
+    const int nh = t.T.hist.n_mat * P;
     if (!wide) L.off_e2 = take(8 * (P + 1), 16);
     L.off_band = wide ? take(4 * (P + 1), 16) : take(8 * (nh + 1), 16);
     L.off_tot = take(4 * nh, 16);
     L.off_box4 = take(np > 0 ? 0 : 32 * nb, 16);
-    L.off_grid = take(np > 0 ? 8 * g.T.geom.gx * g.T.geom.gy * g.T.geom.gz : 0, 16);
+    L.off_grid = take(np > 0 ? 8 * t.T.geom.gx * t.T.geom.gy * t.T.geom.gz : 0, 16);
     L.off_planes = take(np > 0 ? (int)sizeof(mt::BlockPlanes) * (np + 1) : 0, 16);
     L.off_bf = take(16 * nb, 16);
     L.off_mat = take(4 * nb, 16);
@@ -253,8 +257,8 @@ std::vector<unsigned char> make_image(bool wide, mt::LdsLayout &L) {
     auto put = [&](int o, const auto &v) {
         if (!v.empty()) std::memcpy(img.data() + o, v.data(), v.size() * sizeof(v[0]));
     };
-    const auto &H = g.host;
-    if (g.hist_loaded) {
+    const auto &H = t.host;
+    if (t.hist_loaded) {
         put(L.off_e2, H.e2);
         put(L.off_tot, H.totals);
         // bands or their ends (see kBandLow); the kernels raise them to the run's threshold
@@ -296,21 +300,48 @@ std::vector<unsigned char> make_image(bool wide, mt::LdsLayout &L) {
     return img;
 }
 
-// Both layouts' images, uploaded as one block.
-int build_image() {
+// Makes `next` the loaded state: uploads both layouts' images as one block.  On
+// failure nothing has changed.
+int publish(Loaded &next) {
     mt::LdsLayout L{}, W{};
-    std::vector<unsigned char> img = make_image(false, L);
+    std::vector<unsigned char> img = make_image(next, false, L);
     const size_t wide_at = (img.size() + 255) / 256 * 256;
-    const std::vector<unsigned char> wide = make_image(true, W);
+    const std::vector<unsigned char> wide = make_image(next, true, W);
     img.resize(wide_at);
     img.insert(img.end(), wide.begin(), wide.end());
-    const int rc = g.image.upload(img.data(), img.size());
-    if (rc) return rc;
-    g.T.lds = L;
-    g.T.wide_lds = W;
-    g.T.image = reinterpret_cast<const uint4 *>(g.image.p);
-    g.T.wide_image = g.T.image + wide_at / sizeof(uint4);
+    DevBuf image;
+    const int rc = image.upload(img.data(), img.size());
+    if (rc) {
+        image.release();
+        return rc;
+    }
+    next.T.lds = L;
+    next.T.wide_lds = W;
+    next.T.image = reinterpret_cast<const uint4 *>(image.p);
+    next.T.wide_image = next.T.image + wide_at / sizeof(uint4);
+    std::swap(g.image, image);
+    static_cast<Loaded &>(g) = std::move(next);
+    tables_changed();
+    image.release();
     return MT_OK;
+}
+
+// Allocates n fresh buffers beside those that they will replace (of `loaded` bytes);
+// where that does not fit but would without them, unload() gives those up first.
+template <class F>
+int allocate_beside(DevBuf *fresh, const size_t *bytes, int n, size_t loaded, F &&unload) {
+    for (bool last = false;; last = true) {
+        int rc = MT_OK;
+        size_t sum = 0, room = 0, total = 0;
+        for (int i = 0; i < n; ++i) {
+            sum += bytes[i];
+            if (!rc && bytes[i] > 0) rc = fresh[i].ensure(bytes[i]);
+        }
+        if (!rc) return MT_OK;
+        for (int i = 0; i < n; ++i) fresh[i].release();
+        if (last || (hipMemGetInfo(&room, &total) == hipSuccess && sum > room + loaded)) return rc;
+        unload();
+    }
 }
 
 std::vector<unsigned char> make_key(const void *a, size_t na, const void *b = nullptr,
@@ -831,20 +862,34 @@ int mt_load_histograms_ex(int32_t n_mat, int32_t n_pbin, const double *p_edges, 
     std::vector<double> e2((size_t)n_pbin + 1);
     for (int i = 0; i <= n_pbin; ++i) e2[i] = p_edges[i] * p_edges[i];
     if ((rc = ensure_device())) return rc;
-    if ((rc = g.cdf.upload(cdf.data(), cdf.size() * 4))) return rc;
-    if ((rc = g.guide.upload(guide.data(), guide.size() * sizeof(uint2)))) return rc;
-    if ((rc = g.alias.upload(alias.data(), alias.size() * sizeof(uint2)))) return rc;
-    mt::DevHist &H = g.T.hist;
-    H.cdf = reinterpret_cast<const uint32_t *>(g.cdf.p);
-    H.guide = reinterpret_cast<const uint2 *>(g.guide.p);
-    H.alias = reinterpret_cast<const uint2 *>(g.alias.p);
+    const void *src[3] = {cdf.data(), guide.data(), alias.data()};
+    const size_t bytes[3] = {cdf.size() * 4, guide.size() * sizeof(uint2),
+                             alias.size() * sizeof(uint2)};
+    DevBuf *loaded[3] = {&g.cdf, &g.guide, &g.alias}, fresh[3];
+    auto drop = [&](int code) {
+        for (DevBuf &d : fresh) d.release();
+        return code;
+    };
+    rc = allocate_beside(fresh, bytes, 3, g.cdf.bytes + g.guide.bytes + g.alias.bytes, [&] {
+        g.hist_loaded = false;
+        g.T.hist = mt::DevHist{};
+        for (DevBuf *d : loaded) d->release();
+        tables_changed();
+    });
+    for (int i = 0; i < 3 && !rc; ++i) rc = fresh[i].upload(src[i], bytes[i]);
+    if (rc) return drop(rc);
+    Loaded next = g;
+    mt::DevHist &H = next.T.hist;
+    H.cdf = reinterpret_cast<const uint32_t *>(fresh[0].p);
+    H.guide = reinterpret_cast<const uint2 *>(fresh[1].p);
+    H.alias = reinterpret_cast<const uint2 *>(fresh[2].p);
     H.n_mat = n_mat;
     H.n_pbin = n_pbin;
     H.n_loss = n_loss;
     H.n_scat = n_scat;
     H.n_cells = (int32_t)K;
     H.gbits = gbits;
-    g.T.narrow = narrow_bins(p_edges, n_mat, n_pbin, n_loss, n_scat, loss_lo, loss_hi, log_l,
+    next.T.narrow = narrow_bins(p_edges, n_mat, n_pbin, n_loss, n_scat, loss_lo, loss_hi, log_l,
                              cdf.data());
     H.nscat_f = (float)n_scat;
     H.nscat_inv = 1.0f / (float)n_scat;
@@ -857,14 +902,14 @@ int mt_load_histograms_ex(int32_t n_mat, int32_t n_pbin, const double *p_edges, 
     H.scat_w = (float)((s1 - s0) / n_scat);
     H.log_loss = log_l ? 1 : 0;
     H.log_scat = log_s ? 1 : 0;
-    g.n_mat = n_mat;
-    g.n_pbin = n_pbin;
-    g.hist_loaded = true;
-    g.host.e2 = std::move(e2);
-    g.host.totals = std::move(totals);
-    if ((rc = build_image())) return rc;
-    tables_changed();
-    return MT_OK;
+    next.n_mat = n_mat;
+    next.n_pbin = n_pbin;
+    next.hist_loaded = true;
+    next.host.e2 = std::move(e2);
+    next.host.totals = std::move(totals);
+    if ((rc = publish(next))) return drop(rc);
+    for (int i = 0; i < 3; ++i) std::swap(*loaded[i], fresh[i]);
+    return drop(MT_OK);
 }
 
 // One axis of a region [lo, hi]: centre and 1 / half width.  The relative 2^-14
@@ -965,29 +1010,28 @@ int mt_load_geometry(int32_t n_box, const double *box, const int32_t *material, 
     for (int s = 0; s < n_slab; ++s)
         region_axis(slab_z[s], std::min(slab_z[s + 1], world[2]), &sreg[s].zc, &sreg[s].iz);
     if ((rc = ensure_device())) return rc;
-    mt::DevGeom &G = g.T.geom;
+    Loaded next = g;
+    mt::DevGeom &G = next.T.geom;
     G.n_box = n_box;
     G.n_poly = 0;
     G.n_slab = n_slab;
     G.n_mag = n_mag;
     G.disjoint = disjoint ? 1 : 0;
     G.vertical = all_vertical(bf) ? 1 : 0;
-    g.host.box4 = std::move(box4);
-    g.host.bfield = std::move(bf);
-    g.host.material = std::move(mat);
-    g.host.magnet = std::move(mag);
-    g.host.slab_z = std::move(slab_z);
-    g.host.slab_mask = std::move(mask);
-    g.host.box_region = std::move(breg);
-    g.host.slab_region = std::move(sreg);
+    next.host.box4 = std::move(box4);
+    next.host.bfield = std::move(bf);
+    next.host.material = std::move(mat);
+    next.host.magnet = std::move(mag);
+    next.host.slab_z = std::move(slab_z);
+    next.host.slab_mask = std::move(mask);
+    next.host.box_region = std::move(breg);
+    next.host.slab_region = std::move(sreg);
     G.x_max = world[0];
     G.y_max = world[1];
     G.z_max = world[2];
-    g.max_material = max_mat;
-    g.geom_loaded = true;
-    if ((rc = build_image())) return rc;
-    tables_changed();
-    return MT_OK;
+    next.max_material = max_mat;
+    next.geom_loaded = true;
+    return publish(next);
 }
 
 // Convex blocks (Section "Simulation", item 1).  Each block is stored as
@@ -1271,26 +1315,27 @@ int mt_load_blocks(int32_t n, const double *block, const int32_t *material, cons
                     grid[((size_t)k * dims[1] + j) * dims[0] + i] |= 1ull << b;
     }
     if ((rc = ensure_device())) return rc;
+    Loaded next = g;
     std::vector<double> zr;
     for (int b = 0; b < n; ++b) {
         zr.push_back(block[18 * b]);
         zr.push_back(block[18 * b + 1]);
     }
-    z_slabs(zr, g.host.slab_z, g.host.slab_mask);
-    mt::DevGeom &G_ = g.T.geom;
+    z_slabs(zr, next.host.slab_z, next.host.slab_mask);
+    mt::DevGeom &G_ = next.T.geom;
     G_.n_box = n;
     G_.n_poly = n;
-    G_.n_slab = (int)g.host.slab_mask.size();
+    G_.n_slab = (int)next.host.slab_mask.size();
     G_.n_mag = n_mag;
     G_.disjoint = 0;
     G_.vertical = all_vertical(bf) ? 1 : 0;
-    g.host.blk = std::move(rec);
-    g.host.grid = std::move(grid);
-    g.host.block_region = std::move(preg);
-    g.host.block_planes = std::move(planes);
-    g.host.bfield = std::move(bf);
-    g.host.material = std::move(mat);
-    g.host.magnet = std::move(mag);
+    next.host.blk = std::move(rec);
+    next.host.grid = std::move(grid);
+    next.host.block_region = std::move(preg);
+    next.host.block_planes = std::move(planes);
+    next.host.bfield = std::move(bf);
+    next.host.material = std::move(mat);
+    next.host.magnet = std::move(mag);
     G_.gx = dims[0];
     G_.gy = dims[1];
     G_.gz = dims[2];
@@ -1302,11 +1347,9 @@ int mt_load_blocks(int32_t n, const double *block, const int32_t *material, cons
     G_.x_max = world[0];
     G_.y_max = world[1];
     G_.z_max = world[2];
-    g.max_material = max_mat;
-    g.geom_loaded = true;
-    if ((rc = build_image())) return rc;
-    tables_changed();
-    return MT_OK;
+    next.max_material = max_mat;
+    next.geom_loaded = true;
+    return publish(next);
 }
 
 int mt_load_field(int32_t nx, int32_t ny, int32_t nz, const double *lo, const double *hi,
@@ -1587,15 +1630,11 @@ void mt_release(void) {
                       &g.queue, &g.partial,
                       &g.scratch, &g.gs_lane, &g.lists})
         b->release();
-    g.host = {};
     if (g.cap_stream) {
         (void)hipStreamDestroy(g.cap_stream);
         g.cap_stream = nullptr;
     }
-    g.T = AllTables{};
-    g.hist_loaded = g.geom_loaded = false;
-    g.n_mat = g.n_pbin = 0;
-    g.max_material = -1;
+    static_cast<Loaded &>(g) = Loaded{};
     g.tuned.clear();
     g.opt_guide_bits = 0;
     g.opt_adjoint_block = 64;

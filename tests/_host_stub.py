@@ -36,7 +36,7 @@ class Launch:
     grid: int
     block: int
     lds: int
-    image_live: bool
+    tables_live: bool
 
 
 class Stub:

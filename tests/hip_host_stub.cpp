@@ -16,8 +16,7 @@ struct Launch {
     std::string name;
     unsigned grid, block;
     size_t lds;
-    const void *image;      // first word of the first argument (transport kernels: the tables)
-    bool image_live;
+    bool tables_live;       // transport kernels: the tables that the argument starts with
 };
 
 std::map<char *, size_t> live;
@@ -48,12 +47,12 @@ size_t stub_peak(int reset) {
 void stub_cheap(const char *name) { cheap = name; }
 int stub_launches() { return (int)launches.size(); }
 void stub_clear() { launches.clear(); }
-const char *stub_launch(int i, unsigned *grid, unsigned *block, size_t *lds, int *image_live) {
+const char *stub_launch(int i, unsigned *grid, unsigned *block, size_t *lds, int *tables_live) {
     const Launch &l = launches[i];
     *grid = l.grid;
     *block = l.block;
     *lds = l.lds;
-    *image_live = l.image_live;
+    *tables_live = l.tables_live;
     return l.name.c_str();
 }
 
@@ -90,6 +89,11 @@ hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) {
     return hipSuccess;
 }
 
+hipError_t hipMemGetInfo(size_t *room, size_t *total) {
+    *room = limit - used;
+    *total = limit;
+    return hipSuccess;
+}
 hipError_t hipGetDevice(int *d) { return *d = 0, hipSuccess; }
 hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600 *p, int) {
     memset(p, 0, sizeof(*p));
@@ -108,8 +112,11 @@ hipError_t hipGetSymbolAddress(void **p, const void *) {
 
 hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, size_t lds,
                            hipStream_t) {
-    Launch l{names.count(f) ? names[f] : "", grid.x, block.x, lds, *(const void **)args[0], false};
-    l.image_live = is_live(l.image);
+    Launch l{names.count(f) ? names[f] : "", grid.x, block.x, lds, true};
+    const void *const *t = (const void *const *)args[0];     // image, cdf, guide, alias
+    for (const char *k : {"k_plain", "k_pass", "k_variant_waves"})
+        if (l.name.find(std::string(k) + "I") != std::string::npos)
+            l.tables_live = is_live(t[0]) && is_live(t[1]) && is_live(t[2]) && is_live(t[3]);
     launches.push_back(l);
     clock_ms += !cheap.empty() && l.name.find(cheap) != std::string::npos ? 1.f : 2.f;
     return hipSuccess;

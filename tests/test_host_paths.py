@@ -96,3 +96,63 @@ def one_pass(s):
 
 def test_one_pass_at_any_step_cap(stub):
     _host_stub.run(stub, "tests.test_host_paths", "one_pass")
+
+
+# ---- loaders that fail -----------------------------------------------------
+def failing_loads(s, kind):
+    """Each allocation and each copy of a load fails in turn: what was loaded keeps
+    working, with its own tables."""
+    small, large = _tables(20, 1), _tables(95, 8)
+    loads = {"histograms": lambda: s.histograms(large), "boxes": lambda: s.geometry(_boxes(60)),
+             "blocks": lambda: s.geometry(_blocks(60))}
+    runs = [s.params(mode=1, block=256, sampler=k) for k in (0, 1)]
+
+    def launch():
+        for p in runs:
+            assert s.propagate(p, 500_000) == 0
+        got = s.launches()
+        assert got and all(l.tables_live for l in got)
+        return got
+
+    assert s.histograms(small) == 0 and s.geometry(_boxes(5)) == 0
+    launch()
+    used, failures = s.c.stub_used(), 0
+    for fail in (s.c.stub_fail_alloc, s.c.stub_fail_copy):
+        for nth in range(10):
+            assert s.histograms(small) == 0 and s.geometry(_boxes(5)) == 0
+            before = launch()
+            fail(nth)
+            rc = loads[kind]()
+            fail(-1)
+            if rc == 0:
+                break
+            failures += 1
+            assert rc in (-5, -6)
+            assert launch() == before, (fail, nth)
+    assert failures >= 2
+    assert s.histograms(small) == 0 and s.geometry(_boxes(5)) == 0
+    assert s.c.stub_used() == used
+
+
+@pytest.mark.parametrize("kind", ["histograms", "boxes", "blocks"])
+def test_a_load_that_fails_leaves_what_was_loaded(stub, kind):
+    _host_stub.run(stub, "tests.test_host_paths", "failing_loads", kind)
+
+
+def tight_histograms(s):
+    assert s.histograms(_tables(95, 8)) == 0 and s.geometry(_boxes(5)) == 0
+    p = s.params(mode=0, block=256)
+    assert s.propagate(p, 500_000) == 0
+    before = s.launches()
+    used = s.c.stub_used()
+    s.c.stub_limit(used + 50_000)                  # no room for two sets of tables
+    assert s.histograms(_tables(95, 100)) == -7    # (more than the documented limit)
+    assert s.histograms(_tables(95, 40)) == -5     # too large by themselves: the loaded ones stay
+    assert s.propagate(p, 500_000) == 0 and s.launches() == before
+    assert s.histograms(_tables(95, 8)) == 0       # in place of the loaded ones
+    assert s.propagate(p, 500_000) == 0 and s.launches() == before
+    assert s.c.stub_used() == used
+
+
+def test_histograms_that_do_not_fit_beside_the_loaded_ones(stub):
+    _host_stub.run(stub, "tests.test_host_paths", "tight_histograms")
