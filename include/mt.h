@@ -197,7 +197,8 @@ int mt_load_blocks(int32_t n, const double *block, const int32_t *material, cons
  * and rounded to float) in one 128-byte record (128 (nx-1)(ny-1)(nz-1)
  * bytes), so that a trilinear lookup reads one cache line, and a node-major
  * copy (16 nx ny nz bytes) for the nearest node; a vertical map (bx = bz = 0 at
- * every node) also has both for by alone (32 and 4 bytes).
+ * every node) also has both for by alone (32 and 4 bytes), unless only the
+ * general ones fit.
  * Limits: nx ny nz < 2^31, nx < 2^24 and ny nz < 2^24 (MT_ERR_LIMIT).
  * Errors: MT_ERR_INVALID_ARG (also when a coefficient overflows float, which
  * needs values near FLT_MAX), MT_ERR_OOM, MT_ERR_HIP.

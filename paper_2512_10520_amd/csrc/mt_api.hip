@@ -1352,6 +1352,28 @@ int mt_load_blocks(int32_t n, const double *block, const int32_t *material, cons
     return publish(next);
 }
 
+// Lowest cell with an interpolation coefficient beyond single precision, or the
+// number of cells (the formulas of k_map_cells).
+static size_t overflowing_cell(size_t nx, size_t ny, size_t nz, const float *b) {
+    const size_t cx = nx - 1, cy = ny - 1, cz = nz - 1;
+    for (size_t cell = 0; cell < cx * cy * cz; ++cell) {
+        const size_t i = cell % cx, j = cell / cx % cy, k = cell / (cx * cy);
+        for (int a = 0; a < 3; ++a) {
+            double C[8];                             // corner c = dx + 2 dy + 4 dz
+            for (size_t c = 0; c < 8; ++c)
+                C[c] = b[3 * (((k + (c >> 2)) * ny + (j + ((c >> 1) & 1))) * nx + (i + (c & 1))) + a];
+            for (double q : {C[0], C[1] - C[0], C[2] - C[0], C[4] - C[0],
+                             C[3] - C[1] - C[2] + C[0], C[5] - C[1] - C[4] + C[0],
+                             C[6] - C[2] - C[4] + C[0],
+                             C[7] - C[3] - C[5] - C[6] + C[1] + C[2] + C[4] - C[0]})
+                if (!std::isfinite((float)q)) return cell;
+        }
+    }
+    return cx * cy * cz;
+}
+
+constexpr size_t kMapPiece = (size_t)1 << 20;
+
 int mt_load_field(int32_t nx, int32_t ny, int32_t nz, const double *lo, const double *hi,
                   const float *b) {
     std::lock_guard<std::mutex> lk(g.mu);
@@ -1384,50 +1406,72 @@ int mt_load_field(int32_t nx, int32_t ny, int32_t nz, const double *lo, const do
                                   "node indices are formed with 24-bit products)");
     const size_t n_nodes = (size_t)nx * ny * nz;
     bool vertical = true;
+    float largest = 0.0f;
     for (size_t i = 0; i < 3 * n_nodes; ++i) {
         if (!std::isfinite(b[i]))
             return fail(MT_ERR_INVALID_ARG, "field map value %zu (node %zu, component %zu) is "
                                             "not finite", i, i / 3, i % 3);
         if (i % 3 != 1 && b[i] != 0.0f) vertical = false;
+        largest = std::max(largest, std::fabs(b[i]));
     }
-    // The tables are formed on the device from the node values (launch_map_tables);
-    // they replace the loaded map only once they are known to be good.
+    // a coefficient is a sum of at most 8 values
+    if (largest > std::numeric_limits<float>::max() / 16) {
+        const size_t cell = overflowing_cell(nx, ny, nz, b);
+        if (cell < cells)
+            return fail(MT_ERR_INVALID_ARG, "field map cell (%zu, %zu, %zu): an interpolation "
+                                            "coefficient overflows single precision",
+                        cell % cx, cell / cx % cy, cell / (cx * cy));
+    }
+    // The tables are formed on the device, from the node values in pieces of
+    // kMapPiece nodes.  They take the place of the loaded map when they are whole;
+    // where they do not fit beside it the loaded map makes room first, and a vertical
+    // map then does without its own tables (the general ones give the same field).
     if ((rc = ensure_device())) return rc;
-    DevBuf raw, bad, map, mapv, nodes, nodesv;
+    DevBuf *loaded[4] = {&g.map, &g.nodes, &g.mapv, &g.nodesv}, fresh[5];
+    size_t bytes[5] = {cells * 8 * sizeof(float4), n_nodes * sizeof(float4),
+                       vertical ? cells * 2 * sizeof(float4) : 0,
+                       vertical ? n_nodes * sizeof(float) : 0,
+                       std::min(n_nodes, kMapPiece) * 3 * sizeof(float)};
     auto drop = [&](int code) {
-        for (DevBuf *d : {&raw, &bad, &map, &mapv, &nodes, &nodesv}) d->release();
+        for (DevBuf &d : fresh) d.release();
         return code;
     };
-    const unsigned long long none = ~0ull;
-    unsigned long long first = none;
-    if ((rc = raw.upload(b, 3 * n_nodes * sizeof(float))) || (rc = bad.upload(&none, sizeof(none))) ||
-        (rc = map.ensure(cells * 8 * sizeof(float4))) ||
-        (rc = nodes.ensure(n_nodes * sizeof(float4))) ||
-        (vertical && (rc = mapv.ensure(cells * 2 * sizeof(float4)))) ||
-        (vertical && (rc = nodesv.ensure(n_nodes * sizeof(float)))))
-        return drop(rc);
-    const hipError_t e = mt::launch_map_tables(
-        reinterpret_cast<const float *>(raw.p), nx, ny, nz, reinterpret_cast<float4 *>(nodes.p),
-        reinterpret_cast<float *>(nodesv.p), reinterpret_cast<float4 *>(map.p),
-        reinterpret_cast<float4 *>(mapv.p), reinterpret_cast<unsigned long long *>(bad.p), nullptr);
-    if (e != hipSuccess || hipMemcpy(&first, bad.p, sizeof(first), hipMemcpyDeviceToHost) != hipSuccess)
-        return drop(fail(MT_ERR_HIP, "building the field map tables failed: %s",
-                         hipGetErrorString(e != hipSuccess ? e : hipGetLastError())));
-    if (first != none)
-        return drop(fail(MT_ERR_INVALID_ARG, "field map cell (%zu, %zu, %zu): an interpolation "
-                                             "coefficient overflows single precision",
-                         (size_t)first % cx, (size_t)first / cx % cy, (size_t)first / (cx * cy)));
-    std::swap(map, g.map);
-    std::swap(mapv, g.mapv);
-    std::swap(nodes, g.nodes);
-    std::swap(nodesv, g.nodesv);
-    drop(MT_OK);
+    auto unload = [&] {
+        for (DevBuf *d : loaded) d->release();
+        g.T.field = mt::DevField{};
+        tables_changed();
+    };
+    size_t loaded_bytes = 0;
+    for (DevBuf *d : loaded) loaded_bytes += d->bytes;
+    rc = allocate_beside(fresh, bytes, 5, loaded_bytes, unload);
+    if (rc && vertical) {
+        bytes[2] = bytes[3] = 0;
+        rc = allocate_beside(fresh, bytes, 5, loaded_bytes, unload);
+    }
+    if (rc) return drop(rc);
+    float4 *map = reinterpret_cast<float4 *>(fresh[0].p), *nodes = reinterpret_cast<float4 *>(fresh[1].p);
+    float4 *mapv = reinterpret_cast<float4 *>(fresh[2].p);
+    float *nodesv = reinterpret_cast<float *>(fresh[3].p);
+    for (size_t at = 0; at < n_nodes; at += kMapPiece) {
+        const size_t n = std::min(kMapPiece, n_nodes - at);
+        if ((rc = fresh[4].upload(b + 3 * at, n * 3 * sizeof(float)))) return drop(rc);
+        const hipError_t e = mt::launch_map_nodes(reinterpret_cast<const float *>(fresh[4].p),
+                                                  (int64_t)n, nodes + at,
+                                                  nodesv ? nodesv + at : nullptr, nullptr);
+        if (e != hipSuccess) return drop(fail(MT_ERR_HIP, "building the field map failed: %s",
+                                              hipGetErrorString(e)));
+    }
+    hipError_t e = mt::launch_map_cells(nodes, nx, ny, nz, map, mapv, nullptr);
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+    if (e != hipSuccess)
+        return drop(fail(MT_ERR_HIP, "building the field map failed: %s", hipGetErrorString(e)));
+    for (int i = 0; i < 4; ++i) std::swap(*loaded[i], fresh[i]);
     mt::DevField &F = g.T.field;
-    F.map = reinterpret_cast<const float4 *>(g.map.p);
-    F.nodes = reinterpret_cast<const float4 *>(g.nodes.p);
-    F.mapv = reinterpret_cast<const float4 *>(g.mapv.p);
-    F.nodesv = reinterpret_cast<const float *>(g.nodesv.p);
-    F.vertical = vertical ? 1 : 0;
+    F.map = map;
+    F.nodes = nodes;
+    F.mapv = mapv;
+    F.nodesv = nodesv;
+    F.vertical = mapv ? 1 : 0;
     F.nx = nx;
     F.ny = ny;
     F.nz = nz;
@@ -1439,7 +1483,7 @@ int mt_load_field(int32_t nx, int32_t ny, int32_t nz, const double *lo, const do
         F.off[a] = -lo[a] * F.inv_d[a];
     }
     tables_changed();
-    return MT_OK;
+    return drop(MT_OK);
 }
 
 int mt_propagate(const mt_params *params, int64_t n, const mt_muons *in, mt_muons *out,

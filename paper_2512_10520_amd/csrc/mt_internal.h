@@ -216,11 +216,12 @@ hipError_t launch_pass(const AllTables &T, const DevRun &R, const DevIO &io, int
 // Variant-wave form: groups of 2^R.share_shift lanes hold variants of one muon.
 hipError_t launch_variant_waves(const AllTables &T, const DevRun &R, const DevIO &io, int block,
                                hipStream_t s);
-// Field map tables from the node values (device pointers; nodesv and mapv may be
-// nullptr).  *bad, set to ~0 beforehand, receives the lowest cell whose
-// coefficients overflow float.
-hipError_t launch_map_tables(const float *b, int nx, int ny, int nz, float4 *nodes, float *nodesv,
-                             float4 *map, float4 *mapv, unsigned long long *bad, hipStream_t s);
+// Field map tables (device pointers; nodesv and mapv may be nullptr): the node
+// tables of n node values, and from them the cells'.
+hipError_t launch_map_nodes(const float *b, int64_t n, float4 *nodes, float *nodesv,
+                            hipStream_t s);
+hipError_t launch_map_cells(const float4 *nodes, int nx, int ny, int nz, float4 *map, float4 *mapv,
+                            hipStream_t s);
 hipError_t launch_queue_reset(unsigned long long *queue, double *zero, int64_t n_zero,
                               hipStream_t s);
 hipError_t launch_adjoint(const AllTables &T, const DevRun &R, const DevIO &io,

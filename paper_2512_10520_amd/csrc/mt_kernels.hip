@@ -2184,16 +2184,14 @@ __global__ void k_map_nodes(const float *b, int64_t n, float4 *nodes, float *nod
 }
 
 // One thread per cell: the coefficients of its trilinear interpolant (see
-// CellPoly), formed in FP64 from the 8 corner values and rounded.  The lowest
-// cell with a coefficient that overflows float goes to *bad.
-__global__ void k_map_cells(const float4 *nodes, int nx, int ny, int nz, float4 *map, float4 *mapv,
-                            unsigned long long *bad) {
+// CellPoly), formed in FP64 from the 8 corner values and rounded.
+__global__ void k_map_cells(const float4 *nodes, int nx, int ny, int nz, float4 *map,
+                            float4 *mapv) {
     const int64_t cell = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t cx = nx - 1, cy = ny - 1;
     if (cell >= cx * cy * (nz - 1)) return;
     const int64_t i = cell % cx, j = cell / cx % cy, k = cell / (cx * cy);
     float kc[3][8];
-    bool ok = true;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         double C[8];                             // corner c = dx + 2 dy + 4 dz
@@ -2211,12 +2209,8 @@ __global__ void k_map_cells(const float4 *nodes, int nx, int ny, int nz, float4 
                              C[6] - C[2] - C[4] + C[0],
                              C[7] - C[3] - C[5] - C[6] + C[1] + C[2] + C[4] - C[0]};
 #pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            kc[a][c] = (float)q[c];
-            ok = ok && isfinite(kc[a][c]);
-        }
+        for (int c = 0; c < 8; ++c) kc[a][c] = (float)q[c];
     }
-    if (!ok) atomicMin(bad, (unsigned long long)cell);
 #pragma unroll
     for (int c = 0; c < 8; ++c) map[cell * 8 + c] = make_float4(kc[0][c], kc[1][c], kc[2][c], 0.f);
     if (mapv) {
@@ -2435,13 +2429,18 @@ hipError_t launch_variant_waves(const AllTables &T, const DevRun &R, const DevIO
     return hipLaunchKernel(fn, dim3(grid), dim3(block), args, lds, s);
 }
 
-hipError_t launch_map_tables(const float *b, int nx, int ny, int nz, float4 *nodes, float *nodesv,
-                             float4 *map, float4 *mapv, unsigned long long *bad, hipStream_t s) {
-    const int64_t n = (int64_t)nx * ny * nz, cells = (int64_t)(nx - 1) * (ny - 1) * (nz - 1);
+hipError_t launch_map_nodes(const float *b, int64_t n, float4 *nodes, float *nodesv,
+                            hipStream_t s) {
     hipLaunchKernelGGL(k_map_nodes, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, b, n, nodes,
                        nodesv);
+    return hipGetLastError();
+}
+
+hipError_t launch_map_cells(const float4 *nodes, int nx, int ny, int nz, float4 *map, float4 *mapv,
+                            hipStream_t s) {
+    const int64_t cells = (int64_t)(nx - 1) * (ny - 1) * (nz - 1);
     hipLaunchKernelGGL(k_map_cells, dim3((unsigned)((cells + 255) / 256)), dim3(256), 0, s, nodes,
-                       nx, ny, nz, map, mapv, bad);
+                       nx, ny, nz, map, mapv);
     return hipGetLastError();
 }
 

@@ -80,6 +80,13 @@ class Stub:
         return fn(len(mat), vol.ctypes.data, mat.ctypes.data, bb.ctypes.data, mag.ctypes.data,
                   g.n_mag, world.ctypes.data)
 
+    def field(self, b):
+        import numpy as np
+        b = np.ascontiguousarray(b, np.float32)
+        lo, hi = np.zeros(3), np.ones(3)
+        return self.L.mt_load_field(b.shape[2], b.shape[1], b.shape[0], lo.ctypes.data,
+                                    hi.ctypes.data, b.ctypes.data)
+
     def params(self, **kw):
         p = self.m.MtParams(step_m=0.02, max_steps=1000, p_min=0.2, n_variants=1, r_scale=1.0)
         for k, v in kw.items():

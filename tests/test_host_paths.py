@@ -156,3 +156,61 @@ def tight_histograms(s):
 
 def test_histograms_that_do_not_fit_beside_the_loaded_ones(stub):
     _host_stub.run(stub, "tests.test_host_paths", "tight_histograms")
+
+
+# ---- field maps ------------------------------------------------------------
+def maps(s):
+    assert s.histograms(_tables(95, 1)) == 0 and s.geometry(_boxes(5)) == 0
+    assert s.propagate(s.params(block=256), 500_000) == 0      # (with the workspaces)
+    s.launches()
+    used = s.c.stub_used()
+
+    def field(n, vertical):
+        b = np.zeros((n, n, n, 3), np.float32)
+        b[..., 1] = 1.0
+        b[..., 0] = 0.0 if vertical else 0.5
+        return b
+
+    def mask():
+        assert s.propagate(s.params(block=256), 500_000) == 0
+        (l,) = [l for l in s.launches() if "k_plain" in l.name]
+        return int(l.name.split("ILj")[1].split("E")[0]) & (1 | 256)
+
+    general = 128 * 89 ** 3 + 16 * 90 ** 3              # bytes of a map of 90^3 nodes
+    vertical = general + 32 * 89 ** 3 + 4 * 90 ** 3
+    piece = 12 * 90 ** 3
+    # room for one map and the node values in flight
+    s.c.stub_limit(used + general + piece + 4096)
+    for _ in range(2):
+        assert s.field(field(90, False)) == 0           # replaces one of its size
+        assert mask() == 1
+    assert s.field(field(90, True)) == 0                # its own tables do not fit
+    assert mask() == 1
+    assert s.field(field(95, False)) == -5              # too large by itself: the loaded one stays
+    assert mask() == 1
+    s.c.stub_limit(used + vertical + piece + 4096)
+    for _ in range(2):
+        assert s.field(field(90, True)) == 0
+        assert mask() == 1 | 256
+    # a map that is refused, and copies and allocations that fail
+    b = field(90, True)
+    b[0, 0, 1, 1], b[0, 0, 0, 1] = 3e38, -3e38
+    assert s.field(b) == -1 and mask() == 1 | 256
+    s.c.stub_limit(1 << 40)
+    for fail in (s.c.stub_fail_alloc, s.c.stub_fail_copy):
+        for nth in range(8):
+            fail(nth)
+            rc = s.field(field(60, False))
+            fail(-1)
+            if rc == 0:
+                assert mask() == 1
+                assert s.field(field(90, True)) == 0
+                break
+            assert rc in (-5, -6) and mask() == 1 | 256
+    s.launches()
+    assert s.L.mt_load_field(0, 0, 0, None, None, None) == 0
+    assert mask() == 256 and s.c.stub_used() == used
+
+
+def test_map_that_does_not_fit_beside_the_loaded_one(stub):
+    _host_stub.run(stub, "tests.test_host_paths", "maps")
