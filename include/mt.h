@@ -337,8 +337,10 @@ int mt_propagate_backward(const mt_params *params, int64_t n, const mt_muons *in
 /*
  * Pick block size and pass length of the compacting form by timing
  * candidate launches of this exact call (blocks {64,128,256,512} x steps
- * per pass {32,64,128,256,512, the whole step range}) on the caller's stream; for
- * MT_MODE_VARIANT_WAVES only the block size is tuned (best_compact gets 0).
+ * per pass {32,64,128,256,512, the whole step range}) on the caller's stream; few
+ * muons also in the shape that an untuned call gives them (blocks of 64, the whole
+ * step range); for MT_MODE_VARIANT_WAVES only the block size is tuned (best_compact
+ * gets 0).
  * Outputs are overwritten (every candidate writes identical bits).  The
  * choice is returned and remembered for later calls with compact_every = 0
  * and block = 0 on the same workload shape.

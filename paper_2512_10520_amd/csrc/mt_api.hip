@@ -82,7 +82,7 @@ struct GraphEntry {
 
 struct TuneEntry {
     std::vector<unsigned char> key;
-    int block = 0, compact = 0;
+    int block = 0, compact = 0;     // block 0: the shape of an untuned call is the best one
 };
 
 // What the loaders set.  A loader works on a copy, which takes the place of the
@@ -632,7 +632,7 @@ std::vector<unsigned char> tune_key(const mt_params *p, int64_t n) {
 
 int propagate_impl(const mt_params *p, int64_t n, const mt_muons *in, mt_muons *out,
                    mt_result *res, void *hip_stream, int force_block, int force_compact,
-                   bool allow_graph) {
+                   bool allow_graph, bool allow_tuned) {
     Call c;
     int rc = validate(p, n, in, out, res, false, c);
     if (rc) return rc;
@@ -649,8 +649,9 @@ int propagate_impl(const mt_params *p, int64_t n, const mt_muons *in, mt_muons *
         return MT_OK;
     }
     if (p->block == 0 && p->compact_every == 0 && !force_block && !force_compact) {
-        const TuneEntry *t = p->mode != MT_MODE_PLAIN ? find_tuned(tune_key(p, n)) : nullptr;
-        if (t) {
+        const TuneEntry *t = allow_tuned && p->mode != MT_MODE_PLAIN ? find_tuned(tune_key(p, n))
+                                                                     : nullptr;
+        if (t && t->block) {
             c.block = t->block;
             c.compact = t->compact;
         } else {
@@ -1489,7 +1490,7 @@ int mt_load_field(int32_t nx, int32_t ny, int32_t nz, const double *lo, const do
 int mt_propagate(const mt_params *params, int64_t n, const mt_muons *in, mt_muons *out,
                  mt_result *res, void *hip_stream) {
     std::lock_guard<std::mutex> lk(g.mu);
-    return propagate_impl(params, n, in, out, res, hip_stream, 0, 0, true);
+    return propagate_impl(params, n, in, out, res, hip_stream, 0, 0, true, true);
 }
 
 int mt_propagate_noalloc(const mt_params *params, int64_t n, const mt_muons *in, mt_muons *out,
@@ -1577,6 +1578,8 @@ int mt_propagate_backward(const mt_params *params, int64_t n, const mt_muons *in
     return MT_OK;
 }
 
+constexpr int kWholeRange = 1 << 30;      // steps in a pass: all of them
+
 int mt_autotune(const mt_params *params, int64_t n, const mt_muons *in, mt_muons *out,
                 mt_result *res, void *hip_stream, int32_t *best_block, int32_t *best_compact,
                 float *best_ms) {
@@ -1586,42 +1589,47 @@ int mt_autotune(const mt_params *params, int64_t n, const mt_muons *in, mt_muons
         return fail(MT_ERR_INVALID_ARG, "the autotuner tunes MT_MODE_PERSISTENT and "
                                         "MT_MODE_VARIANT_WAVES launches");
     hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
-    const int blocks[] = {64, 128, 256, 512};
-    const bool waves = params->mode == MT_MODE_VARIANT_WAVES;   // no pass length to tune
-    const std::vector<int> compacts =
-        waves ? std::vector<int>{16} : std::vector<int>{32, 64, 128, 256, 512, 1 << 30};
+    Call c;
+    int rc = validate(params, n, in, out, res, false, c);
+    if (rc) return rc;
+    mt_params p = *params;
+    p.tally = nullptr;
+    p.use_graph = 0;
+    p.block = p.compact_every = 0;
+    // (block, pass length) candidates; (0, 0): the shape of an untuned call, where it is
+    // one of its own (lone muons)
+    std::vector<std::pair<int, int>> candidates;
+    for (int b : {64, 128, 256, 512}) {
+        if (p.mode == MT_MODE_VARIANT_WAVES) candidates.emplace_back(b, 16);    // no passes
+        else for (int cpt : {32, 64, 128, 256, 512, kWholeRange}) candidates.emplace_back(b, cpt);
+    }
+    if (c.lanes > 0) shape_small(&p, c);
+    if (c.R.solo) candidates.emplace_back(0, 0);
     hipEvent_t e0, e1;
     MT_HIP(hipEventCreate(&e0));
     MT_HIP(hipEventCreate(&e1));
     float best = std::numeric_limits<float>::infinity();
     int bb = 256, bc = 16;
-    mt_params p = *params;
-    p.tally = nullptr;
-    p.use_graph = 0;
-    int rc = MT_OK;
-    for (int b : blocks) {
-        for (int cpt : compacts) {
-            rc = propagate_impl(&p, n, in, out, res, hip_stream, b, cpt, false);   // warm-up
-            if (rc) break;
-            if (hipEventRecord(e0, s) != hipSuccess) { rc = fail(MT_ERR_HIP, "hipEventRecord failed"); break; }
-            const int reps = 2;
-            for (int r = 0; r < reps && !rc; ++r)
-                rc = propagate_impl(&p, n, in, out, res, hip_stream, b, cpt, false);
-            if (rc) break;
-            if (hipEventRecord(e1, s) != hipSuccess || hipEventSynchronize(e1) != hipSuccess) {
-                rc = fail(MT_ERR_HIP, "event timing failed");
-                break;
-            }
-            float ms = 0.f;
-            (void)hipEventElapsedTime(&ms, e0, e1);
-            ms /= reps;
-            if (ms < best) {
-                best = ms;
-                bb = b;
-                bc = cpt;
-            }
-        }
+    for (const auto &[b, cpt] : candidates) {
+        rc = propagate_impl(&p, n, in, out, res, hip_stream, b, cpt, false, false);   // warm-up
         if (rc) break;
+        if (hipEventRecord(e0, s) != hipSuccess) { rc = fail(MT_ERR_HIP, "hipEventRecord failed"); break; }
+        const int reps = 2;
+        for (int r = 0; r < reps && !rc; ++r)
+            rc = propagate_impl(&p, n, in, out, res, hip_stream, b, cpt, false, false);
+        if (rc) break;
+        if (hipEventRecord(e1, s) != hipSuccess || hipEventSynchronize(e1) != hipSuccess) {
+            rc = fail(MT_ERR_HIP, "event timing failed");
+            break;
+        }
+        float ms = 0.f;
+        (void)hipEventElapsedTime(&ms, e0, e1);
+        ms /= reps;
+        if (ms < best) {
+            best = ms;
+            bb = b;
+            bc = cpt;
+        }
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
@@ -1636,8 +1644,9 @@ int mt_autotune(const mt_params *params, int64_t n, const mt_muons *in, mt_muons
         }
     if (!found) g.tuned.push_back(TuneEntry{key, bb, bc});
     drop_graphs();
-    if (best_block) *best_block = bb;
-    if (best_compact) *best_compact = waves ? 0 : bc;
+    if (best_block) *best_block = bb ? bb : mt::kWave;
+    if (best_compact)
+        *best_compact = p.mode == MT_MODE_VARIANT_WAVES ? 0 : bb ? bc : kWholeRange;
     if (best_ms) *best_ms = best;
     return MT_OK;
 }

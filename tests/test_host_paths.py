@@ -214,3 +214,26 @@ def maps(s):
 
 def test_map_that_does_not_fit_beside_the_loaded_one(stub):
     _host_stub.run(stub, "tests.test_host_paths", "maps")
+
+
+# ---- autotuner -------------------------------------------------------------
+def tuned(s, n, cheap, want):
+    assert s.histograms(_tables(95, 1)) == 0 and s.geometry(_boxes(5)) == 0
+    s.c.stub_cheap(cheap.encode())
+    for bad in ({"block": 96}, {"compact_every": -1}, {"step_m": 0.0}):
+        assert s.autotune(s.params(mode=1, **bad), n)[0] == -1
+    rc, block, compact, ms = s.autotune(s.params(mode=1), n)
+    assert rc == 0 and block in (64, 128, 256, 512) and compact in (32, 64, 128, 256, 512, 1 << 30)
+    s.launches()
+    assert s.propagate(s.params(mode=1), n) == 0
+    assert want in s.launches()[-1].name
+    assert s.propagate(s.params(mode=1, block=64, compact_every=1 << 30), n) == 0
+    assert "k_variant_waves" not in s.launches()[-1].name     # given shapes are not tuned
+
+
+@pytest.mark.parametrize("n,cheap,want", [(2000, "k_variant_waves", "k_variant_waves"),
+                                          (2000, "k_plain", "k_plain"),
+                                          (500_000, "k_pass", "k_pass")])
+def test_autotune_times_the_untuned_shape(stub, n, cheap, want):
+    """Lone muons are a candidate like the others, and remembered if they win."""
+    _host_stub.run(stub, "tests.test_host_paths", "tuned", n, cheap, want)
