@@ -1509,11 +1509,12 @@ __device__ __forceinline__ void write_ckpt(const Lane &L, int64_t g, int k, cons
 //
 // Convex blocks without a map take 116 registers by themselves; held to 96 (5
 // waves) they keep a few values of the cold lookup in scratch.  That pays where
-// the fifth wave saves a dispatch round or the rounds are many (300 000 muons 4.79
-// -> 3.78 ms, 600 000 7.68 -> 7.41, 10^6 11.28 -> 11.02, 3 10^6 29.5 -> 27.9), not with
-// at most 4 waves a SIMD to run (250 000 3.20 -> 3.36, 100 000 2.49 -> 2.66) or 5
-// to 8 (400 000 5.83 -> 5.97, 500 000 6.69 -> 6.74): those run the kernels of
-// kRoom.  Nor with aliases (10^6 10.29 -> 10.52).
+// the fifth wave saves a dispatch round (300 000 muons 4.79 -> 3.78 ms) and past 8
+// waves a SIMD, where blocks end at many times (530 000 7.01 -> 6.45, 655 361 7.75 ->
+// 7.14, 780 000 8.68 -> 8.51, 10^6 11.15 -> 10.91, 3 10^6 29.5 -> 27.9; of 15 sizes
+// only 700 000 lost, 8.08 -> 8.21), not with at most 4 waves a SIMD to run (250 000
+// 3.20 -> 3.36, 100 000 2.49 -> 2.66) or 5 to 8 (400 000 5.83 -> 5.97, 500 000 6.69 ->
+// 6.74): those run the kernels of kRoom.  Nor with aliases (10^6 10.29 -> 10.52).
 // ---------------------------------------------------------------------------
 constexpr bool blocks_alone(unsigned F) { return (F & kPoly) && !(F & (kMap | kAlias)); }
 
@@ -1672,8 +1673,14 @@ k_pass(KArgs A) {
 // lanes belongs to one muon that its first lane carries; the others only form
 // its random words, one step of G each.
 // ---------------------------------------------------------------------------
+//
+// Convex blocks without a map: the kernel that forms draws ahead runs few waves (lone
+// muons, and launches of at most 5 waves a SIMD) and takes the registers it wants;
+// the other is held to 5 waves, as the plain form is (8 variants of 50 000 muons 3.60 ->
+// 3.48 ms, 16 of 50 000 5.52 -> 5.02, 64 of 100 000 28.4 -> 24.6; 16 of 22 000, 5.4 waves
+// a SIMD, 2.90 and 2.91).
 constexpr int waves_min_waves(unsigned F, bool ahead) {
-    if ((F & kPoly) && !(F & kMap)) return 1;     // lone muons (few waves) run these too
+    if ((F & kPoly) && !(F & kMap)) return ahead ? 1 : 5;
     return (F & (kMap | kStages)) ? plain_min_waves(F) : (F & kVert) && !ahead ? 7 : 6;
 }
 

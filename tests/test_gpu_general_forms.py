@@ -63,3 +63,16 @@ def test_replayed_passes():
         torch.cuda.synchronize()
         for k in ("state", "status", "n_steps", "volume"):
             assert torch.equal(getattr(out, k), getattr(want, k)), (i, k)
+
+
+@pytest.mark.parametrize("over", [0, 1], ids=["draws ahead", "many waves"])
+def test_variant_waves_over_blocks(over):
+    """Both sides of 5 waves a SIMD, where the variant-wave kernel changes."""
+    import torch
+    n = 5 * 4 * 64 * torch.cuda.get_device_properties(0).multi_processor_count // 8 + over
+    wl = W.make_workload("blocks", n_muons=n, n_fill=20_000)
+    wl.run = dataclasses.replace(wl.run, max_steps=300, n_variants=8)
+    a = gpu_run(wl, mode="variant_waves")
+    b = gpu_run(wl, mode="plain", block=256)
+    for k in a:
+        assert np.array_equal(a[k], b[k]), k
