@@ -1995,8 +1995,11 @@ __device__ __forceinline__ int replay_step(Lane &L, int k, const Tables &T, cons
 // The segment's start momenta are kept either in LDS (LDSH) or in a per-lane
 // scratch area in device memory; with a field map the start positions are
 // needed too and always go to the scratch area.
-// Without a map the kernel needs 103 VGPRs (4 waves/SIMD); asking for 5 waves
-// spills a few values kept across the segment loops and runs 3 % faster.
+// Without a map the kernel takes 89 VGPRs for vertical fields and 96 for general
+// ones: 5 waves/SIMD, which the bound keeps (when the kernel took 103, 5 waves with a
+// few values in scratch were 3 % faster than 4; now it gives the same time with the
+// bound and without: design step of 10^6 muons 3.00 ms in the adjoint, 200 000 in
+// general fields 1.34 ms with the forward).
 template <bool MAP, bool LDSH, bool V>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MAP ? 1 : 5)))
 k_adjoint(Tables T, DevRun R, DevIO io, const double *g_out,
