@@ -298,8 +298,8 @@ int mt_propagate(const mt_params *params, int64_t n, const mt_muons *in, mt_muon
  * MT_NOALLOC_SCRATCH_BYTES per device instead of library allocations.  The
  * call makes no hipMalloc or hipFree; it neither captures nor replays a graph
  * (use_graph must be 0), does not checkpoint (ckpt_every must be 0), uses
- * the block given (0 = 256), not the autotuner's choice, and runs the
- * compacting form (MT_MODE_PERSISTENT) as one pass over the whole step range
+ * the block given (0: as an untuned mt_propagate), not the autotuner's choice, and
+ * runs the compacting form (MT_MODE_PERSISTENT) as one pass over the whole step range
  * (the survivor lists of several passes would need 112 bytes per lane).  The tables must have been loaded (loaders do
  * allocate).
  * Limit: with a tally, 256 + 24 * n_variants * min(256, max(1, ceil(n /

@@ -1532,8 +1532,10 @@ int mt_propagate_noalloc(const mt_params *params, int64_t n, const mt_muons *in,
                                           s));
         return MT_OK;
     }
-    // block as given (0: default); no autotuner lookup; the persistent form
-    // runs as one pass (its survivor lists would need 112 bytes per lane)
+    // block as given (0: default, or the shape of few muons, which needs no workspace);
+    // no autotuner lookup; the persistent form runs as one pass (its survivor lists
+    // would need 112 bytes per lane)
+    if (params->block == 0 && params->compact_every == 0) shape_small(params, c);
     return enqueue_ws(params, c, s, queue, nullptr, partial);
 }
 

@@ -237,3 +237,24 @@ def tuned(s, n, cheap, want):
 def test_autotune_times_the_untuned_shape(stub, n, cheap, want):
     """Lone muons are a candidate like the others, and remembered if they win."""
     _host_stub.run(stub, "tests.test_host_paths", "tuned", n, cheap, want)
+
+
+# ---- the entry point that allocates nothing --------------------------------
+def same_kernels(s):
+    assert s.histograms(_tables(95, 1)) == 0 and s.geometry(_boxes(5)) == 0
+    for n in (1, 2000, 8192, 8193, 60_000):
+        for mode in (0, 1, 2):
+            for block in (0, 128):
+                p = s.params(mode=mode, block=block)
+                assert s.propagate(p, n) == 0
+                want = s.launches()
+                used = s.c.stub_used()
+                assert s.propagate(p, n, noalloc=True) == 0
+                got = s.launches()
+                assert s.c.stub_used() == used
+                if mode != 1 or block == 0:         # (given a block, passes need lists)
+                    assert got == want, (n, mode, block)
+
+
+def test_noalloc_launches_the_same_kernels(stub):
+    _host_stub.run(stub, "tests.test_host_paths", "same_kernels")
